@@ -29,13 +29,17 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-I" + INCLUDE, "-I" + CSRC,
 ]
-SOURCES = ["api.hip", "featurize.hip", "prep.hip", "join_mfma.hip", "recheck.hip", "sort.hip", "serve.hip",
+# stream.hip holds its R rows, accumulators and fragments in 224 of a wave's
+# 256 registers; the allocator's reversed local order keeps them there (the
+# default order spills 72 registers of the 256-byte kernel).
+FILE_FLAGS = {"stream.hip": ["-mllvm", "-greedy-reverse-local-assignment=1"]}
+SOURCES = ["api.hip", "featurize.hip", "prep.hip", "join_mfma.hip", "stream.hip", "recheck.hip", "sort.hip", "serve.hip",
            "index.hip", "plan.hip", "peak.hip"]
 
 
 def _compile(src: str) -> str:
     obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
-    cmd = [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [HIPCC, *FLAGS, *FILE_FLAGS.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     out = (r.stdout + r.stderr).replace("'-packed-fp32-ops' is not a recognized feature for this target (ignoring feature)\n", "")
     if r.returncode != 0:

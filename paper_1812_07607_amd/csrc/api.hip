@@ -32,6 +32,8 @@ hipError_t launch_band_seed(const Prep&, int64_t, const float*, int, const float
 namespace dl {
 hipError_t launch_cand_eps(dl_prec, CandParams, hipStream_t, int);
 hipError_t launch_cand_list(dl_prec, CandParams, hipStream_t, int);
+bool stream_applies(dl_prec, int64_t, int64_t, int64_t);
+hipError_t launch_stream_eps(dl_prec, const CandParams&, int64_t, hipStream_t, int);
 hipError_t launch_cand_mark(dl_prec, CandParams, hipStream_t, int);
 hipError_t launch_cand_nearest(dl_prec, CandParams, hipStream_t, int);
 // index.hip
@@ -625,7 +627,10 @@ dl_status eps_core(dl_ctx* c, const EpsJob& J, void* ws, size_t ws_bytes, dl_pai
     p.candp = prec == DL_FP8 ? nullptr : L.candp;  // E4M3 stages no P~ (LDS budget)
     p.ccap = cap;
     p.gate = &L.cnt->invalid;
-    DL_HIP(c, launch_cand_eps(prec, p, st, c->cu_count));
+    if (stream_applies(prec, p.qld, R.n, S.n))
+      DL_HIP(c, launch_stream_eps(prec, p, L.pr.npad, st, c->cu_count));
+    else
+      DL_HIP(c, launch_cand_eps(prec, p, st, c->cu_count));
   }
   const int bj = bits_for(S.n);  // the recheck's keys are i << bj | j
   {

@@ -27,16 +27,10 @@
 // transfer counts.  Workgroups are persistent; tiles are ordered in groups of
 // GM row tiles and dealt to the 8 XCDs in contiguous runs so that each XCD's
 // L2 holds the row tiles of its group while S tiles stream past.
-#include "join_params.hpp"
+#include "cand_device.hpp"
 
 namespace dl {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef int i32x8 __attribute__((ext_vector_type(8)));
-
-constexpr int kThreads = 512;
 constexpr int kWaveM = 128, kWaveN = 64;  // outputs per wave
 constexpr int kRingBytes = 128 * 1024;   // LDS operand ring, all stages
 
@@ -54,31 +48,6 @@ struct Pipe {
   static constexpr int kStages = kRingBytes / (2 * kStageBytes);  // 2 or 4
   static constexpr int kRowsPerDma = 1024 / kCB;                  // rows per 1 KiB transfer
 };
-
-typedef __attribute__((address_space(1))) void gvoid_t;
-typedef __attribute__((address_space(3))) void lvoid_t;
-
-// 16 bytes per lane from global memory into LDS (global_load_lds_dwordx4):
-// lane l's bytes land at lds_dst + 16 l.  Issued as inline assembly so that
-// the compiler's wait-count insertion does not treat the transfer as a
-// write to the stage being read; the kernel orders it explicitly (vmcnt(0)
-// and a barrier before a stage is read or overwritten).
-__device__ inline uint32_t lds_addr(const void* lds_ptr) {
-  return __builtin_amdgcn_readfirstlane((uint32_t)reinterpret_cast<uintptr_t>((const lvoid_t*)lds_ptr));
-}
-// the same with the LDS destination given as a wave-uniform LDS address
-__device__ inline void lds_dma16_at(const void* gsrc, uint32_t m0) {
-  // M0 (the LDS base of the transfer) is an operand bound to the register,
-  // so the compiler knows it is written; one wait state separates the M0
-  // write from the LDS-DMA instruction that reads it.
-  asm volatile(
-      "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %0, off"
-      :
-      : "v"(gsrc), "{m0}"(m0)
-      : "memory");
-}
-__device__ inline void lds_dma16(const void* gsrc, void* lds_dst) { lds_dma16_at(gsrc, lds_addr(lds_dst)); }
 
 // LDS byte offset of logical 16-byte piece c of tile row r in a stage with
 // kCB bytes per row.  The piece is stored at slot c ^ f(r), which spreads the
@@ -173,26 +142,6 @@ __device__ inline bool tile_of(const CandParams& p, int64_t L, int64_t& ti, int6
   tj = g * GM + rem / gm;
   ti = g * GM + rem % gm;
   return ti <= tj && tj < nT;
-}
-
-// Marks a block-uniform 64-bit value as such, so that it lives in scalar
-// registers (the uniformity analysis loses tile indices carried around the
-// persistent loop, and 64-bit vector copies of them crowd out the
-// accumulators).
-__device__ inline int64_t uniform64(int64_t v) {
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)v >> 32));
-  return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-
-// This lane's index (0..63), recomputed from the lane-count instructions at
-// every use.  Lane-derived offsets formed from it are not hoisted out of the
-// persistent loop, where they would stay live beside the 128 accumulator
-// registers and be spilled.
-__device__ inline int fresh_lane() {
-  int l;
-  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
-  return l;
 }
 
 // Block-uniform iterator over this workgroup's tiles: eps (and mark) mode
@@ -491,29 +440,6 @@ __device__ inline void mma_step(f32x4 (&acc)[8][4], const uint8_t* la, const uin
 // -------------------------------------------------------------- epilogues
 // Output element (mb, nb, r) of a lane sits at tile row wm*128 + mb*16 +
 // 4*(lane/16) + r and tile column wn*64 + nb*16 + lane%16.
-constexpr int kQueue = 256;  // staged hits per wave (eps candidates or band entries)
-
-// Appends a wave's staged (i, j) candidates to the global list: one atomic
-// for the whole batch, then coalesced stores.  Positions past the list's
-// capacity are counted but not written (the caller then retries with room).
-// With kP, each record's P~ (qp, staged beside q) goes to p.candp too.
-template <bool kP>
-__device__ inline void flush_eps(const CandParams& p, const uint2* q, const uint32_t* qp, int nq) {
-  const int lane = fresh_lane();
-  unsigned long long base = 0;
-  if (lane == 0) base = atomicAdd(p.ccount, (unsigned long long)nq);
-  base = ((unsigned long long)__builtin_amdgcn_readfirstlane((uint32_t)(base >> 32)) << 32) |
-         __builtin_amdgcn_readfirstlane((uint32_t)base);
-  for (int s = lane; s < nq; s += 64) {
-    const unsigned long long pos = base + (unsigned long long)s;
-    if (pos < (unsigned long long)p.ccap) {
-      p.cand[pos] = q[s];
-      if constexpr (kP)
-        if (p.candp) p.candp[pos] = __uint_as_float(qp[s]);
-    }
-  }
-}
-
 // Eps epilogue.  A fast test (each row's maximum over the wave's four
 // column blocks against the row threshold) lets most waves skip the tile,
 // and records which of the eight row blocks hold a hit.  Only those blocks

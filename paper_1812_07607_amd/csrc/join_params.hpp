@@ -75,6 +75,16 @@ struct CandParams {
   const uint64_t* kmaskB;
 };
 
+// Candidate pass over units of (R block, S stage) (stream.hip).
+struct StreamParams {
+  CandParams c;
+  int64_t npad_r;        // rows of the R operand copy
+  int64_t units;
+  int nst, nrb;          // stages of S, blocks of R
+  int stages_per_block;  // self-join: block rb starts at stage rb * stages_per_block
+  int wr;                // waves along R (8 / wr along S)
+};
+
 // eps-join recheck (recheck.hip).
 struct RecheckParams {
   const float* R; int64_t ldr;

@@ -1,0 +1,475 @@
+// stream.hip -- candidate pass of the eps-join for operand rows of up to 512
+// bytes (d <= 256 in 16-bit formats, d <= 512 in E4M3): R stationary in
+// registers, S streamed through LDS.
+//
+// Paper: section "Query Processing" (Nested Loop Join over all pairs) with
+// the Euclidean predicate of section "Derived Data", recast as the product
+// of the two operand copies on the matrix cores.
+//
+// What bounds a short-row pass is not the matrix cores but what feeds them:
+// a 256 x 256 tile of d = 128 bf16 rows is two K-steps of work, for which
+// both operand tiles go through LDS (128 KiB in, 384 KiB out) and every wave
+// meets a barrier and an epilogue.  Here each wave keeps its rows of R as
+// operand fragments in 128 registers for as long as its workgroup works on
+// them, so only S moves: a strip of 32 S rows is read from LDS once per wave
+// and meets all of the wave's 128 (or 64) R rows, a quarter of the LDS reads
+// per product and an eighth of the operand traffic of the tile form.
+//
+// Layout: 512 threads = 8 waves.  WR of them along R, each with
+// 16 * kNB rows of its own, times 8 / WR along S (the strips of a stage are
+// dealt to them); WR is small when R is, so that a few rows still use every
+// wave.  v_mfma_f32_16x16x32 (E4M3: 16x16x128): the strip's two 16-row blocks
+// are the A operand, the wave's R rows the B operand, so the outputs a lane
+// holds of one R block belong to one R row (lane % 16), and the candidate test
+// is a minimum over registers and one compare with one threshold register per
+// block.  The R fragments carry flipped signs: the accumulator starts at h_j
+// and holds h_j - a.b = -P~ (exactly, each rounding being symmetric), which is
+// compared with -thr_i.  The 16x16 form, not the 32x32 one: on random operands
+// the matrix cores run into the board's power limit, and per product the
+// 16x16x32 instruction moves half the accumulator bits (a loop of them on
+// register operands of unit-vector values: 2.05 PFLOP/s at 2.0 GHz, of
+// 32x32x16 ones 1.80; on constants both reach 2.45).
+//
+// S moves in stages of 24 or 32 KiB into a ring of four (global_load_lds,
+// one 1 KiB transfer per 8 rows x 128 bytes, pieces swizzled as in the tile
+// form).  One barrier per stage; at it every transfer but the one issued
+// next has landed (three stages are in LDS or on the way), so a wave reads
+// fragments ahead across stages, and a wave that stages candidates falls
+// behind its SIMD partner, not behind the barrier.
+//
+// Work is counted in units of (block of WR * 16 kNB rows of R, stage of S),
+// R-major; each workgroup takes one contiguous, equal share of the units, so
+// no last round is part empty and R changes only a few times per workgroup.
+// (Workgroups of one XCD walking S in step, so that its L2 serves them all,
+// gained 1% on the 10^6-row join and lost the even shares: S is read at 2.4
+// TB/s in all, which HBM gives.)
+//
+// Measured (one MI355X): the 10^6 x 10^6, d = 128, bf16 pass 158 ms (1.62
+// PFLOP/s) against the tile form's 238 ms; a loop of the same matrix
+// instructions and LDS reads alone, on such operands, runs at 1.94 PFLOP/s.
+#include <type_traits>
+
+#include "cand_device.hpp"
+
+namespace dl {
+
+template <int kPrec, int kKB>
+struct StreamGeom {
+  static constexpr int kSteps = kKB / 64;                   // 16-byte pieces per lane and 16 rows
+  static constexpr int kUnit = kPrec == DL_FP8 ? 2 : 1;     // pieces per matrix instruction
+  static constexpr int kUnits = kSteps / kUnit;
+  // A fragments held: two units; E4M3, whose units are twice as large, holds
+  // one and takes its two 16-row blocks in turn (each is read again while the
+  // other is multiplied)
+  static constexpr bool kTurns = kPrec == DL_FP8;
+  static constexpr int kWindow = kTurns ? 1 : 2;
+  static constexpr int kNB = kKB <= 256 ? 8 : 4;            // 16-row blocks of R per wave
+  static constexpr int kWaveRows = 16 * kNB;
+  static constexpr int kStageRows = kKB == 128 ? 256 : kKB == 256 ? 128 : 64;
+  static constexpr int kStrips = kStageRows / 32;
+  static constexpr int kStageBytes = kStageRows * kKB;
+  static constexpr int kDma = kStageBytes / 1024 / 8;       // transfers per wave and stage
+  static constexpr int kRowGroups = kStageRows / 8;
+};
+constexpr int kStreamStages = 4;
+
+// c = c0 + x.y over one fragment unit (16-bit: 16x16x32; E4M3: 16x16x128 with
+// the row scales sx and byte kByte of sy)
+template <int kPrec, int kByte>
+__device__ inline void stream_mac(f32x4& c, const f32x4& c0, const uint4* x, const uint4* y, int sx, int sy) {
+  if constexpr (kPrec == DL_BF16) {
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x[0]), __builtin_bit_cast(bf16x8, y[0]), c0,
+                                                0, 0, 0);
+  } else if constexpr (kPrec == DL_FP16) {
+    c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, x[0]), __builtin_bit_cast(f16x8, y[0]), c0, 0,
+                                               0, 0);
+  } else {
+    const i32x8 a{(int)x[0].x, (int)x[0].y, (int)x[0].z, (int)x[0].w, (int)x[1].x, (int)x[1].y, (int)x[1].z, (int)x[1].w};
+    const i32x8 b{(int)y[0].x, (int)y[0].y, (int)y[0].z, (int)y[0].w, (int)y[1].x, (int)y[1].y, (int)y[1].z, (int)y[1].w};
+    c = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c0, 0, 0, 0, sx, kByte, sy);
+  }
+}
+
+__device__ inline float min3(float a, float b, float c) {
+  return __builtin_elementwise_minimum(__builtin_elementwise_minimum(a, b), c);
+}
+
+constexpr int kCmpOLE = 5;  // ordered <= (false for NaN)
+__device__ inline uint64_t mask_le(float a, float b) { return __builtin_amdgcn_fcmpf(a, b, kCmpOLE); }
+
+// A unit's place: R block and S stage, from its index.
+struct UnitAt {
+  int rb, st;
+};
+__device__ inline int stream_first(const StreamParams& p, int rb) { return p.c.self_join ? rb * p.stages_per_block : 0; }
+__device__ inline int64_t stream_prefix(const StreamParams& p, int64_t rb) {
+  return rb * p.nst - (p.c.self_join ? (int64_t)p.stages_per_block * (rb * (rb - 1) / 2) : 0);
+}
+__device__ inline UnitAt stream_unit(const StreamParams& p, int64_t L) {
+  int lo = 0, hi = p.nrb - 1;
+  while (lo < hi) {  // largest rb with prefix(rb) <= L
+    const int mid = (lo + hi + 1) >> 1;
+    if (stream_prefix(p, mid) <= L) lo = mid; else hi = mid - 1;
+  }
+  return {lo, stream_first(p, lo) + (int)(L - stream_prefix(p, lo))};
+}
+
+template <int kPrec, int kKB>
+__global__ __launch_bounds__(kThreads, 1) void stream_eps_kernel(StreamParams p) {
+  using G = StreamGeom<kPrec, kKB>;
+  constexpr bool kFp8 = kPrec == DL_FP8;
+  constexpr int kNB = G::kNB, kUnits = G::kUnits, kW = G::kWindow, kU = G::kUnit;
+  __shared__ __attribute__((aligned(1024))) uint8_t ring[kStreamStages][G::kStageBytes];
+  __shared__ __attribute__((aligned(16))) float side_h[kStreamStages][G::kStageRows];
+  __shared__ __attribute__((aligned(16))) int side_s[kFp8 ? kStreamStages : 1][kFp8 ? G::kStageRows : 4];
+  __shared__ __attribute__((aligned(16))) uint2 eq_lds[kThreads / 64][kQueue];
+  constexpr bool kStageP = !kFp8;  // E4M3 stages no P~ (it is never exact)
+  __shared__ uint32_t eqp_lds[kStageP ? kThreads / 64 : 1][kStageP ? kQueue : 1];
+
+  if (p.c.gate && __builtin_amdgcn_readfirstlane(*p.c.gate)) return;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int r16 = lane & 15, quad = lane >> 4;
+  // this workgroup's share of the units; consecutive shares on one XCD
+  const int ng = gridDim.x;
+  const int slot = (blockIdx.x & 7) * (ng >> 3) + (blockIdx.x >> 3);
+  const int64_t u0 = uniform64(p.units * slot / ng), u1 = uniform64(p.units * (slot + 1) / ng);
+  const int nu = (int)(u1 - u0);
+  if (nu <= 0) return;
+  const int wr = p.wr, ws = 8 / wr;
+  const int rw = wave & (wr - 1), grp = wave / wr;  // rows and strips of this wave
+  const int per = G::kStrips / ws;                  // strips of a stage this wave takes
+
+  UnitAt at = stream_unit(p, u0);
+  int rb = __builtin_amdgcn_readfirstlane(at.rb), st = __builtin_amdgcn_readfirstlane(at.st);
+  int lrb = rb, lst = st;  // of the loader's next unit
+  int lu = 0;
+  // One stage: every wave moves kDma blocks of 8 rows x 128 bytes.  A block is
+  // kept as two 64-byte K-steps of 8 rows x 4 pieces; rows 4..7 of each 16
+  // have the pieces exchanged by 1, 8..11 by 2, 12..15 by 3, so that one
+  // piece of 16 rows touches all 64 banks.
+  auto issue = [&]() {
+    const int buf = lu & (kStreamStages - 1);
+    const int64_t j0 = (int64_t)lst * G::kStageRows;
+    const int l = fresh_lane();
+    const uint8_t* src = p.c.qb + j0 * kKB;
+    const uint32_t dst = lds_addr(&ring[buf][0]) + wave * G::kDma * 1024;
+#pragma unroll
+    for (int t = 0; t < G::kDma; ++t) {
+      const int q = wave * G::kDma + t;
+      const int c = q / G::kRowGroups, r8 = q % G::kRowGroups;
+      const int row = r8 * 8 + ((l >> 2) & 7);
+      const int piece = 4 * (l >> 5) + ((l ^ (row >> 2)) & 3);
+      lds_dma16_at(src + (uint32_t)(row * kKB + c * 128 + piece * 16), dst + t * 1024);
+    }
+    if (wave == 7 && l < G::kStageRows / 4) lds_dma16(p.c.hb + j0 + 4 * l, side_h[buf]);
+    if constexpr (kFp8)
+      if (wave == 6 && l < G::kStageRows / 4) lds_dma16(p.c.sexb + j0 + 4 * l, side_s[buf]);
+    ++lu;
+    if (++lst == p.nst) {
+      ++lrb;
+      lst = stream_first(p, lrb);
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < kStreamStages - 1; ++s)
+    if (lu < nu) issue();
+
+  uint4 rf[kNB][G::kSteps];  // the wave's R rows, signs flipped
+  float nthr[kNB];           // -thr_i of row lane % 16 of each block
+  int rsc[kFp8 ? kNB / 4 : 1];  // E4M3: the rows' scales, four blocks to a register
+  f32x4 acc[kNB][2];
+  uint4 a[kW][2][kU];        // A fragments of the coming units, both 16-row blocks
+  f32x4 ini[2];
+  int ssc[2] = {0, 0};
+  int nq = 0;
+  // row numbers fit 32 bits (relations are shorter than 2^31 rows)
+  uint32_t row0 = 0;  // first R row of this wave
+  uint32_t pj = 0;    // first S row of the strip whose outputs await their test
+  const uint32_t ns = (uint32_t)p.c.nS;
+  auto load_r = [&]() {
+    row0 = (uint32_t)(rb * wr + rw) * G::kWaveRows;
+    const uint32_t flip = kFp8 ? 0x80808080u : 0x80008000u;
+    // rows past the padded relation repeat its last row and never hit
+    const int left = (int)(p.npad_r - (int64_t)row0 < G::kWaveRows ? p.npad_r - (int64_t)row0 : G::kWaveRows);
+    const uint32_t i0 = left > 0 ? row0 : (uint32_t)p.npad_r - 1;
+    const uint8_t* const src = p.c.qa + (int64_t)i0 * kKB;
+    const float* const thr = p.c.thr + i0;
+#pragma unroll
+    for (int b = 0; b < kNB; ++b) {
+      const int l = fresh_lane();
+      const int want = b * 16 + (l & 15);
+      const uint32_t i = want < left ? want : (left > 0 ? left - 1 : 0);
+      const uint32_t off = i * kKB + (l >> 4) * 16;
+#pragma unroll
+      for (int f = 0; f < G::kSteps; ++f) {
+        uint4 v = *reinterpret_cast<const uint4*>(src + (off + f * 64));
+        v.x ^= flip; v.y ^= flip; v.z ^= flip; v.w ^= flip;
+        rf[b][f] = v;
+      }
+      nthr[b] = want < left ? -thr[i] : -INFINITY;
+      if constexpr (kFp8) {
+        const int e = (p.c.sexa[i0 + i] + 127) << (8 * (b & 3));
+        rsc[b / 4] = (b & 3) ? rsc[b / 4] | e : e;
+      }
+    }
+  };
+  // Hits among one block's outputs v (strip pj, rows i, threshold nt) into
+  // the wave's queue, a 16-row block of S at a time (at most 256 hits, one
+  // check of the queue's room).
+  auto take = [&](const f32x4 (&v)[2], uint32_t i, float nt) {
+    const bool edge = pj + 32 > ns || (p.c.self_join && pj <= row0 + G::kWaveRows);
+#pragma unroll
+    for (int sb = 0; sb < 2; ++sb) {
+      const uint32_t j = pj + 16 * sb + 4 * (fresh_lane() >> 4);
+      uint64_t m[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) m[r] = mask_le(v[sb][r], nt);
+      if (edge) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          m[r] &= __builtin_amdgcn_ballot_w64(j + r < ns && (!p.c.self_join || j + r > i));
+      }
+      const int n = __popcll(m[0]) + __popcll(m[1]) + __popcll(m[2]) + __popcll(m[3]);
+      if (n == 0) continue;
+      if (nq + n > kQueue) {
+        flush_eps<kStageP>(p.c, eq_lds[wave], eqp_lds[kStageP ? wave : 0], nq);
+        nq = 0;
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if (!m[r]) continue;
+        if (__builtin_amdgcn_inverse_ballot_w64(m[r])) {
+          const int s = nq + __builtin_amdgcn_mbcnt_hi((uint32_t)(m[r] >> 32),
+                                                       __builtin_amdgcn_mbcnt_lo((uint32_t)m[r], 0));
+          eq_lds[wave][s] = make_uint2(i, j + r);
+          if constexpr (kStageP) eqp_lds[wave][s] = __float_as_uint(-v[sb][r]);
+        }
+        nq += __popcll(m[r]);
+      }
+    }
+  };
+  // The candidate test of a strip's outputs: four minimum instructions and a
+  // compare per block, one branch for all.  The blocks with hits go through
+  // one copy of the staging code (a copy each, and its queue flush, would
+  // overflow the instruction cache).
+  auto test = [&]() {
+    uint64_t any = 0, h[kNB];
+#pragma unroll
+    for (int b = 0; b < kNB; ++b) {
+      const f32x4 &v = acc[b][0], &w = acc[b][1];
+      h[b] = mask_le(min3(min3(v[0], v[1], v[2]), min3(v[3], w[0], w[1]), __builtin_elementwise_minimum(w[2], w[3])),
+                     nthr[b]);
+      any |= h[b];
+    }
+    if (!any) return;
+    uint32_t hb = 0;
+#pragma unroll
+    for (int b = 0; b < kNB; ++b) hb |= (h[b] ? 1u : 0u) << b;
+#pragma unroll 1
+    while (hb) {
+      const int b = __builtin_ctz(hb);
+      hb &= hb - 1;
+      f32x4 v[2];
+      float nt = 0.0f;
+#pragma unroll
+      for (int c = 0; c < kNB; ++c)
+        if (b == c) {
+          v[0] = acc[c][0];
+          v[1] = acc[c][1];
+          nt = nthr[c];
+          // a uniform jump to eight moves, not a chain of selects
+          asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(nt));
+        }
+      take(v, row0 + b * 16 + (fresh_lane() & 15), nt);
+    }
+  };
+
+  // the lane's LDS offset of its piece of K-step 0 of 16 rows; the K-step and
+  // the 16-row block are immediate offsets
+  const int lo0 = (r16 >> 3) * 1024 + (r16 & 7) * 64 + ((quad ^ (r16 >> 2)) << 4);
+  auto load_a1 = [&](const uint8_t* strip, int u, int sb) {
+#pragma unroll
+    for (int q = 0; q < kU; ++q) {
+      const int f = u * kU + q;
+      a[u % kW][sb][q] = *reinterpret_cast<const uint4*>(strip + lo0 + (sb * 2048 + (f >> 1) * (G::kStageRows * 128) +
+                                                                        (f & 1) * 512));
+    }
+  };
+  auto load_a = [&](const uint8_t* strip, int u) {
+    load_a1(strip, u, 0);
+    load_a1(strip, u, 1);
+  };
+  auto load_ini = [&](int buf, int strip) {
+    const int l = fresh_lane();
+    const float* h = &side_h[buf][strip * 32 + 4 * (l >> 4)];
+    ini[0] = *reinterpret_cast<const f32x4*>(h);
+    ini[1] = *reinterpret_cast<const f32x4*>(h + 16);
+  };
+  // the E4M3 scales of the strip's 16-row block sb (used by every unit)
+  auto load_scale = [&](int buf, int strip, int sb) {
+    if constexpr (kFp8) ssc[sb] = side_s[buf][strip * 32 + sb * 16 + (fresh_lane() & 15)] + 127;
+  };
+  // unit u of the current strip for blocks b0 .. b0 + 3 and S blocks s0 ..
+  // s1 - 1 (kFirst: from the initial values)
+  auto mac4 = [&](auto first, int u, int b0, int s0, int s1) {
+    constexpr bool kFirst = decltype(first)::value;
+#define DL_STREAM_MAC(B)                                                                                       \
+  _Pragma("unroll") for (int sb = s0; sb < s1; ++sb)                                                           \
+      stream_mac<kPrec, B>(acc[b0 + B][sb], kFirst ? ini[sb] : acc[b0 + B][sb], a[u % kW][sb],                 \
+                           &rf[b0 + B][u * kU], ssc[sb], kFp8 ? rsc[b0 / 4] : 0);
+    DL_STREAM_MAC(0)
+    DL_STREAM_MAC(1)
+    DL_STREAM_MAC(2)
+    DL_STREAM_MAC(3)
+#undef DL_STREAM_MAC
+  };
+  using True = std::true_type;
+  using False = std::false_type;
+
+  load_r();
+#pragma unroll
+  for (int b = 0; b < kNB; ++b) acc[b][0] = acc[b][1] = f32x4{NAN, NAN, NAN, NAN};  // no outputs yet
+  int u = 0, t = 0, buf = 0;
+  bool fresh_r = false;  // the next strip meets a new block of R
+  for (;;) {  // one strip per pass; the last pass only tests
+    if (t == 0 && u < nu) {
+      // the stages up to the next one have landed (this wave's transfers by
+      // the wait, the others' by the barrier), and the stage before this one
+      // is free
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_waitcnt(0x0070);
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      buf = u & (kStreamStages - 1);
+      if (lu < nu) issue();
+      if (u == 0) {
+#pragma unroll
+        for (int f = 0; f < kW; ++f) load_a(ring[buf] + grp * 4096, f);
+        load_ini(buf, grp);
+        load_scale(buf, grp, 0);
+        load_scale(buf, grp, 1);
+      }
+    }
+    // the last strip's outputs are tested just before this strip's first
+    // products replace them
+    test();
+    if (u == nu) break;
+    if (fresh_r) {
+      load_r();
+      fresh_r = false;
+    }
+    const int strip = t * ws + grp;
+    const bool last = t + 1 == per;
+    const int nbuf = last ? (buf + 1) & (kStreamStages - 1) : buf;
+    const int nstrip = last ? grp : strip + ws;
+    const uint8_t* cur = ring[buf] + strip * 4096;
+    const uint8_t* nxt = ring[nbuf] + nstrip * 4096;
+    // the products stay behind the test's branch (moved above it they would
+    // need a second set of accumulators), and fragments are read into the
+    // registers just used, not beside them
+    asm volatile("" : "+v"(ini[0]), "+v"(ini[1]));
+    if constexpr (G::kTurns) {
+#pragma unroll
+      for (int f = 0; f < kUnits; ++f) {
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb) {
+#pragma unroll
+          for (int b = 0; b < kNB; b += 4)
+            if (f == 0) mac4(True{}, f, b, sb, sb + 1); else mac4(False{}, f, b, sb, sb + 1);
+          __builtin_amdgcn_sched_barrier(0);
+          if (f == 0 && sb == 1) load_ini(nbuf, nstrip);
+          load_a1(f + 1 < kUnits ? cur : nxt, f + 1 < kUnits ? f + 1 : 0, sb);
+          if (f + 1 == kUnits) load_scale(nbuf, nstrip, sb);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int f = 0; f < kUnits; ++f) {
+#pragma unroll
+        for (int b = 0; b < kNB; b += 4)
+          if (f == 0) mac4(True{}, f, b, 0, 2); else mac4(False{}, f, b, 0, 2);
+        __builtin_amdgcn_sched_barrier(0);
+        if (f == 0) load_ini(nbuf, nstrip);
+        load_a(f + kW < kUnits ? cur : nxt, f + kW < kUnits ? f + kW : f + kW - kUnits);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    pj = (uint32_t)st * G::kStageRows + strip * 32;
+    if (++t == per) {
+      t = 0;
+      ++u;
+      if (++st == p.nst) {
+        ++rb;
+        st = stream_first(p, rb);
+        fresh_r = true;
+      }
+    }
+  }
+  if (nq) flush_eps<kStageP>(p.c, eq_lds[wave], eqp_lds[kStageP ? wave : 0], nq);
+}
+
+// Whether the pass takes rows of qld operand bytes: as many R fragments as
+// registers hold.  float32 candidates stay with the tile form (its rate is the
+// matrix cores' own there).  The unit count of a workgroup is 32-bit.
+bool stream_applies(dl_prec prec, int64_t qld, int64_t nR, int64_t nS) {
+  return prec != DL_FP32 && (qld == 128 || qld == 256 || qld == 384 || qld == 512) &&
+         (double)nR * (double)nS < 0x1p51;
+}
+
+template <int kPrec, int kKB>
+static hipError_t launch_stream_kb(StreamParams p, int64_t npad_r, hipStream_t st, int cu_count) {
+  using G = StreamGeom<kPrec, kKB>;
+  p.npad_r = npad_r;
+  p.nst = (int)((p.c.nS + G::kStageRows - 1) / G::kStageRows);
+  // waves along R: as many as R fills, fewer while there are fewer than four
+  // units per workgroup (a stage has to hold a strip for every wave along S,
+  // and a self-join's block at least a stage)
+  int wr = 8;
+  const int wr_min = 8 / (G::kStrips < 8 ? G::kStrips : 8);
+  auto units_of = [&](int w) {
+    const int64_t rows = (int64_t)w * G::kWaveRows, nrb = (p.c.nR + rows - 1) / rows;
+    const int64_t spb = rows / G::kStageRows;
+    return nrb * p.nst - (p.c.self_join ? spb * (nrb * (nrb - 1) / 2) : 0);
+  };
+  while (wr > wr_min && (!p.c.self_join || wr / 2 * G::kWaveRows >= G::kStageRows) &&
+         (p.c.nR <= (int64_t)(wr / 2) * G::kWaveRows || units_of(wr) < 4 * (int64_t)cu_count))
+    wr /= 2;
+  p.wr = wr;
+  const int64_t rows = (int64_t)wr * G::kWaveRows;
+  p.nrb = (int)((p.c.nR + rows - 1) / rows);
+  p.stages_per_block = (int)(rows / G::kStageRows);
+  p.units = units_of(wr);
+  int64_t g = cu_count / 8 * 8;
+  if (g > (p.units + 7) / 8 * 8) g = (p.units + 7) / 8 * 8;
+  hipLaunchKernelGGL((stream_eps_kernel<kPrec, kKB>), dim3((unsigned)g), dim3(kThreads), 0, st, p);
+  return hipGetLastError();
+}
+
+template <int kPrec>
+static hipError_t launch_stream_prec(const StreamParams& p, int64_t npad_r, hipStream_t st, int cu_count) {
+  switch (p.c.qld) {
+    case 128: return launch_stream_kb<kPrec, 128>(p, npad_r, st, cu_count);
+    case 256: return launch_stream_kb<kPrec, 256>(p, npad_r, st, cu_count);
+    case 384: return launch_stream_kb<kPrec, 384>(p, npad_r, st, cu_count);
+    case 512: return launch_stream_kb<kPrec, 512>(p, npad_r, st, cu_count);
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_stream_eps(dl_prec prec, const CandParams& c, int64_t npad_r, hipStream_t st, int cu_count) {
+  if (c.nR == 0 || c.nS == 0) return hipSuccess;
+  StreamParams p{};
+  p.c = c;
+  switch (prec) {
+    case DL_BF16: return launch_stream_prec<DL_BF16>(p, npad_r, st, cu_count);
+    case DL_FP16: return launch_stream_prec<DL_FP16>(p, npad_r, st, cu_count);
+    case DL_FP8: return launch_stream_prec<DL_FP8>(p, npad_r, st, cu_count);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace dl
