@@ -34,6 +34,8 @@ hipError_t launch_cand_eps(dl_prec, CandParams, hipStream_t, int);
 hipError_t launch_cand_list(dl_prec, CandParams, hipStream_t, int);
 bool stream_applies(dl_prec, int64_t, int64_t, int64_t);
 hipError_t launch_stream_eps(dl_prec, const CandParams&, int64_t, hipStream_t, int);
+bool stream_band_applies(int64_t, int);
+hipError_t launch_stream_band(dl_prec, const CandParams&, int64_t, int, uint32_t*, hipStream_t, int);
 hipError_t launch_cand_mark(dl_prec, CandParams, hipStream_t, int);
 hipError_t launch_cand_nearest(dl_prec, CandParams, hipStream_t, int);
 // index.hip
@@ -700,9 +702,15 @@ dl_status topk_core(dl_ctx* c, const TopkJob& J, void* ws, size_t ws_bytes, uint
     return fail(c, DL_ERR_WORKSPACE, "workspace of %zu bytes below the %zu needed", ws_bytes, need);
   }
   if (R.n == 0) return DL_OK;
-  // the pilot (see pilot_of) runs first, in its own part of the workspace
+  // The streaming pass (stream.hip) sets each row's threshold from a sample of
+  // S and fills one buffer per row, the memory of its P split buffers; should
+  // a row's buffer overflow (the sample missed a dense neighbourhood), the
+  // tile form, which tightens as it goes, runs after it.
+  bool stream = !J.surv && !J.seed && S.n > 0 && stream_applies(prec, dpad_of(R.d, prec) * elem_bytes(prec), R.n, S.n) &&
+                stream_band_applies(S.n, k + (excl ? 1 : 0)) && (int64_t)P * band_cap < (1 << 30);
+  // the pilot (see pilot_of), in its own part of the workspace
   const float* pilot_dist = nullptr;
-  if (pilot) {
+  auto run_pilot = [&]() -> dl_status {
     uint8_t* pw = static_cast<uint8_t*>(ws) + main_bytes;
     uint32_t* pj = reinterpret_cast<uint32_t*>(pw);
     float* pd = reinterpret_cast<float*>(pw + pilot_out_bytes(R.n, k));
@@ -714,8 +722,11 @@ dl_status topk_core(dl_ctx* c, const TopkJob& J, void* ws, size_t ws_bytes, uint
     const dl_status ps = topk_core(c, Jp, pws, ws_bytes - main_bytes - 2 * pilot_out_bytes(R.n, k), pj, pd, nullptr,
                                    st);
     if (ps == DL_OK) pilot_dist = pd;  // otherwise the E4M3 pass starts unseeded
-    else if (ps != DL_ERR_WORKSPACE) return ps;
-  }
+    return ps == DL_ERR_WORKSPACE ? DL_OK : ps;
+  };
+  if (pilot && !stream)
+    if (const dl_status ps = run_pilot()) return ps;
+  bool restarted = false;  // the streaming pass overflowed
   TopkLayout L = layout_topk(ws, R.n, S.n, R.d, prec, self, P, band_cap, sx);
   if (sx) {
     L.ps = *J.ps_ext;
@@ -734,11 +745,11 @@ dl_status topk_core(dl_ctx* c, const TopkJob& J, void* ws, size_t ws_bytes, uint
                      (int64_t)(sizeof(Counters) / 4));
   hipLaunchKernelGGL(zero_words_kernel, dim3(64), dim3(256), 0, st, reinterpret_cast<uint32_t*>(L.rstate), R.n);
   hipLaunchKernelGGL(zero_words_kernel, dim3(64), dim3(256), 0, st, reinterpret_cast<uint32_t*>(L.wide), R.n);
-  if (S.n == 0 || J.surv) {
-    // nothing to match (every row is padding), or work items whose tiles
-    // the index rules out all (they store no count)
+  if (S.n == 0 || J.surv || stream) {
+    // nothing to match (every row is padding), work items whose tiles the
+    // index rules out all (they store no count), or rows' own counters
     hipLaunchKernelGGL(zero_words_kernel, dim3(256), dim3(256), 0, st, reinterpret_cast<uint32_t*>(L.bcount),
-                       R.n * (int64_t)P);
+                       stream ? R.n : R.n * (int64_t)P);
   }
   {
     StageTimer t(c, 1, st);
@@ -749,60 +760,84 @@ dl_status topk_core(dl_ctx* c, const TopkJob& J, void* ws, size_t ws_bytes, uint
     if (pilot_dist) DL_HIP(c, launch_band_seed(L.pr, R.n, pilot_dist, k, L.marg, L.gkey, st));
     if (J.seed) DL_HIP(c, launch_band_seed(L.pr, R.n, J.seed, 1, L.marg, L.gkey, st));
   }
-  if (S.n > 0) {
-    StageTimer t(c, 2, st);
-    CandParams p{};
-    p.qa = static_cast<const uint8_t*>(L.pr.q);
-    p.qb = static_cast<const uint8_t*>(L.ps.q);
-    p.qld = L.pr.qld;
-    p.nchunks = (int)(L.pr.qld / kChunkBytes);
-    p.hb = L.ps.h;
-    p.sexa = L.pr.sexp;
-    p.sexb = L.ps.sexp;
-    p.nR = R.n;
-    p.nS = S.n;
-    p.self_join = self;
-    p.exclude_self = excl;
-    p.P = P;
-    p.k = k;
-    p.cap = band_cap;
-    p.limit = band_limit_of(band_cap, k, tps);
-    p.batch = band_defers(band_cap, k, tps) ? 8 : 1;  // one row per wave of the workgroup
-    p.retight = retight_of(k, p.limit);
-    p.marg = L.marg;
-    p.gkey = L.gkey;
-    p.flood = (pilot_dist || J.seed) ? 0 : 1;  // (flood_band stores unmapped j: never with jmap)
-    p.surv = J.surv;
-    p.sw = J.sw;
-    p.jmap = J.jmap;
-    p.kmaskA = J.kmA;
-    p.kmaskB = J.kmB;
-    p.band = L.band;
-    p.bcount = L.bcount;
-    p.overflow = &L.cnt->overflow;
-    p.gate = &L.cnt->invalid;
-    DL_HIP(c, launch_cand_band(prec, p, st));
-  }
   SelectParams q{};
   const bool small_sel = topk_select_small(k);
-  {
-    StageTimer t(c, 5, st);
-    q.R = R.data; q.ldr = R.ld;
-    q.S = S.data; q.lds = S.ld;
-    q.d = R.d; q.nR = R.n;
-    q.band = L.band; q.bcount = L.bcount; q.P = P; q.cap = band_cap; q.k = k;
-    q.marg = L.marg;
-    q.xnR = L.pr.xnorm; q.mlR = L.pr.mlsb;
-    q.sS = L.ss;
-    q.out_j = out_j; q.out_dist = out_dist;
-    q.nband = &L.cnt->band; q.nties = &L.cnt->ties; q.too_many = &L.cnt->too_many;
-    q.gate = &L.cnt->invalid;
-    q.rstate = L.rstate;
-    q.wide = L.wide;
-    DL_HIP(c, launch_topk_select(q, small_sel, st));
+  Counters hc;
+  for (;;) {
+    if (S.n > 0) {
+      StageTimer t(c, 2, st);
+      CandParams p{};
+      p.qa = static_cast<const uint8_t*>(L.pr.q);
+      p.qb = static_cast<const uint8_t*>(L.ps.q);
+      p.qld = L.pr.qld;
+      p.nchunks = (int)(L.pr.qld / kChunkBytes);
+      p.hb = L.ps.h;
+      p.sexa = L.pr.sexp;
+      p.sexb = L.ps.sexp;
+      p.nR = R.n;
+      p.nS = S.n;
+      p.self_join = self;
+      p.exclude_self = excl;
+      p.marg = L.marg;
+      p.gkey = L.gkey;
+      p.band = L.band;
+      p.bcount = L.bcount;
+      p.overflow = &L.cnt->overflow;
+      p.gate = &L.cnt->invalid;
+      if (stream) {
+        p.cap = P * band_cap;
+        // (the group maxima lie in the band's memory, which is written later)
+        DL_HIP(c, launch_stream_band(prec, p, L.pr.npad, k + (excl ? 1 : 0), reinterpret_cast<uint32_t*>(L.band), st,
+                                     c->cu_count));
+      } else {
+        p.P = P;
+        p.k = k;
+        p.cap = band_cap;
+        p.limit = band_limit_of(band_cap, k, tps);
+        p.batch = band_defers(band_cap, k, tps) ? 8 : 1;  // one row per wave of the workgroup
+        p.retight = retight_of(k, p.limit);
+        p.flood = (pilot_dist || J.seed || restarted) ? 0 : 1;  // (flood_band stores unmapped j: never with jmap)
+        p.surv = J.surv;
+        p.sw = J.sw;
+        p.jmap = J.jmap;
+        p.kmaskA = J.kmA;
+        p.kmaskB = J.kmB;
+        DL_HIP(c, launch_cand_band(prec, p, st));
+      }
+    }
+    {
+      StageTimer t(c, 5, st);
+      q.R = R.data; q.ldr = R.ld;
+      q.S = S.data; q.lds = S.ld;
+      q.d = R.d; q.nR = R.n;
+      q.band = L.band; q.bcount = L.bcount; q.k = k;
+      q.P = stream ? 1 : P;
+      q.cap = stream ? P * band_cap : band_cap;
+      q.marg = L.marg;
+      q.xnR = L.pr.xnorm; q.mlR = L.pr.mlsb;
+      q.sS = L.ss;
+      q.out_j = out_j; q.out_dist = out_dist;
+      q.nband = &L.cnt->band; q.nties = &L.cnt->ties; q.too_many = &L.cnt->too_many;
+      q.gate = &L.cnt->invalid;
+      q.rstate = L.rstate;
+      q.wide = L.wide;
+      DL_HIP(c, launch_topk_select(q, small_sel, st));
+    }
+    DL_HIP(c, readback(c, L.cnt, L.sr, L.ss, st));
+    hc = *reinterpret_cast<const Counters*>(c->pinned);
+    if (!(stream && hc.overflow)) break;
+    // the tile form from the thresholds found (the gate stays as it is)
+    stream = false;
+    restarted = true;
+    if (pilot) {
+      if (const dl_status ps = run_pilot()) return ps;
+      if (pilot_dist) DL_HIP(c, launch_band_seed(L.pr, R.n, pilot_dist, k, L.marg, L.gkey, st));
+    }
+    hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t*>(L.cnt),
+                       (int64_t)(offsetof(Counters, invalid) / 4));
+    hipLaunchKernelGGL(zero_words_kernel, dim3(64), dim3(256), 0, st, reinterpret_cast<uint32_t*>(L.rstate), R.n);
+    hipLaunchKernelGGL(zero_words_kernel, dim3(64), dim3(256), 0, st, reinterpret_cast<uint32_t*>(L.wide), R.n);
   }
-  DL_HIP(c, readback(c, L.cnt, L.sr, L.ss, st));
-  Counters hc = *reinterpret_cast<const Counters*>(c->pinned);
   if (small_sel && hc.too_many && !hc.overflow) {
     // a row had more near-tie contenders than the small selection holds:
     // select again (the bands are unchanged) with the large one

@@ -83,6 +83,10 @@ struct StreamParams {
   int nst, nrb;          // stages of S, blocks of R
   int stages_per_block;  // self-join: block rb starts at stage rb * stages_per_block
   int wr;                // waves along R (8 / wr along S)
+  // max mode: every stride-th stage of S, in nslots runs (of slot_strips 32-row strips) whose largest P~ per
+  // row and lane quarter go to gmax[(4 slot + quarter) * nR + row] (order keys)
+  int stride, nslots, slot_strips;
+  uint32_t* gmax;
 };
 
 // eps-join recheck (recheck.hip).

@@ -220,6 +220,9 @@ __device__ inline uint32_t ord_f(float f) {
 }
 
 
+// Entries in a row's buffer (the streaming pass counts past its end).
+__device__ inline int band_count(const SelectParams& p, int64_t at) { return min(p.bcount[at], p.cap); }
+
 // One wave per row.  Counting over the row's band entries uses ballots
 // (scalar popcounts, no shuffle chains); distances are computed one entry
 // per lane; the k nearest are emitted by rank, since the (key, j) pairs of a
@@ -248,7 +251,7 @@ __global__ __launch_bounds__(64 * kSelWaves, kSelMax == kSelSmall ? 6 : 4) void 
   }
   const uint64_t lt = __lanemask_lt();
   int total = 0;
-  for (int s = 0; s < p.P; ++s) total += p.bcount[i * p.P + s];
+  for (int s = 0; s < p.P; ++s) total += band_count(p, i * p.P + s);
   const double xsum = (double)p.xnR[i] + (double)p.sS->xnorm_max;
   const bool ex = exact32(min(p.mlR[i], p.sS->mlsb_min), xsum);
   const double c1 = ex ? 0.0 : 2.0 * gamma_n((double)p.d + 2.0, 0x1p-24);
@@ -271,7 +274,7 @@ __global__ __launch_bounds__(64 * kSelWaves, kSelMax == kSelSmall ? 6 : 4) void 
     int g = 0;
     for (int s = 0; s < p.P; ++s) {
       const uint2* e = p.band + (i * p.P + s) * (int64_t)p.cap;
-      const int n = p.bcount[i * p.P + s];
+      const int n = band_count(p, i * p.P + s);
       for (int base = 0; base < n; base += 64) {
         const int t = base + lane;
         const uint2 v = t < n ? e[t] : make_uint2(0, 0);
@@ -385,7 +388,7 @@ __global__ __launch_bounds__(64 * kSelWaves, kSelMax == kSelSmall ? 6 : 4) void 
       int c = 0;
       for (int s = 0; s < p.P; ++s) {
         const uint2* e = p.band + (i * p.P + s) * (int64_t)p.cap;
-        const int n = p.bcount[i * p.P + s];
+        const int n = band_count(p, i * p.P + s);
         for (int base = 0; base < n; base += 64) {
           const int t = base + lane;
           c += __popcll(__ballot(t < n && pred(e[t].x)));
@@ -408,7 +411,7 @@ __global__ __launch_bounds__(64 * kSelWaves, kSelMax == kSelSmall ? 6 : 4) void 
       // band): the steps below, and any later selection of the row, read that
       for (int s = 0; s < p.P; ++s) {
         uint2* e = p.band + (i * p.P + s) * (int64_t)p.cap;
-        const int n = p.bcount[i * p.P + s];
+        const int n = band_count(p, i * p.P + s);
         for (int base = 0; base < n; base += 64) {
           const int t = base + lane;
           const uint2 v = t < n ? e[t] : make_uint2(0, 0);
@@ -432,7 +435,7 @@ __global__ __launch_bounds__(64 * kSelWaves, kSelMax == kSelSmall ? 6 : 4) void 
     const double cut = cut_of(dk);
     for (int s = 0; s < p.P; ++s) {
       const uint2* e = p.band + (i * p.P + s) * (int64_t)p.cap;
-      const int n = p.bcount[i * p.P + s];
+      const int n = band_count(p, i * p.P + s);
       for (int base = 0; base < n; base += 64) {
         const int t = base + lane;
         uint2 v = make_uint2(0x7f800000u, 0);
@@ -530,12 +533,12 @@ __global__ __launch_bounds__(64 * kSelWaves) void topk_select_wide_kernel(Select
   const bool vec4 = ((reinterpret_cast<uintptr_t>(p.S) | reinterpret_cast<uintptr_t>(a)) & 15) == 0 &&
                     (p.lds & 3) == 0;
   int total = 0;
-  for (int s = 0; s < p.P; ++s) total += p.bcount[i * p.P + s];
+  for (int s = 0; s < p.P; ++s) total += band_count(p, i * p.P + s);
   auto count = [&](auto pred) {
     int c = 0;
     for (int s = 0; s < p.P; ++s) {
       const uint2* e = p.band + (i * p.P + s) * (int64_t)p.cap;
-      const int n = p.bcount[i * p.P + s];
+      const int n = band_count(p, i * p.P + s);
       for (int base = 0; base < n; base += 64) {
         const int t = base + lane;
         c += __popcll(__ballot(t < n && pred(e[t])));
@@ -557,7 +560,7 @@ __global__ __launch_bounds__(64 * kSelWaves) void topk_select_wide_kernel(Select
     }
     for (int s = 0; s < p.P; ++s) {
       uint2* e = p.band + (i * p.P + s) * (int64_t)p.cap;
-      const int n = p.bcount[i * p.P + s];
+      const int n = band_count(p, i * p.P + s);
       for (int base = 0; base < n; base += 64) {
         const int t = base + lane;
         const uint2 v = t < n ? e[t] : make_uint2(0, 0);
@@ -614,7 +617,7 @@ __global__ __launch_bounds__(64 * kSelWaves) void topk_select_wide_kernel(Select
   int g = 0;
   for (int s = 0; s < p.P; ++s) {
     const uint2* e = p.band + (i * p.P + s) * (int64_t)p.cap;
-    const int n = p.bcount[i * p.P + s];
+    const int n = band_count(p, i * p.P + s);
     for (int base = 0; base < n; base += 64) {
       const int t = base + lane;
       const uint2 v = t < n ? e[t] : make_uint2(0x7f800000u, 0);

@@ -114,16 +114,42 @@ __device__ inline UnitAt stream_unit(const StreamParams& p, int64_t L) {
   return {lo, stream_first(p, lo) + (int)(L - stream_prefix(p, lo))};
 }
 
-template <int kPrec, int kKB>
-__global__ __launch_bounds__(kThreads, 1) void stream_eps_kernel(StreamParams p) {
+// kStreamEps: candidates (P~ >= thr_i) to the global list.  kStreamBand: top-k
+// band entries (P~ >= the row's threshold of p.gkey) to the row's buffer.
+// kStreamMax: per row and group of S rows the largest P~ (p.gmax), from which
+// the band's thresholds come.
+enum : int { kStreamEps = 0, kStreamBand = 1, kStreamMax = 2 };
+
+// A wave's staged band entries to their rows' buffers: one slot each from the
+// row's counter (two in flight per lane); entries past the buffer are counted
+// and flagged.
+__device__ inline void flush_rows(const StreamParams& p, const uint2* q, const uint32_t* qp, int nq) {
+  const int lane = fresh_lane();
+#pragma unroll 1
+  for (int s = lane; s < nq; s += 128) {
+    const bool two = s + 64 < nq;
+    const uint2 e0 = q[s], e1 = two ? q[s + 64] : e0;
+    const uint32_t p0 = (uint32_t)atomicAdd(p.c.bcount + e0.x, 1);
+    const uint32_t p1 = two ? (uint32_t)atomicAdd(p.c.bcount + e1.x, 1) : 0u;
+    const uint32_t cap = (uint32_t)p.c.cap;
+    if (p0 < cap) p.c.band[(int64_t)e0.x * p.c.cap + p0] = make_uint2(qp[s], e0.y);
+    if (two && p1 < cap) p.c.band[(int64_t)e1.x * p.c.cap + p1] = make_uint2(qp[s + 64], e1.y);
+    if (p0 >= cap || p1 >= cap) *p.c.overflow = 1;
+  }
+}
+
+template <int kPrec, int kKB, int kMode>
+__global__ __launch_bounds__(kThreads, 1) void stream_kernel(StreamParams p) {
   using G = StreamGeom<kPrec, kKB>;
   constexpr bool kFp8 = kPrec == DL_FP8;
   constexpr int kNB = G::kNB, kUnits = G::kUnits, kW = G::kWindow, kU = G::kUnit;
   __shared__ __attribute__((aligned(1024))) uint8_t ring[kStreamStages][G::kStageBytes];
   __shared__ __attribute__((aligned(16))) float side_h[kStreamStages][G::kStageRows];
   __shared__ __attribute__((aligned(16))) int side_s[kFp8 ? kStreamStages : 1][kFp8 ? G::kStageRows : 4];
-  __shared__ __attribute__((aligned(16))) uint2 eq_lds[kThreads / 64][kQueue];
-  constexpr bool kStageP = !kFp8;  // E4M3 stages no P~ (it is never exact)
+  constexpr bool kMax = kMode == kStreamMax;
+  __shared__ __attribute__((aligned(16))) uint2 eq_lds[kMax ? 1 : kThreads / 64][kMax ? 1 : kQueue];
+  // P~ of the staged records (eps with E4M3 needs none: it is never exact)
+  constexpr bool kStageP = kMode == kStreamBand || (kMode == kStreamEps && !kFp8);
   __shared__ uint32_t eqp_lds[kStageP ? kThreads / 64 : 1][kStageP ? kQueue : 1];
 
   if (p.c.gate && __builtin_amdgcn_readfirstlane(*p.c.gate)) return;
@@ -132,8 +158,8 @@ __global__ __launch_bounds__(kThreads, 1) void stream_eps_kernel(StreamParams p)
   const int r16 = lane & 15, quad = lane >> 4;
   // this workgroup's share of the units; consecutive shares on one XCD
   const int ng = gridDim.x;
-  const int slot = (blockIdx.x & 7) * (ng >> 3) + (blockIdx.x >> 3);
-  const int64_t u0 = uniform64(p.units * slot / ng), u1 = uniform64(p.units * (slot + 1) / ng);
+  const int share = (blockIdx.x & 7) * (ng >> 3) + (blockIdx.x >> 3);
+  const int64_t u0 = uniform64(p.units * share / ng), u1 = uniform64(p.units * (share + 1) / ng);
   const int nu = (int)(u1 - u0);
   if (nu <= 0) return;
   const int wr = p.wr, ws = 8 / wr;
@@ -150,7 +176,7 @@ __global__ __launch_bounds__(kThreads, 1) void stream_eps_kernel(StreamParams p)
   // piece of 16 rows touches all 64 banks.
   auto issue = [&]() {
     const int buf = lu & (kStreamStages - 1);
-    const int64_t j0 = (int64_t)lst * G::kStageRows;
+    const int64_t j0 = (int64_t)lst * G::kStageRows * (kMax ? p.stride : 1);
     const int l = fresh_lane();
     const uint8_t* src = p.c.qb + j0 * kKB;
     const uint32_t dst = lds_addr(&ring[buf][0]) + wave * G::kDma * 1024;
@@ -176,7 +202,9 @@ __global__ __launch_bounds__(kThreads, 1) void stream_eps_kernel(StreamParams p)
     if (lu < nu) issue();
 
   uint4 rf[kNB][G::kSteps];  // the wave's R rows, signs flipped
-  float nthr[kNB];           // -thr_i of row lane % 16 of each block
+  // of row lane % 16 of each block: -thr_i; max mode: the smallest output so
+  // far of the lane's S rows of the current group
+  float nthr[kNB];
   int rsc[kFp8 ? kNB / 4 : 1];  // E4M3: the rows' scales, four blocks to a register
   f32x4 acc[kNB][2];
   uint4 a[kW][2][kU];        // A fragments of the coming units, both 16-row blocks
@@ -194,7 +222,6 @@ __global__ __launch_bounds__(kThreads, 1) void stream_eps_kernel(StreamParams p)
     const int left = (int)(p.npad_r - (int64_t)row0 < G::kWaveRows ? p.npad_r - (int64_t)row0 : G::kWaveRows);
     const uint32_t i0 = left > 0 ? row0 : (uint32_t)p.npad_r - 1;
     const uint8_t* const src = p.c.qa + (int64_t)i0 * kKB;
-    const float* const thr = p.c.thr + i0;
 #pragma unroll
     for (int b = 0; b < kNB; ++b) {
       const int l = fresh_lane();
@@ -207,18 +234,45 @@ __global__ __launch_bounds__(kThreads, 1) void stream_eps_kernel(StreamParams p)
         v.x ^= flip; v.y ^= flip; v.z ^= flip; v.w ^= flip;
         rf[b][f] = v;
       }
-      nthr[b] = want < left ? -thr[i] : -INFINITY;
+      if constexpr (kMode == kStreamEps) nthr[b] = want < left ? -p.c.thr[i0 + i] : -INFINITY;
+      // (rows of the padding have no key: they never hit)
+      if constexpr (kMode == kStreamBand)
+        nthr[b] = (int64_t)row0 + want < p.c.nR ? -key_float(p.c.gkey[i0 + i]) : -INFINITY;
+      if constexpr (kMax) nthr[b] = INFINITY;
       if constexpr (kFp8) {
         const int e = (p.c.sexa[i0 + i] + 127) << (8 * (b & 3));
         rsc[b / 4] = (b & 3) ? rsc[b / 4] | e : e;
       }
     }
   };
-  // Hits among one block's outputs v (strip pj, rows i, threshold nt) into
-  // the wave's queue, a 16-row block of S at a time (at most 256 hits, one
-  // check of the queue's room).
+  auto flush = [&]() {
+    if constexpr (kMode == kStreamEps) flush_eps<kStageP>(p.c, eq_lds[wave], eqp_lds[kStageP ? wave : 0], nq);
+    if constexpr (kMode == kStreamBand) flush_rows(p, eq_lds[wave], eqp_lds[wave], nq);
+    nq = 0;
+  };
+  // whether the strip pj needs its columns checked: the end of S, or the
+  // diagonal (a self-join's j > i, a top-k's j != i)
+  auto at_edge = [&]() {
+    if (pj + 32 > ns) return true;
+    if constexpr (kMode == kStreamEps) return p.c.self_join && pj <= row0 + G::kWaveRows;
+    if constexpr (kMode == kStreamBand)
+      return p.c.exclude_self && pj < row0 + G::kWaveRows && pj + 32 > row0;
+    return false;
+  };
+  // The hits of mask m, rows i and columns j, into the wave's queue.
+  auto stage = [&](uint64_t m, uint32_t i, uint32_t j, float x) {
+    if (__builtin_amdgcn_inverse_ballot_w64(m)) {
+      const int s = nq + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+      eq_lds[wave][s] = make_uint2(i, j);
+      if constexpr (kStageP) eqp_lds[wave][s] = __float_as_uint(-x);
+    }
+    nq += __popcll(m);
+  };
+  // Hits among one block's outputs v (strip pj, rows i, threshold nt), columns
+  // checked, a 16-row block of S at a time (at most 256 hits, one check of the
+  // queue's room).
   auto take = [&](const f32x4 (&v)[2], uint32_t i, float nt) {
-    const bool edge = pj + 32 > ns || (p.c.self_join && pj <= row0 + G::kWaveRows);
+    const bool edge = at_edge();
 #pragma unroll
     for (int sb = 0; sb < 2; ++sb) {
       const uint32_t j = pj + 16 * sb + 4 * (fresh_lane() >> 4);
@@ -228,31 +282,22 @@ __global__ __launch_bounds__(kThreads, 1) void stream_eps_kernel(StreamParams p)
       if (edge) {
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          m[r] &= __builtin_amdgcn_ballot_w64(j + r < ns && (!p.c.self_join || j + r > i));
+          m[r] &= __builtin_amdgcn_ballot_w64(
+              j + r < ns && (kMode == kStreamEps ? !p.c.self_join || j + r > i : !p.c.exclude_self || j + r != i));
       }
       const int n = __popcll(m[0]) + __popcll(m[1]) + __popcll(m[2]) + __popcll(m[3]);
       if (n == 0) continue;
-      if (nq + n > kQueue) {
-        flush_eps<kStageP>(p.c, eq_lds[wave], eqp_lds[kStageP ? wave : 0], nq);
-        nq = 0;
-      }
+      if (nq + n > kQueue) flush();
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        if (!m[r]) continue;
-        if (__builtin_amdgcn_inverse_ballot_w64(m[r])) {
-          const int s = nq + __builtin_amdgcn_mbcnt_hi((uint32_t)(m[r] >> 32),
-                                                       __builtin_amdgcn_mbcnt_lo((uint32_t)m[r], 0));
-          eq_lds[wave][s] = make_uint2(i, j + r);
-          if constexpr (kStageP) eqp_lds[wave][s] = __float_as_uint(-v[sb][r]);
-        }
-        nq += __popcll(m[r]);
-      }
+      for (int r = 0; r < 4; ++r)
+        if (m[r]) stage(m[r], i, j + r, v[sb][r]);
     }
   };
   // The candidate test of a strip's outputs: four minimum instructions and a
-  // compare per block, one branch for all.  The blocks with hits go through
-  // one copy of the staging code (a copy each, and its queue flush, would
-  // overflow the instruction cache).
+  // compare per block, one branch for all.  A strip with few hits stages them
+  // straight from the accumulators; one with many, or at an edge, takes its
+  // blocks through one copy of the code that checks columns and room (a copy
+  // each would overflow the instruction cache).
   auto test = [&]() {
     uint64_t any = 0, h[kNB];
 #pragma unroll
@@ -263,6 +308,25 @@ __global__ __launch_bounds__(kThreads, 1) void stream_eps_kernel(StreamParams p)
       any |= h[b];
     }
     if (!any) return;
+    int most = 0;  // hits of the strip, at most
+#pragma unroll
+    for (int b = 0; b < kNB; ++b) most += 8 * __popcll(h[b]);
+    if (most <= kQueue && !at_edge()) {
+      if (nq + most > kQueue) flush();
+      const int l = fresh_lane();
+      const uint32_t i0 = row0 + (l & 15), j0 = pj + 4 * (l >> 4);
+#pragma unroll
+      for (int b = 0; b < kNB; ++b) {
+        if (!h[b]) continue;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float x = acc[b][e >> 2][e & 3];
+          const uint64_t m = mask_le(x, nthr[b]);
+          if (m) stage(m, i0 + b * 16, j0 + 16 * (e >> 2) + (e & 3), x);
+        }
+      }
+      return;
+    }
     uint32_t hb = 0;
 #pragma unroll
     for (int b = 0; b < kNB; ++b) hb |= (h[b] ? 1u : 0u) << b;
@@ -282,6 +346,38 @@ __global__ __launch_bounds__(kThreads, 1) void stream_eps_kernel(StreamParams p)
           asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(nt));
         }
       take(v, row0 + b * 16 + (fresh_lane() & 15), nt);
+    }
+  };
+  // Max mode: the strip's outputs into the running minima (columns past S
+  // left out; the row itself, in a self-join, is not: the caller takes the
+  // (k + 1)-th largest).
+  bool fresh_acc = false;  // the accumulators hold a strip's outputs
+  auto fold = [&]() {
+    if (!fresh_acc) return;
+    if (pj + 32 > ns) {
+      const uint32_t j = pj + 4 * (fresh_lane() >> 4);
+#pragma unroll
+      for (int b = 0; b < kNB; ++b)
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          nthr[b] = fminf(nthr[b], j + 16 * (e >> 2) + (e & 3) < ns ? acc[b][e >> 2][e & 3] : INFINITY);
+      return;
+    }
+#pragma unroll
+    for (int b = 0; b < kNB; ++b) {
+      const f32x4 &v = acc[b][0], &w = acc[b][1];
+      nthr[b] = min3(min3(nthr[b], v[0], v[1]), min3(v[2], v[3], w[0]), min3(w[1], w[2], w[3]));
+    }
+  };
+  // the running minima to group `slot` (of every lane quarter), and restart
+  auto put_max = [&](uint32_t slot) {
+    const int l = fresh_lane();
+    uint32_t* const g = p.gmax + (int64_t)slot * 4 * p.c.nR;
+#pragma unroll
+    for (int b = 0; b < kNB; ++b) {
+      const int64_t i = (int64_t)row0 + b * 16 + (l & 15);
+      if (i < p.c.nR) atomicMax(g + (l >> 4) * p.c.nR + i, order_key(-nthr[b]));
+      nthr[b] = INFINITY;
     }
   };
 
@@ -332,6 +428,8 @@ __global__ __launch_bounds__(kThreads, 1) void stream_eps_kernel(StreamParams p)
   for (int b = 0; b < kNB; ++b) acc[b][0] = acc[b][1] = f32x4{NAN, NAN, NAN, NAN};  // no outputs yet
   int u = 0, t = 0, buf = 0;
   bool fresh_r = false;  // the next strip meets a new block of R
+  // max mode: the run of strips being folded, and where it ends
+  uint32_t slot = 0, slot_end = 0;
   for (;;) {  // one strip per pass; the last pass only tests
     if (t == 0 && u < nu) {
       // the stages up to the next one have landed (this wave's transfers by
@@ -355,13 +453,24 @@ __global__ __launch_bounds__(kThreads, 1) void stream_eps_kernel(StreamParams p)
     }
     // the last strip's outputs are tested just before this strip's first
     // products replace them
-    test();
+    const int strip = t * ws + grp;
+    if constexpr (kMax) {
+      fold();
+      const uint32_t s = (uint32_t)(st * G::kStrips + strip);
+      if (!fresh_acc || fresh_r || u == nu || s >= slot_end) {
+        if (fresh_acc) put_max(slot);
+        slot = s / (uint32_t)p.slot_strips;
+        slot_end = (slot + 1) * (uint32_t)p.slot_strips;
+      }
+      fresh_acc = true;
+    } else {
+      test();
+    }
     if (u == nu) break;
     if (fresh_r) {
       load_r();
       fresh_r = false;
     }
-    const int strip = t * ws + grp;
     const bool last = t + 1 == per;
     const int nbuf = last ? (buf + 1) & (kStreamStages - 1) : buf;
     const int nstrip = last ? grp : strip + ws;
@@ -398,7 +507,7 @@ __global__ __launch_bounds__(kThreads, 1) void stream_eps_kernel(StreamParams p)
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    pj = (uint32_t)st * G::kStageRows + strip * 32;
+    pj = (uint32_t)st * (G::kStageRows * (kMax ? p.stride : 1)) + strip * 32;
     if (++t == per) {
       t = 0;
       ++u;
@@ -409,7 +518,44 @@ __global__ __launch_bounds__(kThreads, 1) void stream_eps_kernel(StreamParams p)
       }
     }
   }
-  if (nq) flush_eps<kStageP>(p.c, eq_lds[wave], eqp_lds[kStageP ? wave : 0], nq);
+  if (nq) flush();
+}
+
+// The k-th largest of each row's ngroups group maxima (order keys, group-major,
+// zero where a group is empty), minus the row's margin, as the row's band
+// threshold.  The groups partition a subset of S, so at least k rows of S have
+// a P~ at or above it: the band P~ >= v - E_i keeps every one of the k
+// nearest, as in the tile form's tightening.  One thread per row; the keys are
+// held in registers when there are at most kRegs of them.
+template <int kRegs>
+__global__ __launch_bounds__(64) void band_key_kernel(const uint32_t* __restrict__ gmax, int ngroups, int64_t nR, int k,
+                                                      const float* __restrict__ marg, uint32_t* __restrict__ gkey) {
+  const int64_t i = (int64_t)blockIdx.x * 64 + threadIdx.x;
+  if (i >= nR) return;
+  uint32_t key[kRegs ? kRegs : 1];
+  if constexpr (kRegs > 0) {
+#pragma unroll
+    for (int g = 0; g < kRegs; ++g) key[g] = g < ngroups ? gmax[g * nR + i] : 0u;
+  }
+  uint32_t v = 0;  // largest key with at least k group maxima at or above it
+  for (int b = 31; b >= 0; --b) {
+    const uint32_t t = v | (1u << b);
+    int c = 0;
+    if constexpr (kRegs > 0) {
+#pragma unroll
+      for (int g = 0; g < kRegs; ++g) c += key[g] >= t;
+    } else {
+#pragma unroll 8
+      for (int g = 0; g < ngroups; ++g) c += gmax[g * nR + i] >= t;
+    }
+    if (c >= k) v = t;
+  }
+  if (v <= order_key(-INFINITY)) return;  // fewer than k groups: no bound
+  gkey[i] = max(gkey[i], order_key(f32_down((double)key_float(v) - (double)marg[i])));
+}
+
+__global__ void fill_zero_kernel(uint32_t* p, int64_t n) {
+  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) p[t] = 0;
 }
 
 // Whether the pass takes rows of qld operand bytes: as many R fragments as
@@ -420,22 +566,27 @@ bool stream_applies(dl_prec prec, int64_t qld, int64_t nR, int64_t nS) {
          (double)nR * (double)nS < 0x1p51;
 }
 
-template <int kPrec, int kKB>
+template <int kPrec, int kKB, int kMode>
 static hipError_t launch_stream_kb(StreamParams p, int64_t npad_r, hipStream_t st, int cu_count) {
   using G = StreamGeom<kPrec, kKB>;
   p.npad_r = npad_r;
   p.nst = (int)((p.c.nS + G::kStageRows - 1) / G::kStageRows);
+  if (kMode == kStreamMax) {
+    p.nst = (p.nst + p.stride - 1) / p.stride;
+    p.slot_strips = (p.nst * G::kStrips + p.nslots - 1) / p.nslots;
+  }
   // waves along R: as many as R fills, fewer while there are fewer than four
   // units per workgroup (a stage has to hold a strip for every wave along S,
   // and a self-join's block at least a stage)
   int wr = 8;
   const int wr_min = 8 / (G::kStrips < 8 ? G::kStrips : 8);
+  const bool tri = p.c.self_join;
   auto units_of = [&](int w) {
     const int64_t rows = (int64_t)w * G::kWaveRows, nrb = (p.c.nR + rows - 1) / rows;
     const int64_t spb = rows / G::kStageRows;
-    return nrb * p.nst - (p.c.self_join ? spb * (nrb * (nrb - 1) / 2) : 0);
+    return nrb * p.nst - (tri ? spb * (nrb * (nrb - 1) / 2) : 0);
   };
-  while (wr > wr_min && (!p.c.self_join || wr / 2 * G::kWaveRows >= G::kStageRows) &&
+  while (wr > wr_min && (!tri || wr / 2 * G::kWaveRows >= G::kStageRows) &&
          (p.c.nR <= (int64_t)(wr / 2) * G::kWaveRows || units_of(wr) < 4 * (int64_t)cu_count))
     wr /= 2;
   p.wr = wr;
@@ -445,31 +596,90 @@ static hipError_t launch_stream_kb(StreamParams p, int64_t npad_r, hipStream_t s
   p.units = units_of(wr);
   int64_t g = cu_count / 8 * 8;
   if (g > (p.units + 7) / 8 * 8) g = (p.units + 7) / 8 * 8;
-  hipLaunchKernelGGL((stream_eps_kernel<kPrec, kKB>), dim3((unsigned)g), dim3(kThreads), 0, st, p);
+  hipLaunchKernelGGL((stream_kernel<kPrec, kKB, kMode>), dim3((unsigned)g), dim3(kThreads), 0, st, p);
   return hipGetLastError();
 }
 
-template <int kPrec>
+template <int kMode, int kPrec>
 static hipError_t launch_stream_prec(const StreamParams& p, int64_t npad_r, hipStream_t st, int cu_count) {
   switch (p.c.qld) {
-    case 128: return launch_stream_kb<kPrec, 128>(p, npad_r, st, cu_count);
-    case 256: return launch_stream_kb<kPrec, 256>(p, npad_r, st, cu_count);
-    case 384: return launch_stream_kb<kPrec, 384>(p, npad_r, st, cu_count);
-    case 512: return launch_stream_kb<kPrec, 512>(p, npad_r, st, cu_count);
+    case 128: return launch_stream_kb<kPrec, 128, kMode>(p, npad_r, st, cu_count);
+    case 256: return launch_stream_kb<kPrec, 256, kMode>(p, npad_r, st, cu_count);
+    case 384: return launch_stream_kb<kPrec, 384, kMode>(p, npad_r, st, cu_count);
+    case 512: return launch_stream_kb<kPrec, 512, kMode>(p, npad_r, st, cu_count);
   }
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_stream_eps(dl_prec prec, const CandParams& c, int64_t npad_r, hipStream_t st, int cu_count) {
-  if (c.nR == 0 || c.nS == 0) return hipSuccess;
-  StreamParams p{};
-  p.c = c;
+template <int kMode>
+static hipError_t launch_stream(dl_prec prec, const StreamParams& p, int64_t npad_r, hipStream_t st, int cu_count) {
+  if (p.c.nR == 0 || p.c.nS == 0) return hipSuccess;
   switch (prec) {
-    case DL_BF16: return launch_stream_prec<DL_BF16>(p, npad_r, st, cu_count);
-    case DL_FP16: return launch_stream_prec<DL_FP16>(p, npad_r, st, cu_count);
-    case DL_FP8: return launch_stream_prec<DL_FP8>(p, npad_r, st, cu_count);
+    case DL_BF16: return launch_stream_prec<kMode, DL_BF16>(p, npad_r, st, cu_count);
+    case DL_FP16: return launch_stream_prec<kMode, DL_FP16>(p, npad_r, st, cu_count);
+    case DL_FP8: return launch_stream_prec<kMode, DL_FP8>(p, npad_r, st, cu_count);
     default: return hipErrorInvalidValue;
   }
+}
+
+hipError_t launch_stream_eps(dl_prec prec, const CandParams& c, int64_t npad_r, hipStream_t st, int cu_count) {
+  StreamParams p{};
+  p.c = c;
+  return launch_stream<kStreamEps>(prec, p, npad_r, st, cu_count);
+}
+
+// Groups of S rows whose maxima bound a row's k-th largest P~: a few times k,
+// so that the k largest rarely share one (ngroups / 4 runs of S rows, each
+// split over the four lane quarters).
+int stream_groups(int k) {
+  const int g = (4 * k + 63) / 64 * 64;
+  return g < 64 ? 64 : g;
+}
+
+// Whether the streaming top-k's thresholds exist (enough groups of S rows) or
+// are not needed (all of S fits a row's buffer, of at least kAllRows entries).
+constexpr int64_t kAllRows = 512;
+bool stream_band_applies(int64_t nS, int k) { return nS >= 16 * (int64_t)k || nS <= kAllRows; }
+
+// Top-k band of every row of R: the group maxima of a sample of S (every
+// stride-th stage) give each row's threshold, then the pass over all of S
+// stages what reaches it.  gmax: scratch of stream_groups(k) * nR words.
+// c.gkey holds what bounds are known (order keys), c.bcount zeros.
+//
+// The sample costs 1 / stride of a pass and leaves about stride times the
+// rows of the band itself to be staged, each at a price of about 250 cycles of
+// a wave; the sum is smallest where stride^2 is nS / 100 (k + 90) or so.  The
+// E4M3 margin is as wide as the spread of near rows, so its bands grow faster
+// as the threshold loosens and a buffer may not hold them (50,000 queries x
+// 4M rows, d = 256, top-32: stride 18 overflows buffers, 9 takes 64 ms of
+// call time, 4 takes 70): at most 8.
+//
+// Measured (one MI355X): top-10 of 200,000 x 200,000, d = 128, bf16: sample
+// 1.8 ms, thresholds 0.05, pass 8.6, against 21.4 ms for the tile form, whose
+// bands are tightened row by row inside the pass.
+hipError_t launch_stream_band(dl_prec prec, const CandParams& c, int64_t npad_r, int k, uint32_t* gmax, hipStream_t st,
+                              int cu_count) {
+  StreamParams p{};
+  p.c = c;
+  p.c.self_join = 0;
+  if (c.nR == 0 || c.nS == 0) return hipSuccess;
+  hipError_t e;
+  if (c.nS > kAllRows) {
+    const int ng = stream_groups(k);
+    p.stride = 1;
+    while ((int64_t)(p.stride + 1) * (p.stride + 1) * 100 * (k + 90) <= c.nS) ++p.stride;
+    if (prec == DL_FP8 && p.stride > 8) p.stride = 8;
+    p.nslots = ng / 4;
+    p.gmax = gmax;
+    hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)(cu_count * 4)), dim3(256), 0, st, gmax, ng * c.nR);
+    if ((e = launch_stream<kStreamMax>(prec, p, npad_r, st, cu_count)) != hipSuccess) return e;
+    const dim3 grid((unsigned)((c.nR + 63) / 64));
+    if (ng <= 64) hipLaunchKernelGGL(band_key_kernel<64>, grid, dim3(64), 0, st, gmax, ng, c.nR, k, c.marg, c.gkey);
+    else if (ng <= 128) hipLaunchKernelGGL(band_key_kernel<128>, grid, dim3(64), 0, st, gmax, ng, c.nR, k, c.marg, c.gkey);
+    else hipLaunchKernelGGL(band_key_kernel<0>, grid, dim3(64), 0, st, gmax, ng, c.nR, k, c.marg, c.gkey);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  return launch_stream<kStreamBand>(prec, p, npad_r, st, cu_count);
 }
 
 }  // namespace dl

@@ -46,3 +46,39 @@ def test_stream_every_pair(orc, prec):
     S = synth.uniform_rows(517, 128, seed=3, stream=1)
     assert_eps_equal(ops.join_eps(dev(R), dev(S), float("inf"), prec), orc.eps_join(R, S, float("inf")), 128, prec)
     assert_eps_equal(ops.join_eps(dev(S), None, float("inf"), prec), orc.eps_join(S, None, float("inf")), 128, prec)
+
+
+@pytest.mark.parametrize("prec,d", [("bf16", 64), ("bf16", 128), ("fp16", 100), ("fp16", 256), ("fp8", 256), ("fp8", 500)])
+def test_stream_topk_edges(orc, prec, d):
+    """Row blocks, strips and stages of the top-k band, the group maxima's
+    runs, S that fits a row's buffer whole, k from one to nearly all of S."""
+    from gpu_util import assert_topk_equal, dev
+    from paper_1812_07607_amd import ops
+    for nr, ns, k in [(1, 40, 5), (130, 511, 3), (257, 513, 32), (40, 9001, 10), (1025, 2100, 1), (70, 4500, 256)]:
+        R = synth.gaussian_mixture_unit(nr, d, 5, 0.05, seed=d, stream=0)
+        S = synth.gaussian_mixture_unit(ns, d, 5, 0.05, seed=d, stream=1)
+        j, _, dist = orc.topk(R, S, k)
+        assert_topk_equal(ops.join_topk(dev(R), dev(S), k, prec=prec), j, dist, d, "%s %dx%d k=%d" % (prec, nr, ns, k))
+    j, _, dist = orc.topk(S, None, 7, exclude_self=True)
+    got = ops.join_topk(dev(S), None, 7, exclude_self=True, prec=prec)
+    assert_topk_equal(got, j, dist, d, "%s self" % prec)
+
+
+def test_stream_topk_sample_misses_the_neighbours(orc):
+    """Every near row of S lies in stages the group maxima skip, and there are
+    more of them than a row's buffer holds: the rows' bounds are loose, the
+    buffers overflow, and the call still returns the oracle's rows."""
+    from gpu_util import assert_topk_equal, dev, host
+    from paper_1812_07607_amd import ops
+    rng = np.random.default_rng(5)
+    ns, d, k = 45000, 64, 10
+    S = synth.uniform_rows(ns, d, lo=2.0, hi=3.0, seed=1)
+    near = np.nonzero((np.arange(ns) // 256) % 2 == 1)[0]
+    near = rng.choice(near, size=4000, replace=False)
+    S[near] = synth.uniform_rows(4000, d, lo=-0.01, hi=0.01, seed=2)
+    R = synth.uniform_rows(70000, d, lo=-0.01, hi=0.01, seed=3)
+    got = ops.join_topk(dev(R), dev(S), k, prec="bf16")
+    rows = rng.choice(len(R), size=60, replace=False)
+    j, _, dist = orc.topk(R[rows], S, k)
+    got.j, got.dist = got.j[rows.tolist()], got.dist[rows.tolist()]
+    assert_topk_equal(got, j, dist, d, "sampled rows")
