@@ -71,7 +71,7 @@ hipError_t launch_cand_band(dl_prec, CandParams, hipStream_t);
 hipError_t launch_recheck_eps(const RecheckParams&, hipStream_t, int);
 hipError_t launch_pair_d2(const float*, int64_t, int64_t, const float*, int64_t, int64_t, int, const uint32_t*,
                           const uint32_t*, int64_t, double*, int*, hipStream_t, int);
-hipError_t launch_topk_select(const SelectParams&, bool, hipStream_t);
+hipError_t launch_topk_select(const SelectParams&, bool, bool, hipStream_t);
 hipError_t launch_topk_select_wide(const SelectParams&, hipStream_t);
 bool topk_select_small(int);
 int64_t row_sort_words(int64_t);
@@ -89,15 +89,13 @@ struct Counters {
   unsigned long long cand;   // candidates appended
   unsigned long long out;    // pairs confirmed
   unsigned long long ties;   // float64 decisions
-  unsigned long long band;   // top-k band entries
   int bad_index;
   int overflow;
   int too_many;
   int invalid;  // an input relation has a non-finite value or a row norm >= 2^62
-  int pad[12];
+  int pad[6];
 };
-static_assert(sizeof(Counters) == 96, "counter block size");
-static_assert(offsetof(Counters, band) == offsetof(Counters, ties) + 8, "ties and band are cleared together");
+static_assert(sizeof(Counters) == 64, "counter block size");
 
 // Sets *invalid when either relation holds a non-finite value or a row whose
 // norm reaches 2^62 (squared distances would overflow float32).  The
@@ -176,6 +174,7 @@ struct TopkLayout {
   Prep pr, ps;
   RelStats *sr, *ss;
   Counters* cnt;
+  SelectCount* sel;  // kSelectCounts of them
   float* marg;
   uint32_t* gkey;  // per row: best band threshold of any split so far (order key)
   uint2* band;
@@ -218,6 +217,7 @@ static TopkLayout layout_topk(void* ws, int64_t nR, int64_t nS, int d, dl_prec p
   TopkLayout L;
   Bump b(ws);
   L.cnt = b.take<Counters>(1);
+  L.sel = b.take<SelectCount>(kSelectCounts);
   L.sr = b.take<RelStats>(1);
   L.ss = (self || s_ext) ? L.sr : b.take<RelStats>(1);
   L.pr = carve_prep(b, nR, d, prec);
@@ -310,10 +310,15 @@ dl_status check_mat(dl_ctx* c, const dl_mat& m, const char* name) {
 
 bool prec_ok(int p) { return p == DL_FP32 || p == DL_BF16 || p == DL_FP16 || p == DL_FP8; }
 
+constexpr int kPinSelect = 32;  // the selection's counts in the pinned block
 // Counters and both relations' statistics into the pinned block, then wait:
 // the one host synchronisation of a join.
-hipError_t readback(dl_ctx* c, const Counters* cnt, const RelStats* sr, const RelStats* ss, hipStream_t st) {
+hipError_t readback(dl_ctx* c, const Counters* cnt, const RelStats* sr, const RelStats* ss, hipStream_t st,
+                    const SelectCount* sel = nullptr) {
   hipError_t e;
+  if (sel && (e = hipMemcpyAsync(c->pinned + kPinSelect, sel, kSelectCounts * sizeof(SelectCount),
+                                 hipMemcpyDeviceToHost, st)) != hipSuccess)
+    return e;
   if ((e = hipMemcpyAsync(c->pinned, cnt, sizeof(Counters), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
   if ((e = hipMemcpyAsync(c->pinned + 12, sr, sizeof(RelStats), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
   if ((e = hipMemcpyAsync(c->pinned + 20, ss, sizeof(RelStats), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
@@ -381,7 +386,7 @@ dl_status dl_create(int device, dl_ctx** out) {
   c->device = device;
   c->pending = new (std::nothrow) std::vector<dl_ctx::Rec>();
   if (hipSetDevice(device) != hipSuccess || !c->pending ||
-      hipHostMalloc(reinterpret_cast<void**>(&c->pinned), 256, hipHostMallocDefault) != hipSuccess) {
+      hipHostMalloc(reinterpret_cast<void**>(&c->pinned), 4096, hipHostMallocDefault) != hipSuccess) {
     delete c->pending;
     delete c;
     return DL_ERR_DEVICE;
@@ -743,6 +748,11 @@ dl_status topk_core(dl_ctx* c, const TopkJob& J, void* ws, size_t ws_bytes, uint
   }
   hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t*>(L.cnt),
                      (int64_t)(sizeof(Counters) / 4));
+  auto zero_counts = [&]() {
+    hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(256), 0, st, reinterpret_cast<uint32_t*>(L.sel),
+                       (int64_t)(kSelectCounts * sizeof(SelectCount) / 4));
+  };
+  zero_counts();
   hipLaunchKernelGGL(zero_words_kernel, dim3(64), dim3(256), 0, st, reinterpret_cast<uint32_t*>(L.rstate), R.n);
   hipLaunchKernelGGL(zero_words_kernel, dim3(64), dim3(256), 0, st, reinterpret_cast<uint32_t*>(L.wide), R.n);
   if (S.n == 0 || J.surv || stream) {
@@ -814,16 +824,17 @@ dl_status topk_core(dl_ctx* c, const TopkJob& J, void* ws, size_t ws_bytes, uint
       q.P = stream ? 1 : P;
       q.cap = stream ? P * band_cap : band_cap;
       q.marg = L.marg;
+      q.nrm2R = L.pr.nrm2;
       q.xnR = L.pr.xnorm; q.mlR = L.pr.mlsb;
       q.sS = L.ss;
       q.out_j = out_j; q.out_dist = out_dist;
-      q.nband = &L.cnt->band; q.nties = &L.cnt->ties; q.too_many = &L.cnt->too_many;
+      q.counts = L.sel; q.too_many = &L.cnt->too_many;
       q.gate = &L.cnt->invalid;
       q.rstate = L.rstate;
       q.wide = L.wide;
-      DL_HIP(c, launch_topk_select(q, small_sel, st));
+      DL_HIP(c, launch_topk_select(q, small_sel, prec == DL_FP8, st));
     }
-    DL_HIP(c, readback(c, L.cnt, L.sr, L.ss, st));
+    DL_HIP(c, readback(c, L.cnt, L.sr, L.ss, st, L.sel));
     hc = *reinterpret_cast<const Counters*>(c->pinned);
     if (!(stream && hc.overflow)) break;
     // the tile form from the thresholds found (the gate stays as it is)
@@ -835,22 +846,22 @@ dl_status topk_core(dl_ctx* c, const TopkJob& J, void* ws, size_t ws_bytes, uint
     }
     hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t*>(L.cnt),
                        (int64_t)(offsetof(Counters, invalid) / 4));
+    zero_counts();
     hipLaunchKernelGGL(zero_words_kernel, dim3(64), dim3(256), 0, st, reinterpret_cast<uint32_t*>(L.rstate), R.n);
     hipLaunchKernelGGL(zero_words_kernel, dim3(64), dim3(256), 0, st, reinterpret_cast<uint32_t*>(L.wide), R.n);
   }
   if (small_sel && hc.too_many && !hc.overflow) {
     // a row had more near-tie contenders than the small selection holds:
     // select again (the bands are unchanged) with the large one
-    hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t*>(&L.cnt->ties),
-                       (int64_t)4);  // ties and band
+    zero_counts();
     hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t*>(&L.cnt->too_many),
                        (int64_t)1);
     hipLaunchKernelGGL(zero_words_kernel, dim3(64), dim3(256), 0, st, reinterpret_cast<uint32_t*>(L.wide), R.n);
     {
       StageTimer t(c, 5, st);
-      DL_HIP(c, launch_topk_select(q, false, st));
+      DL_HIP(c, launch_topk_select(q, false, prec == DL_FP8, st));
     }
-    DL_HIP(c, readback(c, L.cnt, L.sr, L.ss, st));
+    DL_HIP(c, readback(c, L.cnt, L.sr, L.ss, st, L.sel));
     hc = *reinterpret_cast<const Counters*>(c->pinned);
   }
   if (hc.too_many && !hc.overflow) {
@@ -862,12 +873,15 @@ dl_status topk_core(dl_ctx* c, const TopkJob& J, void* ws, size_t ws_bytes, uint
       StageTimer t(c, 5, st);
       DL_HIP(c, launch_topk_select_wide(q, st));
     }
-    DL_HIP(c, readback(c, L.cnt, L.sr, L.ss, st));
+    DL_HIP(c, readback(c, L.cnt, L.sr, L.ss, st, L.sel));
     hc = *reinterpret_cast<const Counters*>(c->pinned);
   }
   if (info) {
-    info->band_entries = (int64_t)hc.band;
-    info->ties = (int64_t)hc.ties;
+    const SelectCount* n = reinterpret_cast<const SelectCount*>(c->pinned + kPinSelect);
+    for (int t = 0; t < kSelectCounts; ++t) {
+      info->band_entries += (int64_t)n[t].band;
+      info->ties += (int64_t)n[t].ties;
+    }
   }
   if (dl_status bad = check_inputs(c)) return bad;
   if (hc.overflow || hc.too_many) {

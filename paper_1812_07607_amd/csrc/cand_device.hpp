@@ -60,27 +60,53 @@ __device__ inline int fresh_lane() {
 
 constexpr int kQueue = 256;  // staged hits per wave (eps candidates or band entries)
 
-// Appends a wave's staged (i, j) candidates to the global list: one atomic
-// for the whole batch, then coalesced stores.  Positions past the list's
-// capacity are counted but not written (the caller then retries with room).
-// With kP, each record's P~ (qp, staged beside q) goes to p.candp too.
+// Writes a wave's staged (i, j) candidates to the global list from slot base
+// on.  Positions past the list's capacity are counted but not written (the
+// caller then retries with room).  With kP, each record's P~ (qp, staged
+// beside q) goes to p.candp too.
 template <bool kP>
-__device__ inline void flush_eps(const CandParams& p, const uint2* q, const uint32_t* qp, int nq) {
-  const int lane = fresh_lane();
-  unsigned long long base = 0;
-  if (lane == 0) base = atomicAdd(p.ccount, (unsigned long long)nq);
-  base = ((unsigned long long)__builtin_amdgcn_readfirstlane((uint32_t)(base >> 32)) << 32) |
-         __builtin_amdgcn_readfirstlane((uint32_t)base);
+__device__ inline void write_eps(const CandParams& p, const uint2* q, const uint32_t* qp, int nq,
+                                 unsigned long long base) {
   // the records that fit; addresses are a scalar base and a 32-bit offset
   const unsigned long long cap = (unsigned long long)p.ccap;
   const int fit = base >= cap ? 0 : (cap - base < (unsigned long long)nq ? (int)(cap - base) : nq);
   uint2* const dst = p.cand + base;
   float* const dstp = kP && p.candp ? p.candp + base : nullptr;
-  for (int s = lane; s < fit; s += 64) {
+  for (int s = fresh_lane(); s < fit; s += 64) {
     dst[s] = q[s];
     if constexpr (kP)
       if (dstp) dstp[s] = __uint_as_float(qp[s]);
   }
+}
+
+// The wave's staged candidates, with one atomic for the whole batch.
+template <bool kP>
+__device__ inline void flush_eps(const CandParams& p, const uint2* q, const uint32_t* qp, int nq) {
+  unsigned long long base = 0;
+  if (fresh_lane() == 0) base = atomicAdd(p.ccount, (unsigned long long)nq);
+  write_eps<kP>(p, q, qp, nq, (unsigned long long)uniform64((int64_t)base));
+}
+
+// What every wave of the workgroup has left, at the end of its work: one
+// atomic for the workgroup (one counter serves the whole grid, and its atomics
+// queue at 10 ns or more each, so one per wave would add 20 us to a call).
+// s_left: one word per wave and two for the base; every wave calls it.
+template <bool kP>
+__device__ inline void flush_eps_last(const CandParams& p, const uint2* q, const uint32_t* qp, int nq, int* s_left) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  unsigned long long* const s_base = reinterpret_cast<unsigned long long*>(s_left + kThreads / 64);
+  if ((threadIdx.x & 63) == 0) s_left[wave] = nq;
+  __syncthreads();
+  int before = 0, all = 0;
+  for (int w = 0; w < kThreads / 64; ++w) {
+    const int n = __builtin_amdgcn_readfirstlane(s_left[w]);
+    if (w < wave) before += n;
+    all += n;
+  }
+  if (all == 0) return;
+  if (threadIdx.x == 0) *s_base = atomicAdd(p.ccount, (unsigned long long)all);
+  __syncthreads();
+  write_eps<kP>(p, q, qp, nq, (unsigned long long)uniform64((int64_t)*s_base) + before);
 }
 
 }  // namespace dl

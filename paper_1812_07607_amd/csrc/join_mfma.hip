@@ -1151,7 +1151,8 @@ __global__ __launch_bounds__(kThreads, 1) void cand_kernel(CandParams p) {
     }
   }
   if constexpr (kQ) {
-    if (eq) flush_eps<kStageP>(p, lds_eq[wave], lds_eqp[kStageP ? wave : 0], eq);
+    __shared__ __attribute__((aligned(8))) int s_left[kThreads / 64 + 2];
+    flush_eps_last<kStageP>(p, lds_eq[wave], lds_eqp[kStageP ? wave : 0], eq, s_left);
   } else if constexpr (!kEps) {
     __syncthreads();
     tighten_rows(p, ti, split, band, true);

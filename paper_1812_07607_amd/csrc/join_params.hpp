@@ -112,6 +112,15 @@ struct RecheckParams {
   int swap;
 };
 
+// Counts of the selection, spread over cache lines of their own (summed by the
+// host).
+struct SelectCount {
+  unsigned long long band;  // entries in the exact band
+  unsigned long long ties;  // entries ordered in float64
+  unsigned long long pad[6];
+};
+constexpr int kSelectCounts = 32;
+
 // top-k exact selection (recheck.hip).
 struct SelectParams {
   const float* R; int64_t ldr;
@@ -119,10 +128,11 @@ struct SelectParams {
   int d; int64_t nR;
   uint2* band; const int* bcount; int P; int cap; int k;
   const float* marg;
+  const double* nrm2R;  // |a|^2 per R row (float64)
   const float* xnR; const int* mlR;
   const RelStats* sS;  // S maxima: xnorm_max, mlsb_min
   uint32_t* out_j; float* out_dist;
-  unsigned long long* nband; unsigned long long* nties; int* too_many;
+  SelectCount* counts; int* too_many;
   const int* gate;  // nonzero: invalid input, every row is written as padding
   // per row (nullable): rstate 1 once a selection over memory has replaced
   // the row's band P~ by float32 d2; wide 1 when the row had more near-tie

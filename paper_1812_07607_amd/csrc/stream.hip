@@ -518,40 +518,46 @@ __global__ __launch_bounds__(kThreads, 1) void stream_kernel(StreamParams p) {
       }
     }
   }
-  if (nq) flush();
+  if constexpr (kMode == kStreamEps) {
+    __shared__ __attribute__((aligned(8))) int s_left[kThreads / 64 + 2];
+    flush_eps_last<kStageP>(p.c, eq_lds[wave], eqp_lds[kStageP ? wave : 0], nq, s_left);
+  } else if constexpr (kMode == kStreamBand) {
+    if (nq) flush();
+  }
 }
 
 // The k-th largest of each row's ngroups group maxima (order keys, group-major,
 // zero where a group is empty), minus the row's margin, as the row's band
 // threshold.  The groups partition a subset of S, so at least k rows of S have
 // a P~ at or above it: the band P~ >= v - E_i keeps every one of the k
-// nearest, as in the tile form's tightening.  One thread per row; the keys are
-// held in registers when there are at most kRegs of them.
-template <int kRegs>
+// nearest, as in the tile form's tightening.  kPer lanes share a row, each
+// with kKeys of its keys in registers, 64 / kPer rows side by side in a wave.
+constexpr int kKeys = 64;
+template <int kPer>
 __global__ __launch_bounds__(64) void band_key_kernel(const uint32_t* __restrict__ gmax, int ngroups, int64_t nR, int k,
                                                       const float* __restrict__ marg, uint32_t* __restrict__ gkey) {
-  const int64_t i = (int64_t)blockIdx.x * 64 + threadIdx.x;
-  if (i >= nR) return;
-  uint32_t key[kRegs ? kRegs : 1];
-  if constexpr (kRegs > 0) {
+  constexpr int kRows = 64 / kPer;
+  const int part = threadIdx.x / kRows;
+  const int64_t i = (int64_t)blockIdx.x * kRows + threadIdx.x % kRows;
+  uint32_t key[kKeys];
 #pragma unroll
-    for (int g = 0; g < kRegs; ++g) key[g] = g < ngroups ? gmax[g * nR + i] : 0u;
+  for (int t = 0; t < kKeys; ++t) {
+    const int g = t * kPer + part;
+    key[t] = g < ngroups && i < nR ? gmax[(int64_t)g * nR + i] : 0u;
   }
   uint32_t v = 0;  // largest key with at least k group maxima at or above it
   for (int b = 31; b >= 0; --b) {
-    const uint32_t t = v | (1u << b);
+    const uint32_t cand = v | (1u << b);
     int c = 0;
-    if constexpr (kRegs > 0) {
 #pragma unroll
-      for (int g = 0; g < kRegs; ++g) c += key[g] >= t;
-    } else {
-#pragma unroll 8
-      for (int g = 0; g < ngroups; ++g) c += gmax[g * nR + i] >= t;
-    }
-    if (c >= k) v = t;
+    for (int t = 0; t < kKeys; ++t) c += key[t] >= cand;
+#pragma unroll
+    for (int o = kRows; o < 64; o <<= 1) c += __shfl_xor(c, o, 64);
+    if (c >= k) v = cand;
   }
-  if (v <= order_key(-INFINITY)) return;  // fewer than k groups: no bound
-  gkey[i] = max(gkey[i], order_key(f32_down((double)key_float(v) - (double)marg[i])));
+  // (fewer than k groups: no bound)
+  if (part == 0 && i < nR && v > order_key(-INFINITY))
+    gkey[i] = max(gkey[i], order_key(f32_down((double)key_float(v) - (double)marg[i])));
 }
 
 __global__ void fill_zero_kernel(uint32_t* p, int64_t n) {
@@ -673,10 +679,17 @@ hipError_t launch_stream_band(dl_prec prec, const CandParams& c, int64_t npad_r,
     p.gmax = gmax;
     hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)(cu_count * 4)), dim3(256), 0, st, gmax, ng * c.nR);
     if ((e = launch_stream<kStreamMax>(prec, p, npad_r, st, cu_count)) != hipSuccess) return e;
-    const dim3 grid((unsigned)((c.nR + 63) / 64));
-    if (ng <= 64) hipLaunchKernelGGL(band_key_kernel<64>, grid, dim3(64), 0, st, gmax, ng, c.nR, k, c.marg, c.gkey);
-    else if (ng <= 128) hipLaunchKernelGGL(band_key_kernel<128>, grid, dim3(64), 0, st, gmax, ng, c.nR, k, c.marg, c.gkey);
-    else hipLaunchKernelGGL(band_key_kernel<0>, grid, dim3(64), 0, st, gmax, ng, c.nR, k, c.marg, c.gkey);
+    int per = 1;
+    while (per * kKeys < ng) per *= 2;
+    const dim3 grid((unsigned)((c.nR + 64 / per - 1) / (64 / per))), block(64);
+    switch (per) {
+      case 1: hipLaunchKernelGGL(band_key_kernel<1>, grid, block, 0, st, gmax, ng, c.nR, k, c.marg, c.gkey); break;
+      case 2: hipLaunchKernelGGL(band_key_kernel<2>, grid, block, 0, st, gmax, ng, c.nR, k, c.marg, c.gkey); break;
+      case 4: hipLaunchKernelGGL(band_key_kernel<4>, grid, block, 0, st, gmax, ng, c.nR, k, c.marg, c.gkey); break;
+      case 8: hipLaunchKernelGGL(band_key_kernel<8>, grid, block, 0, st, gmax, ng, c.nR, k, c.marg, c.gkey); break;
+      case 16: hipLaunchKernelGGL(band_key_kernel<16>, grid, block, 0, st, gmax, ng, c.nR, k, c.marg, c.gkey); break;
+      default: hipLaunchKernelGGL(band_key_kernel<32>, grid, block, 0, st, gmax, ng, c.nR, k, c.marg, c.gkey); break;
+    }
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return launch_stream<kStreamBand>(prec, p, npad_r, st, cu_count);
