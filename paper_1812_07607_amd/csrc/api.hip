@@ -9,6 +9,7 @@
 #include <new>
 
 #include "core.hpp"
+#include "join_params.hpp"
 
 namespace dl {
 // featurize.hip
@@ -22,14 +23,16 @@ hipError_t launch_stats_init(RelStats*, hipStream_t);
 hipError_t launch_stats_reduce(const Prep&, int64_t, RelStats*, hipStream_t, int);
 hipError_t launch_prep(const float*, int64_t, int32_t, int64_t, dl_prec, const Prep&, RelStats*, hipStream_t, int,
                        const uint32_t* perm = nullptr);
+hipError_t launch_prep_pair(const PrepPair&, int32_t, dl_prec, hipStream_t, int);
+hipError_t launch_call_init(CallState*, int, uint32_t*, int64_t, uint32_t*, int64_t, uint32_t*, int64_t, hipStream_t,
+                            int);
+hipError_t launch_zero_ranges(uint32_t*, int64_t, uint32_t*, int64_t, uint32_t*, int64_t, uint32_t*, int64_t,
+                              hipStream_t, int);
+hipError_t launch_publish(const void*, int, void*, hipStream_t);
 hipError_t launch_threshold(const Prep&, int64_t, const RelStats*, int, double, const double*, float*, float*, int*,
-                            uint32_t*, hipStream_t);
+                            uint32_t*, hipStream_t, const RelStats*, CallState*);
 hipError_t launch_band_seed(const Prep&, int64_t, const float*, int, const float*, uint32_t*, hipStream_t);
-}  // namespace dl
-
-#include "join_params.hpp"
-
-namespace dl {
+// join_mfma.hip, stream.hip
 hipError_t launch_cand_eps(dl_prec, CandParams, hipStream_t, int);
 hipError_t launch_cand_list(dl_prec, CandParams, hipStream_t, int);
 bool stream_applies(dl_prec, int64_t, int64_t, int64_t);
@@ -75,36 +78,13 @@ hipError_t launch_topk_select(const SelectParams&, bool, bool, hipStream_t);
 hipError_t launch_topk_select_wide(const SelectParams&, hipStream_t);
 bool topk_select_small(int);
 int64_t row_sort_words(int64_t);
-hipError_t row_sort_pairs(const unsigned long long*, const float*, int64_t, int64_t, int, unsigned long long*, float*,
-                          uint32_t*, int64_t, uint32_t*, uint32_t*, float*, hipStream_t, int);
+hipError_t row_sort_pairs(const unsigned long long*, const float*, const Counters*, int64_t, int64_t, int,
+                          unsigned long long*, float*, uint32_t*, int64_t, uint32_t*, uint32_t*, float*, hipStream_t,
+                          int);
 
 // ------------------------------------------------------------ small kernels
 __global__ void zero_words_kernel(uint32_t* p, int64_t n) {
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) p[t] = 0;
-}
-
-// Device-side counters of one call (zeroed by a kernel, so the sequence can
-// be captured in a graph).
-struct Counters {
-  unsigned long long cand;   // candidates appended
-  unsigned long long out;    // pairs confirmed
-  unsigned long long ties;   // float64 decisions
-  int bad_index;
-  int overflow;
-  int too_many;
-  int invalid;  // an input relation has a non-finite value or a row norm >= 2^62
-  int pad[6];
-};
-static_assert(sizeof(Counters) == 64, "counter block size");
-
-// Sets *invalid when either relation holds a non-finite value or a row whose
-// norm reaches 2^62 (squared distances would overflow float32).  The
-// candidate and selection kernels read the flag first and do no work when it
-// is set, so bad input costs prep, not a whole join, before the call reports
-// DL_ERR_INVALID.
-__global__ void input_gate_kernel(const RelStats* r, const RelStats* s, int* invalid) {
-  if (threadIdx.x == 0)
-    *invalid = (r->nonfinite || s->nonfinite || !(r->xnorm_max < 0x1p62f) || !(s->xnorm_max < 0x1p62f)) ? 1 : 0;
 }
 
 // ------------------------------------------------------------ workspace
@@ -127,6 +107,7 @@ static Prep carve_prep(Bump& b, int64_t n, int d, dl_prec prec) {
 }
 
 struct EpsLayout {
+  CallState* state;
   Prep pr, ps;
   RelStats *sr, *ss;
   Counters* cnt;
@@ -146,9 +127,10 @@ static EpsLayout layout_eps(void* ws, int64_t nR, int64_t nS, int d, dl_prec pre
                             bool s_ext = false, bool r_ext = false) {
   EpsLayout L;
   Bump b(ws);
-  L.cnt = b.take<Counters>(1);
-  L.sr = b.take<RelStats>(1);
-  L.ss = (self || s_ext) ? L.sr : b.take<RelStats>(1);
+  L.state = reinterpret_cast<CallState*>(b.take<uint64_t>(kStateWords));  // without the selection's counts
+  L.cnt = &L.state->c;
+  L.sr = &L.state->r;
+  L.ss = (self || s_ext) ? L.sr : &L.state->s;
   if (r_ext) {  // R's operand copy comes from a store: only its row count matters below
     L.pr = Prep{};
     L.pr.npad = round_up(nR < 1 ? 1 : nR, kTile);
@@ -171,10 +153,10 @@ static EpsLayout layout_eps(void* ws, int64_t nR, int64_t nS, int d, dl_prec pre
 }
 
 struct TopkLayout {
+  CallState* state;
   Prep pr, ps;
   RelStats *sr, *ss;
   Counters* cnt;
-  SelectCount* sel;  // kSelectCounts of them
   float* marg;
   uint32_t* gkey;  // per row: best band threshold of any split so far (order key)
   uint2* band;
@@ -216,10 +198,10 @@ static TopkLayout layout_topk(void* ws, int64_t nR, int64_t nS, int d, dl_prec p
                               bool s_ext = false) {
   TopkLayout L;
   Bump b(ws);
-  L.cnt = b.take<Counters>(1);
-  L.sel = b.take<SelectCount>(kSelectCounts);
-  L.sr = b.take<RelStats>(1);
-  L.ss = (self || s_ext) ? L.sr : b.take<RelStats>(1);
+  L.state = b.take<CallState>(1);
+  L.cnt = &L.state->c;
+  L.sr = &L.state->r;
+  L.ss = (self || s_ext) ? L.sr : &L.state->s;
   L.pr = carve_prep(b, nR, d, prec);
   L.ps = (self || s_ext) ? L.pr : carve_prep(b, nS, d, prec);
   L.marg = b.take<float>(L.pr.npad);
@@ -310,26 +292,23 @@ dl_status check_mat(dl_ctx* c, const dl_mat& m, const char* name) {
 
 bool prec_ok(int p) { return p == DL_FP32 || p == DL_BF16 || p == DL_FP16 || p == DL_FP8; }
 
-constexpr int kPinSelect = 32;  // the selection's counts in the pinned block
-// Counters and both relations' statistics into the pinned block, then wait:
-// the one host synchronisation of a join.
-hipError_t readback(dl_ctx* c, const Counters* cnt, const RelStats* sr, const RelStats* ss, hipStream_t st,
-                    const SelectCount* sel = nullptr) {
-  hipError_t e;
-  if (sel && (e = hipMemcpyAsync(c->pinned + kPinSelect, sel, kSelectCounts * sizeof(SelectCount),
-                                 hipMemcpyDeviceToHost, st)) != hipSuccess)
-    return e;
-  if ((e = hipMemcpyAsync(c->pinned, cnt, sizeof(Counters), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
-  if ((e = hipMemcpyAsync(c->pinned + 12, sr, sizeof(RelStats), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
-  if ((e = hipMemcpyAsync(c->pinned + 20, ss, sizeof(RelStats), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
-  return hipStreamSynchronize(st);
+// The call's state into the pinned block (words of it), where `ready` says
+// that it is there.  Work queued behind it runs on while the host waits.
+hipError_t publish(dl_ctx* c, const CallState* state, int words, hipStream_t st) {
+  const hipError_t e = launch_publish(state, words, c->pinned, st);
+  return e != hipSuccess ? e : hipEventRecord(c->ready, st);
 }
+const CallState& published(const dl_ctx* c) { return *reinterpret_cast<const CallState*>(c->pinned); }
+
+// Pinned words that other read-backs use, behind the state.
+constexpr int kPinFree = sizeof(CallState) / 8;
+constexpr int kPinRows = kPinFree, kPinPairs = kPinFree + 2, kPinTiles = kPinFree + 3, kPinSteps = kPinFree + 4,
+              kPinBox = kPinFree + 5, kPinStats = kPinFree + 6;
+static_assert((kPinStats + (int)sizeof(RelStats) / 8) * 8 <= 4096, "pinned block");
 
 // Rows must be finite, and |x| < 2^62 so that every squared distance
 // (at most (|a| + |b|)^2 < 2^126) and norm is finite in float32.
-dl_status check_inputs(dl_ctx* c) {
-  const RelStats* r = reinterpret_cast<const RelStats*>(c->pinned + 12);
-  const RelStats* s = reinterpret_cast<const RelStats*>(c->pinned + 20);
+dl_status check_inputs(dl_ctx* c, const RelStats* r, const RelStats* s) {
   if (r->nonfinite || s->nonfinite)
     return fail(c, DL_ERR_INVALID, "non-finite values in R (%d) or S (%d)", r->nonfinite, s->nonfinite);
   if (!(r->xnorm_max < 0x1p62f) || !(s->xnorm_max < 0x1p62f))
@@ -391,6 +370,12 @@ dl_status dl_create(int device, dl_ctx** out) {
     delete c;
     return DL_ERR_DEVICE;
   }
+  if (hipEventCreateWithFlags(&c->ready, hipEventDisableTiming) != hipSuccess) {
+    (void)hipHostFree(c->pinned);
+    delete c->pending;
+    delete c;
+    return DL_ERR_DEVICE;
+  }
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, device) == hipSuccess) c->cu_count = prop.multiProcessorCount;
   c->scratch = scratch_of(device, &c->scratch_err);
@@ -407,6 +392,7 @@ void dl_destroy(dl_ctx* c) {
     }
     delete c->pending;
   }
+  if (c->ready) (void)hipEventDestroy(c->ready);
   if (c->pinned) (void)hipHostFree(c->pinned);
   delete c;
 }
@@ -480,7 +466,7 @@ dl_status dl_featurize_crops_rgb8(dl_ctx* c, const uint8_t* frames, int64_t nfra
   DL_HIP(c, hipSetDevice(c->device));
   hipStream_t st = static_cast<hipStream_t>(stream);
   // bad-box flag: a plain store into the context's pinned host block
-  volatile int* bad = reinterpret_cast<volatile int*>(c->pinned + 30);
+  volatile int* bad = reinterpret_cast<volatile int*>(c->pinned + kPinBox);
   *bad = 0;
   {
     StageTimer t(c, 0, st);
@@ -573,6 +559,39 @@ size_t topk_workspace(int64_t nR, int64_t nS, int d, dl_prec prec, bool self, bo
   return b;
 }
 
+// Prep of a join's relations into its state's maxima (cleared by the call's
+// init): P null where the operand copy comes from elsewhere.
+static hipError_t prep_relations(dl_ctx* c, const dl_mat& R, const Prep* PR, const uint32_t* permR, const dl_mat& S,
+                                 const Prep* PS, const uint32_t* permS, dl_prec prec, CallState* state,
+                                 hipStream_t st) {
+  PrepPair pair{};
+  int n = 0;
+  if (PR) pair.j[n++] = PrepJob{R.data, R.n, R.ld, *PR, &state->r, permR};
+  if (PS) pair.j[n++] = PrepJob{S.data, S.n, S.ld, *PS, &state->s, permS};
+  return n ? launch_prep_pair(pair, R.d, prec, st, c->cu_count) : hipSuccess;
+}
+
+// The end of an eps call: the state goes to the host while the pairs are put
+// in order (the device reads their number; the outputs hold `capacity`).  The
+// ordering of a call that keeps pairs may still run on return, as its outputs
+// belong to the stream; nothing is in flight otherwise.
+static dl_status order_and_wait(dl_ctx* c, const EpsLayout& L, int64_t cap, int64_t nR, int bj, dl_pairs* out,
+                                hipStream_t st) {
+  DL_HIP(c, publish(c, L.state, kStateWords, st));
+  {
+    StageTimer t(c, 4, st);
+    DL_HIP(c, row_sort_pairs(L.k0, L.v0, L.cnt, cap, nR, bj, L.k1, L.v1, L.rows, out->capacity, out->i, out->j,
+                             out->dist, st, c->cu_count));
+  }
+  DL_HIP(c, hipEventSynchronize(c->ready));
+  const CallState& h = published(c);
+  if (h.c.out == 0 || (int64_t)h.c.cand > cap || h.c.invalid) DL_HIP(c, hipStreamSynchronize(st));
+  if (dl_status bad = check_inputs(c, &h.r, &h.s)) return bad;
+  out->candidates = (int64_t)h.c.cand;
+  out->ties = (int64_t)h.c.ties;
+  return DL_OK;
+}
+
 dl_status eps_core(dl_ctx* c, const EpsJob& J, void* ws, size_t ws_bytes, dl_pairs* out, hipStream_t st) {
   const dl_mat &R = J.R, &S = J.S;
   const bool self = J.self, sx = J.ps_ext != nullptr, rx = J.pr_ext != nullptr;
@@ -606,14 +625,12 @@ dl_status eps_core(dl_ctx* c, const EpsJob& J, void* ws, size_t ws_bytes, dl_pai
     L.ps = *J.ps_ext;
     L.ss = J.ss_ext;
   }
-  hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t*>(L.cnt),
-                     (int64_t)(sizeof(Counters) / 4));
   {
     StageTimer t(c, 1, st);
-    if (!rx) DL_HIP(c, launch_prep(R.data, R.n, R.d, R.ld, prec, L.pr, L.sr, st, c->cu_count));
-    if (!self && !sx) DL_HIP(c, launch_prep(S.data, S.n, S.d, S.ld, prec, L.ps, L.ss, st, c->cu_count));
-    hipLaunchKernelGGL(input_gate_kernel, dim3(1), dim3(64), 0, st, L.sr, L.ss, &L.cnt->invalid);
-    DL_HIP(c, launch_threshold(L.pr, R.n, L.ss, R.d, J.T, J.Trow, L.thr, nullptr, L.pex, nullptr, st));
+    DL_HIP(c, launch_call_init(L.state, 2 * kStateWords, L.rows, R.n + 1, nullptr, 0, nullptr, 0, st, c->cu_count));
+    DL_HIP(c, prep_relations(c, R, rx ? nullptr : &L.pr, nullptr, S, self || sx ? nullptr : &L.ps, nullptr, prec,
+                             L.state, st));
+    DL_HIP(c, launch_threshold(L.pr, R.n, L.ss, R.d, J.T, J.Trow, L.thr, nullptr, L.pex, nullptr, st, L.sr, L.state));
   }
   {
     StageTimer t(c, 2, st);
@@ -655,14 +672,11 @@ dl_status eps_core(dl_ctx* c, const EpsJob& J, void* ws, size_t ws_bytes, dl_pai
     q.T = J.T;
     q.Trow = J.Trow;
     q.bj = bj;
-    q.keys = L.k0; q.dist = L.v0; q.ocount = &L.cnt->out; q.nties = &L.cnt->ties;
+    q.keys = L.k0; q.dist = L.v0; q.ocount = &L.cnt->out; q.nties = &L.cnt->ties; q.rowcnt = L.rows;
     DL_HIP(c, launch_recheck_eps(q, st, c->cu_count));
   }
-  DL_HIP(c, readback(c, L.cnt, L.sr, L.ss, st));
-  const Counters hc = *reinterpret_cast<const Counters*>(c->pinned);
-  if (dl_status bad = check_inputs(c)) return bad;
-  out->candidates = (int64_t)hc.cand;
-  out->ties = (int64_t)hc.ties;
+  if (dl_status s = order_and_wait(c, L, cap, R.n, bj, out, st)) return s;
+  const Counters hc = published(c).c;
   if ((int64_t)hc.cand > cap && cap == kMaxPairs)
     return fail(c, DL_ERR_CAPACITY, "%llu candidates exceed the %lld one call can order; split R", hc.cand,
                 (long long)kMaxPairs);
@@ -671,16 +685,9 @@ dl_status eps_core(dl_ctx* c, const EpsJob& J, void* ws, size_t ws_bytes, dl_pai
         layout_eps(nullptr, R.n, S.n, R.d, prec, self, (int64_t)hc.cand + (int64_t)hc.cand / 8 + 1024, sx).bytes;
     return fail(c, DL_ERR_WORKSPACE, "%llu candidates exceed the workspace capacity %lld", hc.cand, (long long)cap);
   }
-  const int64_t m = (int64_t)hc.out;
-  out->count = m;
-  {
-    StageTimer t(c, 4, st);
-    const int64_t w = m < out->capacity ? m : out->capacity;
-    DL_HIP(c, row_sort_pairs(L.k0, L.v0, m, R.n, bj, L.k1, L.v1, L.rows, w, out->i, out->j, out->dist, st,
-                             c->cu_count));
-  }
-  if (m > out->capacity)
-    return fail(c, DL_ERR_CAPACITY, "%lld pairs exceed the output capacity %lld", (long long)m,
+  out->count = (int64_t)hc.out;
+  if (out->count > out->capacity)
+    return fail(c, DL_ERR_CAPACITY, "%lld pairs exceed the output capacity %lld", (long long)out->count,
                 (long long)out->capacity);
   return DL_OK;
 }
@@ -746,33 +753,39 @@ dl_status topk_core(dl_ctx* c, const TopkJob& J, void* ws, size_t ws_bytes, uint
       L.ss = L.sr;
     }
   }
-  hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t*>(L.cnt),
-                     (int64_t)(sizeof(Counters) / 4));
-  auto zero_counts = [&]() {
-    hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(256), 0, st, reinterpret_cast<uint32_t*>(L.sel),
-                       (int64_t)(kSelectCounts * sizeof(SelectCount) / 4));
-  };
-  zero_counts();
-  hipLaunchKernelGGL(zero_words_kernel, dim3(64), dim3(256), 0, st, reinterpret_cast<uint32_t*>(L.rstate), R.n);
-  hipLaunchKernelGGL(zero_words_kernel, dim3(64), dim3(256), 0, st, reinterpret_cast<uint32_t*>(L.wide), R.n);
-  if (S.n == 0 || J.surv || stream) {
-    // nothing to match (every row is padding), work items whose tiles the
-    // index rules out all (they store no count), or rows' own counters
-    hipLaunchKernelGGL(zero_words_kernel, dim3(256), dim3(256), 0, st, reinterpret_cast<uint32_t*>(L.bcount),
-                       stream ? R.n : R.n * (int64_t)P);
-  }
+  // Counters and rows' words: bcount only where a row's or a work item's
+  // count may not be stored: nothing to match (every row is padding), work
+  // items whose tiles the index rules out all, or rows' own counters.
+  const int64_t nbc = stream ? R.n : (S.n == 0 || J.surv) ? R.n * (int64_t)P : 0;
   {
     StageTimer t(c, 1, st);
-    if (!rx) DL_HIP(c, launch_prep(R.data, R.n, R.d, R.ld, prec, L.pr, L.sr, st, c->cu_count));
-    if (!self && !sx) DL_HIP(c, launch_prep(S.data, S.n, S.d, S.ld, prec, L.ps, L.ss, st, c->cu_count));
-    hipLaunchKernelGGL(input_gate_kernel, dim3(1), dim3(64), 0, st, L.sr, L.ss, &L.cnt->invalid);
-    DL_HIP(c, launch_threshold(L.pr, R.n, L.ss, R.d, 0.0, nullptr, nullptr, L.marg, nullptr, L.gkey, st));
+    DL_HIP(c, launch_call_init(L.state, sizeof(CallState) / 4, reinterpret_cast<uint32_t*>(L.rstate), R.n,
+                               reinterpret_cast<uint32_t*>(L.wide), R.n, reinterpret_cast<uint32_t*>(L.bcount), nbc,
+                               st, c->cu_count));
+    DL_HIP(c, prep_relations(c, R, rx ? nullptr : &L.pr, nullptr, S, self || sx ? nullptr : &L.ps, nullptr, prec,
+                             L.state, st));
+    DL_HIP(c, launch_threshold(L.pr, R.n, L.ss, R.d, 0.0, nullptr, nullptr, L.marg, nullptr, L.gkey, st, L.sr,
+                               L.state));
     if (pilot_dist) DL_HIP(c, launch_band_seed(L.pr, R.n, pilot_dist, k, L.marg, L.gkey, st));
     if (J.seed) DL_HIP(c, launch_band_seed(L.pr, R.n, J.seed, 1, L.marg, L.gkey, st));
   }
   SelectParams q{};
   const bool small_sel = topk_select_small(k);
   Counters hc;
+  auto wait = [&]() -> dl_status {
+    DL_HIP(c, publish(c, L.state, (int)sizeof(CallState) / 8, st));
+    DL_HIP(c, hipEventSynchronize(c->ready));
+    hc = published(c).c;
+    return DL_OK;
+  };
+  // the counts again for another selection (the gate and the maxima stay)
+  auto restart = [&](bool rows) -> dl_status {
+    const int64_t n = (int64_t)(offsetof(Counters, invalid) / 4);
+    DL_HIP(c, launch_zero_ranges(reinterpret_cast<uint32_t*>(L.cnt), n, reinterpret_cast<uint32_t*>(L.state->sel),
+                                 (int64_t)(sizeof(L.state->sel) / 4), reinterpret_cast<uint32_t*>(L.wide), R.n,
+                                 reinterpret_cast<uint32_t*>(L.rstate), rows ? R.n : 0, st, c->cu_count));
+    return DL_OK;
+  };
   for (;;) {
     if (S.n > 0) {
       StageTimer t(c, 2, st);
@@ -828,14 +841,13 @@ dl_status topk_core(dl_ctx* c, const TopkJob& J, void* ws, size_t ws_bytes, uint
       q.xnR = L.pr.xnorm; q.mlR = L.pr.mlsb;
       q.sS = L.ss;
       q.out_j = out_j; q.out_dist = out_dist;
-      q.counts = L.sel; q.too_many = &L.cnt->too_many;
+      q.counts = L.state->sel; q.too_many = &L.cnt->too_many;
       q.gate = &L.cnt->invalid;
       q.rstate = L.rstate;
       q.wide = L.wide;
       DL_HIP(c, launch_topk_select(q, small_sel, prec == DL_FP8, st));
     }
-    DL_HIP(c, readback(c, L.cnt, L.sr, L.ss, st, L.sel));
-    hc = *reinterpret_cast<const Counters*>(c->pinned);
+    if (const dl_status s = wait()) return s;
     if (!(stream && hc.overflow)) break;
     // the tile form from the thresholds found (the gate stays as it is)
     stream = false;
@@ -844,25 +856,17 @@ dl_status topk_core(dl_ctx* c, const TopkJob& J, void* ws, size_t ws_bytes, uint
       if (const dl_status ps = run_pilot()) return ps;
       if (pilot_dist) DL_HIP(c, launch_band_seed(L.pr, R.n, pilot_dist, k, L.marg, L.gkey, st));
     }
-    hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t*>(L.cnt),
-                       (int64_t)(offsetof(Counters, invalid) / 4));
-    zero_counts();
-    hipLaunchKernelGGL(zero_words_kernel, dim3(64), dim3(256), 0, st, reinterpret_cast<uint32_t*>(L.rstate), R.n);
-    hipLaunchKernelGGL(zero_words_kernel, dim3(64), dim3(256), 0, st, reinterpret_cast<uint32_t*>(L.wide), R.n);
+    if (const dl_status s = restart(true)) return s;
   }
   if (small_sel && hc.too_many && !hc.overflow) {
     // a row had more near-tie contenders than the small selection holds:
     // select again (the bands are unchanged) with the large one
-    zero_counts();
-    hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t*>(&L.cnt->too_many),
-                       (int64_t)1);
-    hipLaunchKernelGGL(zero_words_kernel, dim3(64), dim3(256), 0, st, reinterpret_cast<uint32_t*>(L.wide), R.n);
+    if (const dl_status s = restart(false)) return s;
     {
       StageTimer t(c, 5, st);
       DL_HIP(c, launch_topk_select(q, false, prec == DL_FP8, st));
     }
-    DL_HIP(c, readback(c, L.cnt, L.sr, L.ss, st, L.sel));
-    hc = *reinterpret_cast<const Counters*>(c->pinned);
+    if (const dl_status s = wait()) return s;
   }
   if (hc.too_many && !hc.overflow) {
     // rows with more near-tie contenders than the selection holds: the wide
@@ -873,17 +877,16 @@ dl_status topk_core(dl_ctx* c, const TopkJob& J, void* ws, size_t ws_bytes, uint
       StageTimer t(c, 5, st);
       DL_HIP(c, launch_topk_select_wide(q, st));
     }
-    DL_HIP(c, readback(c, L.cnt, L.sr, L.ss, st, L.sel));
-    hc = *reinterpret_cast<const Counters*>(c->pinned);
+    if (const dl_status s = wait()) return s;
   }
   if (info) {
-    const SelectCount* n = reinterpret_cast<const SelectCount*>(c->pinned + kPinSelect);
+    const SelectCount* n = published(c).sel;
     for (int t = 0; t < kSelectCounts; ++t) {
       info->band_entries += (int64_t)n[t].band;
       info->ties += (int64_t)n[t].ties;
     }
   }
-  if (dl_status bad = check_inputs(c)) return bad;
+  if (dl_status bad = check_inputs(c, &published(c).r, &published(c).s)) return bad;
   if (hc.overflow || hc.too_many) {
     c->required_ws = topk_workspace(R.n, S.n, R.d, prec, self, sx, k, band_cap * 2, c->cu_count);
     return fail(c, DL_ERR_WORKSPACE, "top-k band exceeded its capacity (%s); retry with band_cap %d",
@@ -1026,7 +1029,7 @@ static dl_status bound_pass(dl_ctx* c, const float* cent, int64_t nb, const doub
   const int64_t nTD = (nD + kTile - 1) / kTile;
   hipLaunchKernelGGL(zero_words_kernel, dim3(256), dim3(256), 0, st, m, nTD * mw);
   DL_HIP(c, launch_prep(cent, nb, d, d, prec, pc, sc, st, c->cu_count));
-  DL_HIP(c, launch_threshold(pc, nb, sD, d, 0.0, Tb, thr, nullptr, nullptr, nullptr, st));
+  DL_HIP(c, launch_threshold(pc, nb, sD, d, 0.0, Tb, thr, nullptr, nullptr, nullptr, st, nullptr, nullptr));
   CandParams q{};
   q.qa = static_cast<const uint8_t*>(pc.q);
   q.qb = static_cast<const uint8_t*>(D.q);
@@ -1091,14 +1094,11 @@ dl_status eps_indexed_core(dl_ctx* c, const EpsJob& J, double eps, int32_t pivot
     if (s == DL_OK && !self) s = order_by_pivot(c, S, I, P, prec, L.ps, L.ss, I.permS, st);
     if (s != DL_OK) return s;
   }
-  hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t*>(L.cnt),
-                     (int64_t)(sizeof(Counters) / 4));
   {
     StageTimer t(c, 1, st);
-    DL_HIP(c, launch_prep(R.data, R.n, d, R.ld, prec, L.pr, L.sr, st, c->cu_count, I.permR));
-    if (!self) DL_HIP(c, launch_prep(S.data, S.n, d, S.ld, prec, L.ps, L.ss, st, c->cu_count, I.permS));
-    hipLaunchKernelGGL(input_gate_kernel, dim3(1), dim3(64), 0, st, L.sr, L.ss, &L.cnt->invalid);
-    DL_HIP(c, launch_threshold(L.pr, R.n, L.ss, d, J.T, nullptr, L.thr, nullptr, L.pex, nullptr, st));
+    DL_HIP(c, launch_call_init(L.state, 2 * kStateWords, L.rows, R.n + 1, nullptr, 0, nullptr, 0, st, c->cu_count));
+    DL_HIP(c, prep_relations(c, R, &L.pr, I.permR, S, self ? nullptr : &L.ps, I.permS, prec, L.state, st));
+    DL_HIP(c, launch_threshold(L.pr, R.n, L.ss, d, J.T, nullptr, L.thr, nullptr, L.pex, nullptr, st, L.sr, L.state));
   }
   // K-step masks: rows ordered by pivot make a tile's rows alike, and bins
   // (elements) that are zero in every row of a tile drop out of its K-steps
@@ -1129,7 +1129,7 @@ dl_status eps_indexed_core(dl_ctx* c, const EpsJob& J, double eps, int32_t pivot
     DL_HIP(c, launch_group_count(I.surv, I.sw, nTR, nTS, I.gm, I.cnt, st, c->cu_count));
     DL_HIP(c, launch_exclusive_scan(I.cnt, ncnt + 1, I.off, I.sums, st));
     DL_HIP(c, launch_group_list(I.surv, I.sw, nTR, nTS, I.gm, I.off, I.tiles, I.ntiles, st, c->cu_count));
-    DL_HIP(c, hipMemcpyAsync(c->pinned + 28, I.ntiles, 8, hipMemcpyDeviceToHost, st));  // read after the final sync
+    DL_HIP(c, hipMemcpyAsync(c->pinned + kPinTiles, I.ntiles, 8, hipMemcpyDeviceToHost, st));  // read after the final sync
   }
   // When most tiles survive, the full grid (its order needs no per-tile
   // list reads, which for a list of many millions of entries miss every
@@ -1163,14 +1163,14 @@ dl_status eps_indexed_core(dl_ctx* c, const EpsJob& J, double eps, int32_t pivot
     p.list_all = all_tiles;
     DL_HIP(c, launch_cand_list(prec, p, st, c->cu_count));
   }
-  c->pinned[29] = -1;
+  c->pinned[kPinSteps] = -1;
   if (kmask && info) {
     // the K-steps run, read back with the counters below
     hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t*>(I.ksteps),
                        (int64_t)2);
     DL_HIP(c, launch_kstep_count(I.tiles, I.ntiles, all_tiles, nTR, nTS, self ? 1 : 0, I.kmR, I.kmS, I.ksteps, st,
                                  c->cu_count));
-    DL_HIP(c, hipMemcpyAsync(c->pinned + 29, I.ksteps, 8, hipMemcpyDeviceToHost, st));
+    DL_HIP(c, hipMemcpyAsync(c->pinned + kPinSteps, I.ksteps, 8, hipMemcpyDeviceToHost, st));
   }
   const int bj = bits_for(S.n);
   {
@@ -1187,23 +1187,22 @@ dl_status eps_indexed_core(dl_ctx* c, const EpsJob& J, double eps, int32_t pivot
     q.xnS = L.ps.xnorm; q.mlS = L.ps.mlsb;
     q.T = J.T;
     q.bj = bj;
-    q.keys = L.k0; q.dist = L.v0; q.ocount = &L.cnt->out; q.nties = &L.cnt->ties;
+    q.keys = L.k0; q.dist = L.v0; q.ocount = &L.cnt->out; q.nties = &L.cnt->ties; q.rowcnt = L.rows;
     q.permR = I.permR;
     q.permS = I.permS;
     q.swap = self ? 1 : 0;
     DL_HIP(c, launch_recheck_eps(q, st, c->cu_count));
   }
-  DL_HIP(c, readback(c, L.cnt, L.sr, L.ss, st));
-  const Counters hc = *reinterpret_cast<const Counters*>(c->pinned);
+  const dl_status os = order_and_wait(c, L, cap, R.n, bj, out, st);
+  if (os != DL_OK && os != DL_ERR_INVALID) return os;
+  const Counters hc = published(c).c;
   if (info) {
-    const int64_t survivors = c->pinned[28];
+    const int64_t survivors = c->pinned[kPinTiles];
     info->tiles_computed = 2 * survivors < all_tiles ? survivors : all_tiles;
     info->ksteps_per_tile = nsteps;
-    info->ksteps_computed = c->pinned[29] >= 0 ? c->pinned[29] : info->tiles_computed * nsteps;
+    info->ksteps_computed = c->pinned[kPinSteps] >= 0 ? c->pinned[kPinSteps] : info->tiles_computed * nsteps;
   }
-  if (dl_status bad = check_inputs(c)) return bad;
-  out->candidates = (int64_t)hc.cand;
-  out->ties = (int64_t)hc.ties;
+  if (os != DL_OK) return os;
   if ((int64_t)hc.cand > cap && cap == kMaxPairs)
     return fail(c, DL_ERR_CAPACITY, "%llu candidates exceed the %lld one call can order; split R", hc.cand,
                 (long long)kMaxPairs);
@@ -1212,16 +1211,9 @@ dl_status eps_indexed_core(dl_ctx* c, const EpsJob& J, double eps, int32_t pivot
                                            pivots, c->cu_count);
     return fail(c, DL_ERR_WORKSPACE, "%llu candidates exceed the workspace capacity %lld", hc.cand, (long long)cap);
   }
-  const int64_t m = (int64_t)hc.out;
-  out->count = m;
-  {
-    StageTimer t(c, 4, st);
-    const int64_t w = m < out->capacity ? m : out->capacity;
-    DL_HIP(c, row_sort_pairs(L.k0, L.v0, m, R.n, bj, L.k1, L.v1, L.rows, w, out->i, out->j, out->dist, st,
-                             c->cu_count));
-  }
-  if (m > out->capacity)
-    return fail(c, DL_ERR_CAPACITY, "%lld pairs exceed the output capacity %lld", (long long)m,
+  out->count = (int64_t)hc.out;
+  if (out->count > out->capacity)
+    return fail(c, DL_ERR_CAPACITY, "%lld pairs exceed the output capacity %lld", (long long)out->count,
                 (long long)out->capacity);
   return DL_OK;
 }
@@ -1485,9 +1477,9 @@ dl_status eps_filtered_core(dl_ctx* c, const EpsJob& J, const int32_t* labR, con
     // pairs mapped back to the original rows (increasing maps keep the order)
     DL_HIP(c, launch_select_rows(labR, R.n, want, F.rowsR, F.scratch, F.counts, st));
     if (!self) DL_HIP(c, launch_select_rows(labS, S.n, want, F.rowsS, F.scratch, F.counts + 1, st));
-    DL_HIP(c, hipMemcpyAsync(c->pinned + 24, F.counts, 16, hipMemcpyDeviceToHost, st));
+    DL_HIP(c, hipMemcpyAsync(c->pinned + kPinRows, F.counts, 16, hipMemcpyDeviceToHost, st));
     DL_HIP(c, hipStreamSynchronize(st));
-    const int64_t mR = c->pinned[24], mS = self ? mR : c->pinned[25];
+    const int64_t mR = c->pinned[kPinRows], mS = self ? mR : c->pinned[kPinRows + 1];
     DL_HIP(c, launch_gather(R.data, R.ld, d, F.rowsR, mR, F.Rg, st, c->cu_count));
     if (!self) DL_HIP(c, launch_gather(S.data, S.ld, d, F.rowsS, mS, F.Sg, st, c->cu_count));
     EpsJob Jf = J;
@@ -1514,9 +1506,9 @@ dl_status eps_filtered_core(dl_ctx* c, const EpsJob& J, const int32_t* labR, con
   out->ties = all.ties;
   DL_HIP(c, launch_filter_pairs(F.ti, F.tj, F.td, all.count, labR, self ? labR : labS, want, out->i, out->j,
                                 out->dist, out->capacity, F.scratch, F.counts + 2, st));
-  DL_HIP(c, hipMemcpyAsync(c->pinned + 26, F.counts + 2, 8, hipMemcpyDeviceToHost, st));
+  DL_HIP(c, hipMemcpyAsync(c->pinned + kPinPairs, F.counts + 2, 8, hipMemcpyDeviceToHost, st));
   DL_HIP(c, hipStreamSynchronize(st));
-  const int64_t m = c->pinned[26];
+  const int64_t m = c->pinned[kPinPairs];
   out->count = m;
   if (m > out->capacity)
     return fail(c, DL_ERR_CAPACITY, "%lld pairs exceed the output capacity %lld", (long long)m,
@@ -1765,14 +1757,14 @@ dl_status dl_store_create(dl_ctx* c, dl_mat base, dl_prec prec, void* mem, size_
       return fail(c, DL_ERR_DEVICE, "prep: %s", hipGetErrorString(e));
     }
   }
-  hipError_t e = hipMemcpyAsync(c->pinned + 12, S->stats, sizeof(RelStats), hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipMemcpyAsync(c->pinned + 20, S->stats, sizeof(RelStats), hipMemcpyDeviceToHost, st);
+  hipError_t e = hipMemcpyAsync(c->pinned + kPinStats, S->stats, sizeof(RelStats), hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) {
     delete S;
     return fail(c, DL_ERR_DEVICE, "store readback: %s", hipGetErrorString(e));
   }
-  if (dl_status bad = check_inputs(c)) {
+  const RelStats* hs = reinterpret_cast<const RelStats*>(c->pinned + kPinStats);
+  if (dl_status bad = check_inputs(c, hs, hs)) {
     delete S;
     return bad;
   }
@@ -1811,7 +1803,7 @@ dl_status dl_store_featurize_rgb8(dl_ctx* c, const uint8_t* pixels, int64_t n, i
   S->base = dl_mat{out_hist, rows, d, d};
   S->prec = prec;
   S->device = c->device;
-  volatile int* bad = reinterpret_cast<volatile int*>(c->pinned + 30);
+  volatile int* bad = reinterpret_cast<volatile int*>(c->pinned + kPinBox);
   *bad = 0;
   hipError_t e;
   {
@@ -1822,8 +1814,8 @@ dl_status dl_store_featurize_rgb8(dl_ctx* c, const uint8_t* pixels, int64_t n, i
                          c->cu_count);
     if (e == hipSuccess) e = launch_stats_reduce(S->prep, rows, S->stats, st, c->cu_count);
   }
-  if (e == hipSuccess) e = hipMemcpyAsync(c->pinned + 12, S->stats, sizeof(RelStats), hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipMemcpyAsync(c->pinned + 20, S->stats, sizeof(RelStats), hipMemcpyDeviceToHost, st);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(c->pinned + kPinStats, S->stats, sizeof(RelStats), hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) {
     delete S;
@@ -1833,7 +1825,8 @@ dl_status dl_store_featurize_rgb8(dl_ctx* c, const uint8_t* pixels, int64_t n, i
     delete S;
     return fail(c, DL_ERR_INVALID, "a box lies outside its frame");
   }
-  if (dl_status badin = check_inputs(c)) {
+  const RelStats* hs = reinterpret_cast<const RelStats*>(c->pinned + kPinStats);
+  if (dl_status badin = check_inputs(c, hs, hs)) {
     delete S;
     return badin;
   }

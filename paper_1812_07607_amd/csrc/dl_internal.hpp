@@ -210,6 +210,7 @@ struct dl_ctx {
   std::string err;
   size_t required_ws = 0;
   int64_t* pinned = nullptr;  // small pinned host buffer for counts
+  hipEvent_t ready = nullptr;  // recorded behind their copy
   bool timing = false;
   // per stage: pending (start, stop) event pairs and accumulated results
   struct Rec { hipEvent_t a, b; int stage; };

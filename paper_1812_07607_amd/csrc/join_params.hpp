@@ -6,6 +6,51 @@
 
 namespace dl {
 
+// Device-side counters of one call (cleared by a kernel, so the sequence can
+// be captured in a graph).
+struct Counters {
+  unsigned long long cand;   // candidates appended
+  unsigned long long out;    // pairs confirmed
+  unsigned long long ties;   // float64 decisions
+  int bad_index;
+  int overflow;
+  int too_many;
+  int invalid;  // an input relation has a non-finite value or a row norm >= 2^62
+  int pad[6];
+};
+static_assert(sizeof(Counters) == 64, "counter block size");
+
+// Counts of the top-k selection, spread over cache lines of their own (summed
+// by the host).
+struct SelectCount {
+  unsigned long long band;  // entries in the exact band
+  unsigned long long ties;  // entries ordered in float64
+  unsigned long long pad[6];
+};
+constexpr int kSelectCounts = 32;
+
+// What a join call clears at its start and sends to the host at its end, in
+// one piece.
+struct CallState {
+  Counters c;
+  RelStats r, s;  // the relations' maxima
+  SelectCount sel[kSelectCounts];
+};
+constexpr int kStateWords = (sizeof(Counters) + 2 * sizeof(RelStats)) / 8;  // 64-bit words without the counts
+static_assert(sizeof(CallState) == 8 * kStateWords + sizeof(SelectCount) * kSelectCounts, "one piece");
+
+// One relation of a prep launch.
+struct PrepJob {
+  const float* X;
+  int64_t n, ld;
+  Prep P;
+  RelStats* rs;
+  const uint32_t* perm;  // nullable: operand row r holds row perm[r] of X
+};
+struct PrepPair {
+  PrepJob j[2];  // the second may be empty (P.npad 0)
+};
+
 // Candidate pass on the matrix cores (join_mfma.hip).
 struct CandParams {
   const uint8_t* qa;   // R operand rows (qld bytes each, npad rows)
@@ -105,21 +150,13 @@ struct RecheckParams {
   int bj;  // bits of j in the output key
   unsigned long long* keys; float* dist; unsigned long long* ocount;
   unsigned long long* nties;
+  uint32_t* rowcnt;  // pairs written per row of R (zero before)
   // index-pruned join: candidates are rows of the permuted operand copies;
   // permR / permS give each one's row in R / S (null: no permutation), and
   // swap orders a self-join's pair as (min, max)
   const uint32_t* permR; const uint32_t* permS;
   int swap;
 };
-
-// Counts of the selection, spread over cache lines of their own (summed by the
-// host).
-struct SelectCount {
-  unsigned long long band;  // entries in the exact band
-  unsigned long long ties;  // entries ordered in float64
-  unsigned long long pad[6];
-};
-constexpr int kSelectCounts = 32;
 
 // top-k exact selection (recheck.hip).
 struct SelectParams {

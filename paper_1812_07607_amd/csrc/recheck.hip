@@ -265,6 +265,14 @@ __global__ __launch_bounds__(256) void recheck_eps_kernel(RecheckParams p) {
         p.keys[at] = ((unsigned long long)mine[c].x << p.bj) | mine[c].y;
         p.dist[at] = dist[c];
       }
+      // the row counts of the ordering, one atomic per run of equal rows
+      if (mi[c]) {
+        const uint32_t prev = __shfl_up(mine[c].x, 1, 64);
+        const bool head = lane == 0 || prev != mine[c].x;
+        const uint64_t later = __ballot(head) & ~lt & ~(1ull << lane);
+        const uint64_t run = mi[c] & ~lt & (later ? (later & -later) - 1 : ~0ull);
+        if (head && run) atomicAdd(p.rowcnt + mine[c].x, (uint32_t)__popcll(run));
+      }
       pos += __popcll(mi[c]);
     }
     __syncthreads();

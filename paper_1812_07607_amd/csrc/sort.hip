@@ -4,7 +4,7 @@
 // by row with a count, an exclusive scan and an atomic placement, then each
 // row's segment is ordered by j.  Deterministic: the output depends only on
 // the set of pairs, not on the order the candidate kernel produced them in.
-#include "dl_internal.hpp"
+#include "join_params.hpp"
 
 namespace dl {
 
@@ -63,10 +63,20 @@ __global__ __launch_bounds__(1024) void scan_top_kernel(uint32_t* sums, int64_t 
   }
 }
 
-// each thread owns kScanItems consecutive entries of the chunk
+// Each thread owns kScanItems consecutive entries of the chunk.  scanned: sums
+// holds the chunks' offsets; otherwise their plain sums, and a workgroup adds
+// up the chunks before its own.
 __global__ __launch_bounds__(kScanThreads) void scan_apply_kernel(const uint32_t* in, int64_t n, const uint32_t* sums,
-                                                                  uint32_t* out) {
+                                                                  bool scanned, uint32_t* out) {
   __shared__ uint32_t lw[kScanThreads / 64];
+  uint32_t before = 0;
+  if (scanned) {
+    before = sums[blockIdx.x];
+  } else if (blockIdx.x > 0) {
+    uint32_t x = 0;
+    for (int t = threadIdx.x; t < (int)blockIdx.x; t += kScanThreads) x += sums[t];
+    block_exclusive_scan(x, lw, before);
+  }
   const int64_t base = (int64_t)blockIdx.x * kScanChunk + (int64_t)threadIdx.x * kScanItems;
   uint32_t v[kScanItems];
   uint32_t s = 0;
@@ -76,7 +86,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_apply_kernel(const uint32_t
     s += v[t];
   }
   uint32_t tot;
-  uint32_t run = block_exclusive_scan(s, lw, tot) + sums[blockIdx.x];
+  uint32_t run = block_exclusive_scan(s, lw, tot) + before;
 #pragma unroll
   for (int t = 0; t < kScanItems; ++t) {
     if (base + t < n) out[base + t] = run;
@@ -86,18 +96,23 @@ __global__ __launch_bounds__(kScanThreads) void scan_apply_kernel(const uint32_t
 
 int64_t scan_scratch_words(int64_t n) { return (n + kScanChunk - 1) / kScanChunk; }
 
+// One launch for a single chunk and two up to kScanFlat chunks, whose sums
+// every workgroup adds up for itself (a few loads a thread, where the third
+// launch costs about 5 us); three beyond, where that would grow quadratically.
+constexpr int64_t kScanFlat = 4096;
 hipError_t launch_exclusive_scan(const uint32_t* in, int64_t n, uint32_t* out, uint32_t* sums, hipStream_t st) {
   if (n == 0) return hipSuccess;
   const int64_t nb = (n + kScanChunk - 1) / kScanChunk;
-  hipLaunchKernelGGL(scan_reduce_kernel, dim3((unsigned)nb), dim3(kScanThreads), 0, st, in, n, sums);
-  hipLaunchKernelGGL(scan_top_kernel, dim3(1), dim3(1024), 0, st, sums, nb);
-  hipLaunchKernelGGL(scan_apply_kernel, dim3((unsigned)nb), dim3(kScanThreads), 0, st, in, n, sums, out);
+  if (nb > 1) hipLaunchKernelGGL(scan_reduce_kernel, dim3((unsigned)nb), dim3(kScanThreads), 0, st, in, n, sums);
+  if (nb > kScanFlat) hipLaunchKernelGGL(scan_top_kernel, dim3(1), dim3(1024), 0, st, sums, nb);
+  hipLaunchKernelGGL(scan_apply_kernel, dim3((unsigned)nb), dim3(kScanThreads), 0, st, in, n, sums, nb > kScanFlat,
+                     out);
   return hipGetLastError();
 }
 
 // --------------------------------------------------------------- rows
-// Canonical (i, j) order by rows: count the pairs of each row, scan the
-// counts into row offsets, place every pair in its row's segment (in any
+// Canonical (i, j) order by rows: the recheck has counted the pairs of each
+// row; scan the counts into row offsets, place every pair in its row's segment (in any
 // order), then order each segment by j, one wave per row.  A pair's output
 // slot is the number of the row's pairs with a smaller j (the (i, j) pairs
 // are distinct, so the result does not depend on the order of placement):
@@ -105,11 +120,10 @@ hipError_t launch_exclusive_scan(const uint32_t* in, int64_t n, uint32_t* out, u
 // their j values staged in LDS; longer rows set one bit per pair in an LDS
 // bitmap over a window of j, take a prefix count of the bitmap words, and
 // read each pair's rank from it, window by window (windows that hold no
-// pair are skipped), so the work is linear in the row length.  Six
-// launches where an 8-bit LSD radix sort of 34-bit keys takes 25.
-__global__ void fill_words_kernel(uint32_t* p, int64_t n, uint32_t v) {
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x)
-    p[t] = v;
+// pair are skipped), so the work is linear in the row length.  The number of
+// pairs is read on the device: the launches are queued before the host knows it.
+__device__ inline int64_t ordered_pairs(const Counters* c, int64_t cap) {
+  return (int64_t)c->cand > cap ? 0 : (int64_t)c->out;  // none if candidates were lost: the call fails
 }
 
 // The confirmed pairs arrive in runs of equal i (the candidate pass emits
@@ -137,21 +151,13 @@ __device__ inline RowRun row_run(const unsigned long long* keys, int64_t t, int6
   return r;
 }
 
-__global__ void count_rows_kernel(const unsigned long long* __restrict__ keys, int64_t m, int bj,
-                                  uint32_t* __restrict__ cnt) {
-  const int lane = threadIdx.x & 63;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t t0 = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63); t0 < m; t0 += stride) {
-    const RowRun r = row_run(keys, t0 + lane, m, bj);
-    if (r.valid && r.head == lane) atomicAdd(&cnt[r.i], (uint32_t)r.len);
-  }
-}
-
 // cnt holds each row's pair count on entry and zero on exit: each run takes
 // len of its row's slots by one atomic decrement.
 __global__ void place_rows_kernel(const unsigned long long* __restrict__ keys, const float* __restrict__ vals,
-                                  int64_t m, int bj, const uint32_t* __restrict__ off, uint32_t* __restrict__ cnt,
+                                  const Counters* __restrict__ c, int64_t cap, int bj,
+                                  const uint32_t* __restrict__ off, uint32_t* __restrict__ cnt,
                                   unsigned long long* __restrict__ pk, float* __restrict__ pv) {
+  const int64_t m = ordered_pairs(c, cap);
   const int lane = threadIdx.x & 63;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t t0 = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63); t0 < m; t0 += stride) {
@@ -181,15 +187,16 @@ __device__ inline void wave_lds_sync() {
 
 __global__ __launch_bounds__(64 * kRowWaves) void order_rows_kernel(const unsigned long long* __restrict__ pk,
                                                                    const float* __restrict__ pv, int64_t nR,
-                                                                   const uint32_t* __restrict__ off, int64_t m,
+                                                                   const uint32_t* __restrict__ off,
+                                                                   const Counters* __restrict__ c, int64_t cap,
                                                                    int bj, int64_t w, uint32_t* __restrict__ oi,
                                                                    uint32_t* __restrict__ oj, float* __restrict__ od) {
   __shared__ uint32_t bits_lds[kRowWaves][kWinWords];
   __shared__ uint32_t pre_lds[kRowWaves][kWinWords];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t i = (int64_t)blockIdx.x * kRowWaves + wave;
-  if (i >= nR) return;
-  const int64_t b = off[i], e = i + 1 < nR ? (int64_t)off[i + 1] : m;
+  if (i >= nR || ordered_pairs(c, cap) == 0) return;
+  const int64_t b = off[i], e = off[i + 1];
   const unsigned long long mask = (1ull << bj) - 1;
   auto emit = [&](int64_t at, int64_t t, uint32_t j) {
     if (at < w) {
@@ -294,25 +301,23 @@ __global__ __launch_bounds__(64 * kRowWaves) void order_rows_kernel(const unsign
 
 int64_t row_sort_words(int64_t nR) { return 2 * (nR + 1) + scan_scratch_words(nR + 1) + 1; }
 
-// keys/vals: the m confirmed pairs (key i << bj | j); pk/pv: m entries of
-// scratch; words: row_sort_words(nR) words of scratch.  Writes the first w
-// pairs in (i, j) order to oi/oj/od.
-hipError_t row_sort_pairs(const unsigned long long* keys, const float* vals, int64_t m, int64_t nR, int bj,
-                          unsigned long long* pk, float* pv, uint32_t* words, int64_t w, uint32_t* oi, uint32_t* oj,
-                          float* od, hipStream_t st, int cu_count) {
-  if (m == 0 || nR == 0) return hipSuccess;
+// Scratch layout: the row counts (nR + 1 words, the last 0), the row offsets
+// and the scan's sums.
+// keys/vals: the confirmed pairs (key i << bj | j) of a recheck that counted
+// them into words; c, cap: its counters and candidate capacity; pk/pv: cap
+// entries of scratch.  Writes the first w pairs in (i, j) order to oi/oj/od.
+hipError_t row_sort_pairs(const unsigned long long* keys, const float* vals, const Counters* c, int64_t cap, int64_t nR,
+                          int bj, unsigned long long* pk, float* pv, uint32_t* words, int64_t w, uint32_t* oi,
+                          uint32_t* oj, float* od, hipStream_t st, int cu_count) {
   uint32_t* cnt = words;
   uint32_t* off = words + (nR + 1);
   uint32_t* sums = words + 2 * (nR + 1);
-  const int64_t gw = (nR + 255) / 256 < (int64_t)cu_count * 4 ? (nR + 255) / 256 : (int64_t)cu_count * 4;
-  const int64_t gm = (m + 255) / 256 < (int64_t)cu_count * 8 ? (m + 255) / 256 : (int64_t)cu_count * 8;
-  hipLaunchKernelGGL(fill_words_kernel, dim3((unsigned)gw), dim3(256), 0, st, cnt, nR, 0u);
-  hipLaunchKernelGGL(count_rows_kernel, dim3((unsigned)gm), dim3(256), 0, st, keys, m, bj, cnt);
-  hipError_t e = launch_exclusive_scan(cnt, nR, off, sums, st);
+  const int64_t gm = (cap + 255) / 256 < (int64_t)cu_count * 8 ? (cap + 255) / 256 : (int64_t)cu_count * 8;
+  hipError_t e = launch_exclusive_scan(cnt, nR + 1, off, sums, st);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(place_rows_kernel, dim3((unsigned)gm), dim3(256), 0, st, keys, vals, m, bj, off, cnt, pk, pv);
+  hipLaunchKernelGGL(place_rows_kernel, dim3((unsigned)gm), dim3(256), 0, st, keys, vals, c, cap, bj, off, cnt, pk, pv);
   hipLaunchKernelGGL(order_rows_kernel, dim3((unsigned)((nR + kRowWaves - 1) / kRowWaves)), dim3(64 * kRowWaves), 0,
-                     st, pk, pv, nR, off, m, bj, w, oi, oj, od);
+                     st, pk, pv, nR, off, c, cap, bj, w, oi, oj, od);
   return hipGetLastError();
 }
 
