@@ -78,7 +78,7 @@ hipError_t launch_topk_select(const SelectParams&, bool, bool, hipStream_t);
 hipError_t launch_topk_select_wide(const SelectParams&, hipStream_t);
 bool topk_select_small(int);
 int64_t row_sort_words(int64_t);
-hipError_t row_sort_pairs(const unsigned long long*, const float*, const Counters*, int64_t, int64_t, int,
+hipError_t row_sort_pairs(unsigned long long*, const float*, const Counters*, int64_t, int64_t, int,
                           unsigned long long*, float*, uint32_t*, int64_t, uint32_t*, uint32_t*, float*, hipStream_t,
                           int);
 

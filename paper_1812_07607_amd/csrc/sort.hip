@@ -120,7 +120,8 @@ hipError_t launch_exclusive_scan(const uint32_t* in, int64_t n, uint32_t* out, u
 // their j values staged in LDS; longer rows set one bit per pair in an LDS
 // bitmap over a window of j, take a prefix count of the bitmap words, and
 // read each pair's rank from it, window by window (windows that hold no
-// pair are skipped), so the work is linear in the row length.  The number of
+// pair are skipped), unless its pairs are few for the range of j they span:
+// then buckets of j, ranked within a bucket.  The number of
 // pairs is read on the device: the launches are queued before the host knows it.
 __device__ inline int64_t ordered_pairs(const Counters* c, int64_t cap) {
   return (int64_t)c->cand > cap ? 0 : (int64_t)c->out;  // none if candidates were lost: the call fails
@@ -179,24 +180,22 @@ constexpr int kWinWords = 1024;             // bitmap words per wave
 constexpr int kWinBits = 32 * kWinWords;    // j values per window
 constexpr int kWordsPerLane = kWinWords / 64;
 constexpr int kQuadRow = 256;               // longest row ranked pair against pair
+constexpr int kOrderGroup = 8;              // lanes per short row, where rows are many
+constexpr int kOrderFill = 64;              // ... (this many per CU)
+constexpr uint32_t kFewWindows = 4;         // windows of j that cost no more than buckets
+constexpr uint32_t kBucketMost = 64;        // pairs of a bucket, ranked pair against pair
 
 __device__ inline void wave_lds_sync() {
   __builtin_amdgcn_s_waitcnt(0);
   __builtin_amdgcn_wave_barrier();
 }
 
-__global__ __launch_bounds__(64 * kRowWaves) void order_rows_kernel(const unsigned long long* __restrict__ pk,
-                                                                   const float* __restrict__ pv, int64_t nR,
-                                                                   const uint32_t* __restrict__ off,
-                                                                   const Counters* __restrict__ c, int64_t cap,
-                                                                   int bj, int64_t w, uint32_t* __restrict__ oi,
-                                                                   uint32_t* __restrict__ oj, float* __restrict__ od) {
-  __shared__ uint32_t bits_lds[kRowWaves][kWinWords];
-  __shared__ uint32_t pre_lds[kRowWaves][kWinWords];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t i = (int64_t)blockIdx.x * kRowWaves + wave;
-  if (i >= nR || ordered_pairs(c, cap) == 0) return;
-  const int64_t b = off[i], e = off[i + 1];
+// Orders one row's pairs [b, e) by a whole wave (bm, pre: kWinWords of LDS).
+__device__ inline void order_row(const unsigned long long* __restrict__ pk, const float* __restrict__ pv, int64_t i,
+                                 int64_t b, int64_t e, uint32_t* __restrict__ js, int bj, int64_t w,
+                                 uint32_t* __restrict__ oi, uint32_t* __restrict__ oj, float* __restrict__ od,
+                                 uint32_t* bm, uint32_t* pre) {
+  const int lane = threadIdx.x & 63;
   const unsigned long long mask = (1ull << bj) - 1;
   auto emit = [&](int64_t at, int64_t t, uint32_t j) {
     if (at < w) {
@@ -213,7 +212,6 @@ __global__ __launch_bounds__(64 * kRowWaves) void order_rows_kernel(const unsign
     if (t < e) emit(b + rank, t, j);
     return;
   }
-  uint32_t* bm = bits_lds[wave];
   if (e - b <= kQuadRow) {
     // rank against the row's j values staged in LDS (broadcast reads)
     for (int64_t t = b + lane; t < e; t += 64) bm[t - b] = (uint32_t)(pk[t] & mask);
@@ -236,7 +234,6 @@ __global__ __launch_bounds__(64 * kRowWaves) void order_rows_kernel(const unsign
       if (lane + 64 * q < len) emit(b + rk[q], b + lane + 64 * q, jq[q]);
     return;
   }
-  uint32_t* pre = pre_lds[wave];
   uint32_t jlo = 0xffffffffu, jhi = 0;
   for (int64_t t = b + lane; t < e; t += 64) {
     const uint32_t j = (uint32_t)(pk[t] & mask);
@@ -248,6 +245,61 @@ __global__ __launch_bounds__(64 * kRowWaves) void order_rows_kernel(const unsign
     const uint32_t a = __shfl_xor(jlo, o, 64), z = __shfl_xor(jhi, o, 64);
     jlo = a < jlo ? a : jlo;
     jhi = z > jhi ? z : jhi;
+  }
+  // Few pairs over a wide range of j: 1,024 buckets of equal width instead of
+  // windows (900 queries of a few hundred pairs each among 2M rows: a window
+  // holds 32,768 j, so a row walked 61 of them; the ordering 196 -> 30 us).
+  if (jhi - jlo >= kFewWindows * kWinBits) {
+    const int sh = 22 - __clz(jhi - jlo);  // (jhi - jlo) >> sh < kWinWords
+    const int len = (int)(e - b);
+#pragma unroll
+    for (int q = 0; q < kWordsPerLane; ++q) bm[lane + 64 * q] = 0;
+    wave_lds_sync();
+    for (int t = lane; t < len; t += 64) atomicAdd(&bm[((uint32_t)(pk[b + t] & mask) - jlo) >> sh], 1u);
+    wave_lds_sync();
+    uint32_t c[kWordsPerLane], run = 0, most = 0;
+#pragma unroll
+    for (int q = 0; q < kWordsPerLane; ++q) {
+      const uint32_t n = bm[lane * kWordsPerLane + q];
+      most = n > most ? n : most;
+      c[q] = run;
+      run += n;
+    }
+    uint32_t x = run;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t y = __shfl_up(x, o, 64);
+      if (lane >= o) x += y;
+    }
+    if (!__ballot(most > kBucketMost)) {
+#pragma unroll
+      for (int q = 0; q < kWordsPerLane; ++q) bm[lane * kWordsPerLane + q] = x - run + c[q];
+      wave_lds_sync();
+      // the j values bucket by bucket (in any order within one), in LDS or
+      // behind it in memory; bm ends up holding the buckets' ends
+      const bool fits = len <= kWinWords;
+      for (int t = lane; t < len; t += 64) {
+        const uint32_t j = (uint32_t)(pk[b + t] & mask);
+        const uint32_t at = atomicAdd(&bm[(j - jlo) >> sh], 1u);
+        if (fits) pre[at] = j;
+        else js[b + at] = j;
+      }
+      __threadfence_block();
+      wave_lds_sync();
+      for (int t = lane; t < len; t += 64) {
+        const uint32_t j = (uint32_t)(pk[b + t] & mask);
+        const uint32_t k = (j - jlo) >> sh;
+        const uint32_t u0 = k ? bm[k - 1] : 0u, u1 = bm[k];
+        uint32_t rank = u0;
+        if (fits)
+          for (uint32_t u = u0; u < u1; ++u) rank += pre[u] < j;
+        else
+          for (uint32_t u = u0; u < u1; ++u) rank += js[b + u] < j;
+        emit(b + rank, b + t, j);
+      }
+      return;
+    }
+    wave_lds_sync();
   }
   int64_t below = 0;  // pairs of the row in earlier windows
   uint64_t lo = jlo;
@@ -299,25 +351,76 @@ __global__ __launch_bounds__(64 * kRowWaves) void order_rows_kernel(const unsign
   }
 }
 
+// kGroup lanes per row of at most kGroup pairs, and the wave for the longer
+// ones, one after the other; few rows take a wave each.  Bound by the rows, not
+// their bytes, where they are short: 1M rows of about one pair took 443 us with
+// a wave each (the whole ordering), 305 / 159 / 101 with 32 / 16 / 8 lanes; 1M
+// of about 17 pairs 1321, 1016 / 981 / 982; 60,000 of 25 165, 151 / 149 / 154.
+template <int kGroup>
+__global__ __launch_bounds__(64 * kRowWaves) void order_rows_kernel(const unsigned long long* __restrict__ pk,
+                                                                   const float* __restrict__ pv, int64_t nR,
+                                                                   uint32_t* __restrict__ js,
+                                                                   const uint32_t* __restrict__ off,
+                                                                   const Counters* __restrict__ c, int64_t cap,
+                                                                   int bj, int64_t w, uint32_t* __restrict__ oi,
+                                                                   uint32_t* __restrict__ oj, float* __restrict__ od) {
+  __shared__ uint32_t bits_lds[kRowWaves][kWinWords];
+  __shared__ uint32_t pre_lds[kRowWaves][kWinWords];
+  if (ordered_pairs(c, cap) == 0) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t i0 = ((int64_t)blockIdx.x * kRowWaves + wave) * (64 / kGroup);
+  if (kGroup == 64) {
+    if (i0 < nR)
+      order_row(pk, pv, i0, off[i0], off[i0 + 1], js, bj, w, oi, oj, od, bits_lds[wave], pre_lds[wave]);
+    return;
+  }
+  const int64_t i = i0 + lane / kGroup;
+  const uint32_t b = i < nR ? off[i] : 0u, e = i < nR ? off[i + 1] : 0u;
+  const uint32_t t = b + (lane & (kGroup - 1));
+  const bool in = e - b <= kGroup && t < e;
+  const uint32_t j = in ? (uint32_t)(pk[t] & ((1ull << bj) - 1)) : 0xffffffffu;
+  uint32_t at = b;
+#pragma unroll
+  for (int u = 0; u < kGroup; ++u) at += __shfl(j, (lane & ~(kGroup - 1)) + u, 64) < j;
+  if (in && at < w) {
+    oi[at] = (uint32_t)i;
+    oj[at] = j;
+    od[at] = pv[t];
+  }
+  uint64_t longer = __ballot(e - b > kGroup && (lane & (kGroup - 1)) == 0);
+  while (longer) {
+    const int l = __ffsll((long long)longer) - 1;
+    longer &= longer - 1;
+    order_row(pk, pv, i0 + l / kGroup, __shfl(b, l, 64), __shfl(e, l, 64), js, bj, w, oi, oj, od, bits_lds[wave],
+              pre_lds[wave]);
+    wave_lds_sync();
+  }
+}
+
 int64_t row_sort_words(int64_t nR) { return 2 * (nR + 1) + scan_scratch_words(nR + 1) + 1; }
 
 // Scratch layout: the row counts (nR + 1 words, the last 0), the row offsets
 // and the scan's sums.
 // keys/vals: the confirmed pairs (key i << bj | j) of a recheck that counted
-// them into words; c, cap: its counters and candidate capacity; pk/pv: cap
+// them into words (overwritten); c, cap: its counters and candidate capacity; pk/pv: cap
 // entries of scratch.  Writes the first w pairs in (i, j) order to oi/oj/od.
-hipError_t row_sort_pairs(const unsigned long long* keys, const float* vals, const Counters* c, int64_t cap, int64_t nR,
+hipError_t row_sort_pairs(unsigned long long* keys, const float* vals, const Counters* c, int64_t cap, int64_t nR,
                           int bj, unsigned long long* pk, float* pv, uint32_t* words, int64_t w, uint32_t* oi,
                           uint32_t* oj, float* od, hipStream_t st, int cu_count) {
   uint32_t* cnt = words;
   uint32_t* off = words + (nR + 1);
   uint32_t* sums = words + 2 * (nR + 1);
+  uint32_t* js = reinterpret_cast<uint32_t*>(keys);  // free once the pairs are placed
   const int64_t gm = (cap + 255) / 256 < (int64_t)cu_count * 8 ? (cap + 255) / 256 : (int64_t)cu_count * 8;
   hipError_t e = launch_exclusive_scan(cnt, nR + 1, off, sums, st);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(place_rows_kernel, dim3((unsigned)gm), dim3(256), 0, st, keys, vals, c, cap, bj, off, cnt, pk, pv);
-  hipLaunchKernelGGL(order_rows_kernel, dim3((unsigned)((nR + kRowWaves - 1) / kRowWaves)), dim3(64 * kRowWaves), 0,
-                     st, pk, pv, nR, off, c, cap, bj, w, oi, oj, od);
+  auto order = [&](auto kernel, int rows) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((nR + rows - 1) / rows)), dim3(64 * kRowWaves), 0, st, pk, pv, nR, js,
+                       off, c, cap, bj, w, oi, oj, od);
+  };
+  if (nR >= (int64_t)cu_count * kOrderFill) order(order_rows_kernel<kOrderGroup>, kRowWaves * (64 / kOrderGroup));
+  else order(order_rows_kernel<64>, kRowWaves);
   return hipGetLastError();
 }
 

@@ -43,3 +43,33 @@ def test_calls_without_pairs_between_others():
             out = ops.join_eps(R, None, float("inf"), prec)
             iu = np.triu_indices(300, 1)
             assert np.array_equal(out.i.cpu().numpy(), iu[0]) and np.array_equal(out.j.cpu().numpy(), iu[1])
+
+
+@pytest.mark.parametrize("n", [40, 17000])
+def test_row_lengths(n):
+    """Rows of every ordering path at its edges: a few lanes, a wave, LDS
+    ranks, buckets (in LDS and in memory), windows, and pairs bunched so that
+    a bucket would hold too many; rows few (a wave each) and many."""
+    from paper_1812_07607_amd import ops
+    lens = [0, 1, 7, 8, 9, 63, 64, 65, 255, 256, 257, 1000, 1024, 1025, 9000, 700, 40000]
+    ns = 300000
+    rng = np.random.default_rng(n)
+    cls = np.full(ns, 999, np.int64)
+    cls[5000:5000 + lens[15] - 2] = 15  # bunched, with two far away
+    free = rng.permutation(np.flatnonzero(cls == 999))
+    cls[free[:2]] = 15
+    free = free[2:]
+    for c, m in enumerate(lens):
+        if c != 15:
+            cls[free[:m]] = c
+            free = free[m:]
+    own = np.full(n, 500, np.int64)  # no partner
+    own[rng.permutation(n)[:2 * len(lens)]] = np.tile(np.arange(len(lens)), 2)
+    R = torch.tensor(own, device="cuda").to(torch.float32).reshape(-1, 1)
+    S = torch.tensor(cls, device="cuda").to(torch.float32).reshape(-1, 1)
+    out = ops.join_eps(R, S, 0.25, "bf16")
+    members = [np.flatnonzero(cls == c) for c in range(len(lens))]
+    want_i = np.concatenate([np.full(len(members[c]), i) for i, c in enumerate(own) if c < len(lens)])
+    want_j = np.concatenate([members[c] for c in own if c < len(lens)])
+    assert np.array_equal(out.i.cpu().numpy(), want_i) and np.array_equal(out.j.cpu().numpy(), want_j)
+    assert not out.dist.any()
