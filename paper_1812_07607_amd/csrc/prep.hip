@@ -68,21 +68,71 @@ hipError_t launch_zero_ranges(uint32_t* p0, int64_t n0, uint32_t* p1, int64_t n1
   return call_init(nullptr, 0, ZeroRanges{{p0, p1, p2, p3}, {n0, n1, n2, n3}}, stream, cu_count);
 }
 
-// One wave per row; rows in [n, npad) get zero operands and zero statistics.
-// Both relations of a join in one launch (npad is a multiple of the four rows
-// of a workgroup).
+// kLanes lanes per row; rows in [n, npad) get zero operands and zero
+// statistics.  Both relations of a join in one launch (npad is a multiple of
+// the rows of a workgroup).
+template <int kLanes>
+__device__ inline int64_t prep_row_of(const PrepPair& pair, int& which) {
+  constexpr int kRows = 256 / kLanes;  // of a workgroup
+  const int64_t first = pair.j[0].P.npad / kRows;
+  which = blockIdx.x >= first;
+  return ((int64_t)blockIdx.x - (which ? first : 0)) * kRows + threadIdx.x / kLanes;
+}
+
+template <int kPrec, int kLanes>
+__global__ __launch_bounds__(256) void prep_short_kernel(PrepPair pair, int32_t d, int64_t dpad) {
+  static_assert(kTile % (256 / kLanes) == 0, "whole workgroups per relation");
+  const int sub = threadIdx.x & (kLanes - 1);
+  int which;
+  const int64_t row = prep_row_of<kLanes>(pair, which);
+  const PrepJob& J = pair.j[which];
+  const Prep P = J.P;
+  if (row >= P.npad) return;
+  const bool real = row < J.n;
+  const float* const x = J.X + (real ? (J.perm ? (int64_t)J.perm[row] : row) * J.ld : 0);
+  const int dr = real ? d : 0;
+  const bool vec = (J.ld & 3) == 0 && (reinterpret_cast<uintptr_t>(J.X) & 15) == 0;
+  auto load = [&](int k, float (&v)[4]) {
+    if (vec && k + 4 <= dr) {
+      const float4 t = *reinterpret_cast<const float4*>(x + k);
+      v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = k + u < dr ? x[k + u] : 0.0f;
+    }
+  };
+  int sexp = 0;
+  if (kPrec == DL_FP8 && real) {
+    float amax = 0.0f;
+    for (int k = 4 * sub; k < d; k += 4 * kLanes) {
+      float v[4];
+      load(k, v);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) amax = fmaxf(amax, fabsf(v[u]));
+    }
+    sexp = e4m3_row_scale(wave_max<kLanes>(amax));
+  }
+  RowPrep<kPrec> rp(P, row, sexp);
+#pragma unroll 2
+  for (int k = 4 * sub; k < dpad; k += 4 * kLanes) {
+    float v[4];
+    load(k, v);
+    rp.four(v, k);
+  }
+  rp.template finish<kLanes>(P, row, dpad, real, J.rs, sub);
+}
+
 template <int kPrec>
 __global__ __launch_bounds__(256) void prep_kernel(PrepPair pair, int32_t d, int64_t dpad) {
   const int lane = threadIdx.x & 63;
-  const int64_t first = pair.j[0].P.npad / 4;
-  const int which = blockIdx.x >= first;
+  int which;
+  const int64_t row = prep_row_of<64>(pair, which);
   const PrepJob& J = pair.j[which];
   const float* const X = J.X;
   const int64_t n = J.n, ld = J.ld;
   const Prep P = J.P;
   RelStats* const rs = J.rs;
   const uint32_t* const perm = J.perm;
-  const int64_t row = ((int64_t)blockIdx.x - (which ? first : 0)) * 4 + (threadIdx.x >> 6);
   if (row >= P.npad) return;
   const bool real = row < n;
   const float* x = X + (real ? (perm ? (int64_t)perm[row] : row) * ld : 0);
@@ -302,14 +352,37 @@ static int reduce_blocks(int64_t n, int cu_count) {
   return (int)(blocks > (int64_t)cu_count ? (int64_t)cu_count : blocks);
 }
 
+// Lanes per row.  A wave per row spends its time in the reductions (sixty
+// cross-lane moves and one lane's statistics a row), not in the row's bytes:
+// 1M rows of 128 in bf16 take 721 us with 64 lanes, 422 / 306 / 249 with 32 /
+// 16 / 8 (floor 160: 0.8 GB); 300,000 of 500 345, 276 / 247 / 231; 100,000 of
+// 1024 177, 167 / 159 / 166.  Long rows, and rows too few to fill the CUs, want
+// the lanes (2,000 of 1024: 30 us with 64, 37 / 51 with 16 / 8; of 512: 24, 26
+// / 34).
+static int prep_lanes(int64_t dpad, int64_t rows, int cu_count) {
+  if (dpad > 512) return 64;
+  return dpad <= 256 && rows >= (int64_t)cu_count * 128 ? 8 : 16;
+}
+
+template <int kPrec>
+static void go_prep(const PrepPair& pair, int32_t d, int64_t dpad, int lanes, dim3 grid, hipStream_t st) {
+  const dim3 block(256);
+  if (lanes == 8) hipLaunchKernelGGL((prep_short_kernel<kPrec, 8>), grid, block, 0, st, pair, d, dpad);
+  else if (lanes == 16) hipLaunchKernelGGL((prep_short_kernel<kPrec, 16>), grid, block, 0, st, pair, d, dpad);
+  else hipLaunchKernelGGL(prep_kernel<kPrec>, grid, block, 0, st, pair, d, dpad);
+}
+
 // Operand copies, statistics and maxima (cleared before) of one or two
 // relations: two launches.  A small join is bound by its launches (4 to 5 us
 // each on an idle device): with the init, the prep, the gate, the ordering and
 // the read-back fused into ten launches and no copy commands, where there were
 // nineteen and three, 2,000 x 2,000 rows of 64 take 74 us instead of 134.
 hipError_t launch_prep_pair(const PrepPair& pair, int32_t d, dl_prec prec, hipStream_t st, int cu_count) {
+  const int64_t dpad = dpad_of(d, prec);
   const int64_t rows = pair.j[0].P.npad + pair.j[1].P.npad;
-  if (pair.j[1].P.npad && rows * 64 >= (1ll << 32)) {  // past one launch's threads: one relation at a time
+  const int lanes = prep_lanes(dpad, rows, cu_count);
+  const int64_t blocks = rows / (256 / lanes);
+  if (pair.j[1].P.npad && blocks * 256 >= (1ll << 32)) {  // past one launch's threads: one relation at a time
     PrepPair one{};
     for (int q = 0; q < 2; ++q) {
       one.j[0] = pair.j[q];
@@ -318,13 +391,12 @@ hipError_t launch_prep_pair(const PrepPair& pair, int32_t d, dl_prec prec, hipSt
     }
     return hipSuccess;
   }
-  const int64_t dpad = dpad_of(d, prec);
-  const dim3 grid((unsigned)(rows / 4)), block(256);
+  const dim3 grid((unsigned)blocks);
   switch (prec) {
-    case DL_FP32: hipLaunchKernelGGL(prep_kernel<DL_FP32>, grid, block, 0, st, pair, d, dpad); break;
-    case DL_BF16: hipLaunchKernelGGL(prep_kernel<DL_BF16>, grid, block, 0, st, pair, d, dpad); break;
-    case DL_FP16: hipLaunchKernelGGL(prep_kernel<DL_FP16>, grid, block, 0, st, pair, d, dpad); break;
-    case DL_FP8: hipLaunchKernelGGL(prep_kernel<DL_FP8>, grid, block, 0, st, pair, d, dpad); break;
+    case DL_FP32: go_prep<DL_FP32>(pair, d, dpad, lanes, grid, st); break;
+    case DL_BF16: go_prep<DL_BF16>(pair, d, dpad, lanes, grid, st); break;
+    case DL_FP16: go_prep<DL_FP16>(pair, d, dpad, lanes, grid, st); break;
+    case DL_FP8: go_prep<DL_FP8>(pair, d, dpad, lanes, grid, st); break;
   }
   const int b0 = reduce_blocks(pair.j[0].n, cu_count), b1 = pair.j[1].P.npad ? reduce_blocks(pair.j[1].n, cu_count) : 0;
   if (b0 + b1 > 0) hipLaunchKernelGGL(stats_reduce_kernel, dim3(b0 + b1), dim3(256), 0, st, pair, b0);

@@ -7,19 +7,23 @@
 
 namespace dl {
 
-__device__ inline double wave_sum(double v) {
+// Reductions over aligned groups of kLanes lanes (the wave by default).
+template <int kLanes = 64, class T>
+__device__ inline T wave_sum(T v) {
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  for (int o = kLanes / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
 }
+template <int kLanes = 64>
 __device__ inline float wave_max(float v) {
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+  for (int o = kLanes / 2; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
   return v;
 }
+template <int kLanes = 64>
 __device__ inline int wave_min(int v) {
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
+  for (int o = kLanes / 2; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
   return v;
 }
 
@@ -58,37 +62,55 @@ struct RowPrep {
     mlsb = min(mlsb, lsb_exp(v));
   }
 
-  __device__ void element(float v, int64_t k) {
+  // the operand code of v (its bits in a register); counts it
+  __device__ uint32_t code(float v) {
     if (!isfinite(v)) { bad++; v = 0.0f; }
     float qv;
+    uint32_t c;
     if (kPrec == DL_FP32) {
       qv = v;
-      reinterpret_cast<float*>(qrow)[k] = v;
+      c = __float_as_uint(v);
     } else if (kPrec == DL_BF16) {
-      uint16_t c = enc_bf16(v);
-      qv = dec_bf16(c);
-      reinterpret_cast<uint16_t*>(qrow)[k] = c;
+      c = enc_bf16(v);
+      qv = dec_bf16((uint16_t)c);
     } else if (kPrec == DL_FP16) {
-      uint16_t c = enc_f16(v);
-      qv = dec_f16(c);
-      reinterpret_cast<uint16_t*>(qrow)[k] = c;
+      c = enc_f16(v);
+      qv = dec_f16((uint16_t)c);
     } else {
-      uint8_t c = enc_e4m3(v * inv_scale);
-      qv = dec_e4m3(c) * scale;  // exact: power-of-two scale of a normal value
-      qrow[k] = c;
+      c = enc_e4m3(v * inv_scale);
+      qv = dec_e4m3((uint8_t)c) * scale;  // exact: power-of-two scale of a normal value
     }
     stats(v, qv);
+    return c;
   }
 
-  // Wave reductions and the row's statistics (lane 0 stores); bad elements
-  // of a real row are counted into rs.
+  __device__ void element(float v, int64_t k) {
+    const uint32_t c = code(v);
+    if (kPrec == DL_FP32) reinterpret_cast<uint32_t*>(qrow)[k] = c;
+    else if (kPrec == DL_FP8) qrow[k] = (uint8_t)c;
+    else reinterpret_cast<uint16_t*>(qrow)[k] = (uint16_t)c;
+  }
+
+  // four elements from k on, k a multiple of four
+  __device__ void four(const float (&v)[4], int64_t k) {
+    uint32_t c[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) c[u] = code(v[u]);
+    if (kPrec == DL_FP32) reinterpret_cast<uint4*>(qrow)[k / 4] = make_uint4(c[0], c[1], c[2], c[3]);
+    else if (kPrec == DL_FP8) reinterpret_cast<uint32_t*>(qrow)[k / 4] = c[0] | c[1] << 8 | c[2] << 16 | c[3] << 24;
+    else reinterpret_cast<uint2*>(qrow)[k / 4] = make_uint2(c[0] | c[1] << 16, c[2] | c[3] << 16);
+  }
+
+  // Reductions over the row's kLanes lanes and the row's statistics (their
+  // lane 0 stores); bad elements of a real row are counted into rs.
+  template <int kLanes = 64>
   __device__ void finish(const Prep& P, int64_t row, int64_t dpad, bool real, RelStats* rs, int lane) {
-    nrm2 = wave_sum(nrm2);
-    qn2 = wave_sum(qn2);
-    r2 = wave_sum(r2);
-    qlsb = wave_min(qlsb);
-    mlsb = wave_min(mlsb);
-    bad = (int)wave_sum((double)bad);
+    nrm2 = wave_sum<kLanes>(nrm2);
+    qn2 = wave_sum<kLanes>(qn2);
+    r2 = wave_sum<kLanes>(r2);
+    qlsb = wave_min<kLanes>(qlsb);
+    mlsb = wave_min<kLanes>(mlsb);
+    bad = wave_sum<kLanes>(bad);
     if (lane == 0) {
       // float64 sums of at most dpad exact squares: relative error <= gamma_dpad
       const double g = gamma_n((double)dpad + 2.0, 0x1p-53);
