@@ -4,12 +4,13 @@
 // image matching); the patches are crops of frames given by bounding boxes
 // (section "Iterator API for Patches": a patch refers to a region of an
 // image), either already cut out (n patches of h x w pixels) or as boxes over
-// full frames.  One wavefront builds the histogram of one patch in a
-// wave-private LDS array, so no histogram crosses waves: the waves of a
-// workgroup never wait for one another (wave-level LDS ordering only), and
-// the only global traffic is one read of the pixels and one coalesced write
-// of the normalised bins.  HBM-bound: algorithmic bytes per patch are
-// h*w*3 read plus bins^3*4 written.
+// full frames.  One wavefront builds the histogram of one aligned patch in a
+// wave-private LDS array, so the waves of a workgroup never wait for one
+// another (wave-level LDS ordering only); a box over a frame, or a patch no
+// 16-byte load fits, takes a workgroup of two or four waves.  The only global
+// traffic is one read of the pixels and one coalesced write of the normalised
+// bins.  HBM-bound: algorithmic bytes per patch are h*w*3 read plus bins^3*4
+// written.
 //
 // The fused kernel (materialise into a store, section "Visual ETL") hands
 // each bin straight from LDS to the operand prep of the join (operand copy
@@ -56,6 +57,83 @@ __device__ inline void count16(uint32_t* __restrict__ hist, const uint32_t w[12]
   atomicAdd(&hist[prev], run);
 }
 
+// Counts of `rows` runs of cw pixels, pitch bytes apart, into the bins, by
+// kThreads threads (t of them).  A thread takes four neighbouring pixels at a
+// time, 12 bytes in one (unaligned) load; a run's last four overlap the ones
+// before, whose pixels it leaves out, so no byte beside the run is read.
+// kUnits such groups are in flight per thread.
+constexpr int kUnits = 4;
+struct __attribute__((packed)) Bytes12 {
+  uint32_t w[3];
+};
+template <int kThreads>
+__device__ inline void count_runs(uint32_t* __restrict__ hist, const uint8_t* __restrict__ base, int64_t pitch, int cw,
+                                  int rows, int shift, int bins, int t) {
+  const int width = 8 - shift;
+  auto field = [&](uint32_t w, int off) { return __builtin_amdgcn_ubfe(w, off + shift, width); };
+  auto bin_of = [&](uint32_t r, uint32_t g, uint32_t b) { return __umul24(__umul24(r, bins) + g, bins) + b; };
+  const int per = cw < 4 ? cw : (cw + 3) / 4;  // pixels (narrow runs) or groups of a run
+  const int units = per * rows;
+  // run of a unit by a float reciprocal, then one correction step each way
+  // (units < 2^24, so the estimate is off by at most one)
+  const float rper = 1.0f / (float)per;
+  auto run_of = [&](int q, int& x) {
+    int y = (int)((float)q * rper);
+    x = q - y * per;
+    if (x < 0) {
+      --y;
+      x += per;
+    } else if (x >= per) {
+      ++y;
+      x -= per;
+    }
+    return base + y * pitch;
+  };
+  if (cw < 4) {
+    for (int q = t; q < units; q += kThreads) {
+      int x;
+      const uint8_t* px = run_of(q, x) + 3 * x;
+      atomicAdd(&hist[bin_of(px[0] >> shift, px[1] >> shift, px[2] >> shift)], 1u);
+    }
+    return;
+  }
+  for (int q0 = 0; q0 < units; q0 += kThreads * kUnits) {
+    Bytes12 v[kUnits];
+    int skip[kUnits];
+#pragma unroll
+    for (int u = 0; u < kUnits; ++u) {
+      if (q0 + kThreads * u >= units) break;
+      const int q = q0 + kThreads * u + t;
+      skip[u] = 4;
+      if (q < units) {
+        int x;
+        const uint8_t* run = run_of(q, x);
+        const int at = min(4 * x, cw - 4);
+        skip[u] = 4 * x - at;
+        v[u] = *reinterpret_cast<const Bytes12*>(run + 3 * at);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kUnits; ++u) {
+      if (q0 + kThreads * u >= units) break;
+      const uint32_t w0 = v[u].w[0], w1 = v[u].w[1], w2 = v[u].w[2];
+      const uint32_t b[4] = {bin_of(field(w0, 0), field(w0, 8), field(w0, 16)),
+                             bin_of(field(w0, 24), field(w1, 0), field(w1, 8)),
+                             bin_of(field(w1, 16), field(w1, 24), field(w2, 0)),
+                             bin_of(field(w2, 8), field(w2, 16), field(w2, 24))};
+      // equal neighbours add up to one count
+      uint32_t run = 0;
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        run += p >= skip[u];
+        if (p < 3 && b[p] == b[p + 1]) continue;
+        if (run) atomicAdd(&hist[b[p]], run);
+        run = 0;
+      }
+    }
+  }
+}
+
 // Pixel sources.  kSrcPatch48: contiguous patches whose pixel count is a
 // multiple of 16, 16-byte aligned (three 16-byte loads per 16 pixels);
 // kSrcPatch: any contiguous patches; kSrcCrop: boxes over frames.
@@ -69,9 +147,10 @@ struct PixelSource {
   int* bad_box;            // crops: set when a box is not inside its frame
 };
 
-// Counts the pixels of patch p into the wave's bins; returns the pixel
-// count (0 for an invalid box, which contributes nothing).
-template <int kSrc>
+// Counts the pixels of patch p into the bins by kThreads threads (`lane` of
+// them); returns the pixel count (0 for an invalid box, which contributes
+// nothing).
+template <int kSrc, int kThreads = 64>
 __device__ inline int count_patch(const PixelSource& src, int64_t p, uint32_t* __restrict__ hist, int shift,
                                   int bins, int lane) {
   if constexpr (kSrc == kSrcCrop) {
@@ -84,56 +163,7 @@ __device__ inline int count_patch(const PixelSource& src, int64_t p, uint32_t* _
     }
     const int cw = bx.x1 - bx.x0, area = cw * (bx.y1 - bx.y0);
     const uint8_t* base = src.pix + (((int64_t)bx.frame * src.h + bx.y0) * src.w + bx.x0) * 3;
-    // row of pixel q by a float reciprocal, then one correction step each
-    // way (q < 2^24, so the estimate is off by at most one)
-    const float rcw = 1.0f / (float)cw;
-    auto at = [&](int q) {
-      int y = (int)((float)q * rcw);
-      int x = q - y * cw;
-      if (x < 0) {
-        --y;
-        x += cw;
-      } else if (x >= cw) {
-        ++y;
-        x -= cw;
-      }
-      return base + ((int64_t)y * src.w + x) * 3;
-    };
-    auto bin_of = [&](uint32_t r, uint32_t g, uint32_t b) {
-      return (((r >> shift) * bins) + (g >> shift)) * bins + (b >> shift);
-    };
-    // eight (then four) pixels' loads in flight per lane, then their counts (a box's
-    // rows are short strided runs, so the loads' latency, not their bytes,
-    // bounds a wave)
-    int q = lane;
-    for (; q + 7 * 64 < area; q += 8 * 64) {
-      uint32_t c[8][3];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const uint8_t* px = at(q + 64 * u);
-        c[u][0] = px[0];
-        c[u][1] = px[1];
-        c[u][2] = px[2];
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) atomicAdd(&hist[bin_of(c[u][0], c[u][1], c[u][2])], 1u);
-    }
-    for (; q + 3 * 64 < area; q += 4 * 64) {
-      uint32_t c[4][3];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const uint8_t* px = at(q + 64 * u);
-        c[u][0] = px[0];
-        c[u][1] = px[1];
-        c[u][2] = px[2];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) atomicAdd(&hist[bin_of(c[u][0], c[u][1], c[u][2])], 1u);
-    }
-    for (; q < area; q += 64) {
-      const uint8_t* px = at(q);
-      atomicAdd(&hist[bin_of(px[0], px[1], px[2])], 1u);
-    }
+    count_runs<kThreads>(hist, base, (int64_t)src.w * 3, cw, bx.y1 - bx.y0, shift, bins, lane);
     return area;
   } else {
     const int npx = src.h * src.w;
@@ -150,19 +180,21 @@ __device__ inline int count_patch(const PixelSource& src, int64_t p, uint32_t* _
         count16(hist, w, shift, bins);
       }
     } else {
-      for (int q = lane; q < npx; q += 64) {
-        const uint32_t r = s[3 * q], g = s[3 * q + 1], b = s[3 * q + 2];
-        const uint32_t bin = (((r >> shift) * bins) + (g >> shift)) * bins + (b >> shift);
-        atomicAdd(&hist[bin], 1u);
-      }
+      count_runs<kThreads>(hist, s, 0, npx, 1, shift, bins, lane);
     }
     return npx;
   }
 }
 
-// Histograms only: bin / pixel count, rounded once (IEEE division).
-template <int kSrc>
-__global__ __launch_bounds__(64 * kHistWaves) void hist_rgb8_kernel(PixelSource src, int64_t n, int32_t bins,
+static int bin_shift(int bins) {
+  int shift = 0;
+  while ((256 >> shift) > bins) ++shift;
+  return shift;
+}
+
+// Histograms only: bin / pixel count, rounded once (IEEE division).  Aligned
+// patches: a wave each.
+__global__ __launch_bounds__(64 * kHistWaves) void hist_patch48_kernel(PixelSource src, int64_t n, int32_t bins,
                                                                     int32_t shift, float* __restrict__ out) {
   extern __shared__ uint32_t lds_hist[];
   const int nb = bins * bins * bins;
@@ -174,13 +206,49 @@ __global__ __launch_bounds__(64 * kHistWaves) void hist_rgb8_kernel(PixelSource 
     if (p >= n) break;
     for (int b = lane; b < nb; b += 64) hist[b] = 0u;
     wave_lds_fence();
-    const int npx = count_patch<kSrc>(src, p, hist, shift, bins, lane);
+    const int npx = count_patch<kSrcPatch48>(src, p, hist, shift, bins, lane);
     wave_lds_fence();
     const float fnpx = (float)(npx > 0 ? npx : 1);  // exact: npx < 2^24
     float* dst = out + p * (int64_t)nb;
     for (int b = lane; b < nb; b += 64) dst[b] = (float)hist[b] / fnpx;  // IEEE division
     wave_lds_fence();  // the bins are read before the next patch clears them
   }
+}
+
+// Boxes and other patches: a workgroup each.  A box's size varies, and a wave
+// alone is bound by its loads' latency round after round (200 boxes of up to
+// 200 x 200: 38 us with a wave each, 20 / 12 with two / four); many boxes are
+// bound by how many a CU holds at once, times the same latency (40,000 of up to
+// 64 x 64: 43, 41 / 57).  So four waves while every box is resident at once, two
+// beyond.  20,000 boxes of up to 96 x 96: 47 -> 34 us.
+constexpr int64_t kRunBlocks = 1 << 20;
+template <int kSrc, int kThreads>
+__global__ __launch_bounds__(kThreads) void hist_runs_kernel(PixelSource src, int64_t n, int32_t bins, int32_t shift,
+                                                             float* __restrict__ out) {
+  extern __shared__ uint32_t lds_hist[];
+  const int nb = bins * bins * bins;
+  for (int64_t p = blockIdx.x; p < n; p += gridDim.x) {
+    for (int b = threadIdx.x; b < nb; b += kThreads) lds_hist[b] = 0u;
+    __syncthreads();
+    const int npx = count_patch<kSrc, kThreads>(src, p, lds_hist, shift, bins, threadIdx.x);
+    __syncthreads();
+    const float fnpx = (float)(npx > 0 ? npx : 1);
+    float* dst = out + p * (int64_t)nb;
+    for (int b = threadIdx.x; b < nb; b += kThreads) dst[b] = (float)lds_hist[b] / fnpx;
+    __syncthreads();
+  }
+}
+
+template <int kSrc>
+static hipError_t launch_hist_runs(const PixelSource& src, int64_t n, int32_t bins, float* out, hipStream_t st,
+                                   int cu_count) {
+  const dim3 grid((unsigned)(n < kRunBlocks ? n : kRunBlocks));
+  const size_t lds = bins * bins * bins * sizeof(uint32_t);
+  if (n <= (int64_t)cu_count * 8)
+    hipLaunchKernelGGL((hist_runs_kernel<kSrc, 256>), grid, dim3(256), lds, st, src, n, bins, bin_shift(bins), out);
+  else
+    hipLaunchKernelGGL((hist_runs_kernel<kSrc, 128>), grid, dim3(128), lds, st, src, n, bins, bin_shift(bins), out);
+  return hipGetLastError();
 }
 
 // Histograms plus the join's operand prep of each histogram row (rows n..npad
@@ -228,12 +296,6 @@ __global__ __launch_bounds__(64 * kHistWaves) void hist_prep_kernel(PixelSource 
   }
 }
 
-static int bin_shift(int bins) {
-  int shift = 0;
-  while ((256 >> shift) > bins) ++shift;
-  return shift;
-}
-
 // Host launchers; arguments validated by the caller.
 hipError_t launch_hist_rgb8(const uint8_t* patches, int64_t n, int32_t h, int32_t w, int32_t bins,
                             float* out, hipStream_t st, int cu_count) {
@@ -244,13 +306,10 @@ hipError_t launch_hist_rgb8(const uint8_t* patches, int64_t n, int32_t h, int32_
   const int64_t ngroups = (n + kHistWaves - 1) / kHistWaves;
   const int grid = (int)(ngroups < (int64_t)cu_count * 64 ? ngroups : (int64_t)cu_count * 64);
   const PixelSource src{patches, h, w, nullptr, 0, nullptr};
-  const bool vec = (npx % 16 == 0) && ((reinterpret_cast<uintptr_t>(patches) & 15) == 0);
-  if (vec)
-    hipLaunchKernelGGL(hist_rgb8_kernel<kSrcPatch48>, dim3(grid), dim3(64 * kHistWaves), lds, st, src, n, bins,
-                       bin_shift(bins), out);
-  else
-    hipLaunchKernelGGL(hist_rgb8_kernel<kSrcPatch>, dim3(grid), dim3(64 * kHistWaves), lds, st, src, n, bins,
-                       bin_shift(bins), out);
+  if (npx % 16 != 0 || (reinterpret_cast<uintptr_t>(patches) & 15) != 0)
+    return launch_hist_runs<kSrcPatch>(src, n, bins, out, st, cu_count);
+  hipLaunchKernelGGL(hist_patch48_kernel, dim3(grid), dim3(64 * kHistWaves), lds, st, src, n, bins, bin_shift(bins),
+                     out);
   return hipGetLastError();
 }
 
@@ -258,14 +317,7 @@ hipError_t launch_hist_crops(const uint8_t* frames, int64_t nframes, int32_t hei
                              const dl_box* boxes, int64_t n, int32_t bins, float* out, int* bad_box, hipStream_t st,
                              int cu_count) {
   if (n == 0) return hipSuccess;
-  const int nb = bins * bins * bins;
-  const size_t lds = (size_t)kHistWaves * nb * sizeof(uint32_t);
-  const int64_t ngroups = (n + kHistWaves - 1) / kHistWaves;
-  const int grid = (int)(ngroups < (int64_t)cu_count * 64 ? ngroups : (int64_t)cu_count * 64);
-  const PixelSource src{frames, height, width, boxes, nframes, bad_box};
-  hipLaunchKernelGGL(hist_rgb8_kernel<kSrcCrop>, dim3(grid), dim3(64 * kHistWaves), lds, st, src, n, bins,
-                     bin_shift(bins), out);
-  return hipGetLastError();
+  return launch_hist_runs<kSrcCrop>(PixelSource{frames, height, width, boxes, nframes, bad_box}, n, bins, out, st, cu_count);
 }
 
 template <int kSrc>
