@@ -625,9 +625,17 @@ dl_status eps_core(dl_ctx* c, const EpsJob& J, void* ws, size_t ws_bytes, dl_pai
     L.ps = *J.ps_ext;
     L.ss = J.ss_ext;
   }
+  // The streaming pass's part counters lie where the ordering puts its row
+  // offsets later (few rows: one counter does).
+  const bool stream = stream_applies(prec, L.pr.qld, R.n, S.n);
+  const int64_t at_seg = round_up(R.n + 1, 32);
+  const bool parts = stream && at_seg + 2 * kSegWords * kSegments <= 2 * (R.n + 1);
+  unsigned long long* const seg = parts ? reinterpret_cast<unsigned long long*>(L.rows + at_seg) : nullptr;
   {
     StageTimer t(c, 1, st);
-    DL_HIP(c, launch_call_init(L.state, 2 * kStateWords, L.rows, R.n + 1, nullptr, 0, nullptr, 0, st, c->cu_count));
+    DL_HIP(c, launch_call_init(L.state, 2 * kStateWords, L.rows,
+                               parts ? at_seg + 2 * kSegWords * kSegments : R.n + 1, nullptr, 0, nullptr, 0, st,
+                               c->cu_count));
     DL_HIP(c, prep_relations(c, R, rx ? nullptr : &L.pr, nullptr, S, self || sx ? nullptr : &L.ps, nullptr, prec,
                              L.state, st));
     DL_HIP(c, launch_threshold(L.pr, R.n, L.ss, R.d, J.T, J.Trow, L.thr, nullptr, L.pex, nullptr, st, L.sr, L.state));
@@ -651,7 +659,8 @@ dl_status eps_core(dl_ctx* c, const EpsJob& J, void* ws, size_t ws_bytes, dl_pai
     p.candp = prec == DL_FP8 ? nullptr : L.candp;  // E4M3 stages no P~ (LDS budget)
     p.ccap = cap;
     p.gate = &L.cnt->invalid;
-    if (stream_applies(prec, p.qld, R.n, S.n))
+    p.seg = seg;
+    if (stream)
       DL_HIP(c, launch_stream_eps(prec, p, L.pr.npad, st, c->cu_count));
     else
       DL_HIP(c, launch_cand_eps(prec, p, st, c->cu_count));
@@ -669,6 +678,7 @@ dl_status eps_core(dl_ctx* c, const EpsJob& J, void* ws, size_t ws_bytes, dl_pai
     q.nrm2R = L.pr.nrm2;
     q.xnR = L.pr.xnorm; q.mlR = L.pr.mlsb;
     q.xnS = L.ps.xnorm; q.mlS = L.ps.mlsb;
+    q.seg = seg;
     q.T = J.T;
     q.Trow = J.Trow;
     q.bj = bj;

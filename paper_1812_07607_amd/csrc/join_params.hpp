@@ -51,6 +51,19 @@ struct PrepPair {
   PrepJob j[2];  // the second may be empty (P.npad 0)
 };
 
+// A candidate list in parts: part s holds the slots from segment_first(cap, s)
+// to the next part's first.  A pass that finds many candidates is bound by the
+// list's counter (17 ns an atomic on one address, whoever sends it: 195M
+// candidates in flushes of 128 took 26 ms of counter); eight count side by
+// side.  A flush that its part has no room for goes on in the next one, so the
+// list holds as many candidates as one part of its size would.
+constexpr int kSegments = 8;
+constexpr int kSegWords = 16;  // 64-bit words between counters: lines of their own
+__host__ __device__ inline int64_t segment_first(int64_t cap, int s) { return cap / kSegments * s; }
+__host__ __device__ inline int64_t segment_end(int64_t cap, int s) {
+  return s + 1 == kSegments ? cap : segment_first(cap, s + 1);
+}
+
 // Candidate pass on the matrix cores (join_mfma.hip).
 struct CandParams {
   const uint8_t* qa;   // R operand rows (qld bytes each, npad rows)
@@ -80,6 +93,9 @@ struct CandParams {
   uint2* cand;         // (i, j) records
   float* candp;        // P~ of each record (null: not kept)
   int64_t ccap;
+  // streaming pass (nullable): counters of the list's kSegments parts, each on
+  // lines of its own; ccount then gets every workgroup's total once
+  unsigned long long* seg;
   // band mode
   int P;               // S splits
   int64_t tps;         // S tiles per split
@@ -140,6 +156,7 @@ struct RecheckParams {
   const float* S; int64_t lds;
   int d;
   const uint2* cand; const unsigned long long* ccount; int64_t ccap;
+  const unsigned long long* seg;  // the parts' counters, or null: one list of *ccount
   const float* candp;   // P~ of each candidate, or null
   const int* pexR;      // per R row: the candidate pass computed P~ exactly
   const double* nrm2R;  // |a|^2 per R row (float64)

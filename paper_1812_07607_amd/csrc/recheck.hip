@@ -135,9 +135,8 @@ __device__ inline void group_d2(const float* const (&a)[kN], const float* const 
 
 // ------------------------------------------------------------ eps recheck
 
-
-// A wave takes 64 candidates at a time, one per lane; each pair of lanes
-// computes the float32 distances of its two candidates in turn, then the wave
+// A wave takes 64 candidates at a time, one per lane; each four lanes compute
+// the float32 distances of their four candidates in turn, then the wave
 // classifies the 64 lane-parallel.  The confirmed ones of a workgroup's four
 // waves, one or kRecheckChunks such batches each, are appended with one atomic
 // (one counter serves the whole grid: at about 10 ns apiece, an atomic per
@@ -147,22 +146,37 @@ __device__ inline void group_d2(const float* const (&a)[kN], const float* const 
 // d2 = |a|^2 - 2 P~ exactly (P~ = a.b - |b|^2/2), evaluated in float64
 // without rounding.
 //
-// Bound by the gather of the rows.  Two lanes a candidate read 32 bytes of a
-// row at a time where one lane reads 16 of 64 different rows; with more lanes
-// the per-candidate work (addresses, the sum across lanes) weighs more.
-// Microseconds with one / two / four / eight lanes: 32k candidates, d = 64:
-// 16 / 14 / 15 / 17; 0.58M, d = 100: 96 / 82 / 80 / 97; 10M, d = 200: 1212 /
-// 972 / 909 / 935; 7.3M of 500,000 x 500,000, d = 128: 2047 / 1629 / 1590 /
-// 1582; 155M, d = 100: 12,600 / 14,500 / 14,200 / 16,200.
+// Bound by the gather of the rows.  Four lanes a candidate read 64 bytes of a
+// row at a time; with fewer a load touches more rows, with more the
+// per-candidate work (addresses, the sum across lanes) weighs more.
+// Microseconds with two / four / eight lanes: 23k candidates, d = 64: 16.5 /
+// 15.5 / 18.5; 0.58M, d = 100: 79 / 82 / 98; 5M, d = 128: 870 / 748 / 741;
+// 195M, d = 100: 20,800 / 17,600 / 19,400; 0.1M, d = 512: 101 / 97 / 96.
 constexpr int kRecheckChunks = 4;  // 64-candidate batches of a wave per output atomic, at most
-constexpr int kRecheckLanes = 2;   // lanes that share a candidate's rows
+constexpr int kRecheckLanes = 4;   // lanes that share a candidate's rows
 
 __global__ __launch_bounds__(256) void recheck_eps_kernel(RecheckParams p) {
   __shared__ unsigned long long s_pos;
   __shared__ int s_in[4];
   const int wave = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63, sub = lane & (kRecheckLanes - 1);
-  const int64_t n = min((int64_t)*p.ccount, p.ccap);
+  // the candidates of the list's part `lane` (one part without seg)
+  int64_t mine_n = 0;
+  if (lane < kSegments) {
+    const int64_t room = p.seg ? segment_end(p.ccap, lane) - segment_first(p.ccap, lane) : lane == 0 ? p.ccap : 0;
+    mine_n = min((int64_t)(p.seg ? p.seg[lane * kSegWords] : *p.ccount), room);
+  }
+  auto part = [&](int s) {  // of part s
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)mine_n, s);
+    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)((uint64_t)mine_n >> 32), s);
+    return (int64_t)((uint64_t)hi << 32 | lo);
+  };
+  int64_t n = 0, some = 0;
+  for (int s = 0; s < kSegments; ++s) {
+    const int64_t len = part(s);
+    n += len;
+    if (len) some = segment_first(p.ccap, s);
+  }
   const uint64_t lt = __lanemask_lt();
   // 16-byte row loads when every row is aligned
   const bool vec4 = ((reinterpret_cast<uintptr_t>(p.S) | reinterpret_cast<uintptr_t>(p.R)) & 15) == 0 &&
@@ -171,11 +185,25 @@ __global__ __launch_bounds__(256) void recheck_eps_kernel(RecheckParams p) {
   // (0.5M candidates without row reads: 31 us with one batch, 20 with four),
   // and, where rows are gathered, fill them several times over (0.58M, d = 100:
   // 82 us with one, 99 with four).
-  const bool gathers = !(p.candp && n > 0 && p.pexR[p.cand[0].x]);
+  const bool gathers = !(p.candp && n > 0 && p.pexR[p.cand[some].x]);
   const int64_t fill = (int64_t)gridDim.x / 16 * 256 * kRecheckChunks;  // the grid is 16 per CU
   const int chunks = n >= fill * (gathers ? 8 : 1) ? kRecheckChunks : 1;
   const int64_t span = 64 * chunks;  // of a wave
-  for (int64_t block0 = blockIdx.x * span * 4; block0 < n; block0 += gridDim.x * span * 4) {
+  const int span_log = chunks == 1 ? 8 : 10;  // of a workgroup
+  static_assert(kRecheckChunks == 4, "span_log");
+  for (int64_t block = blockIdx.x;; block += gridDim.x) {
+    // the part this workgroup's next spans lie in, and where
+    int64_t block0 = -1, end = 0, left = block;
+    for (int s = 0; s < kSegments; ++s) {
+      const int64_t len = part(s), blocks = (len + span * 4 - 1) >> span_log;
+      if (left < blocks) {
+        block0 = segment_first(p.ccap, s) + left * span * 4;
+        end = segment_first(p.ccap, s) + len;
+        break;
+      }
+      left -= blocks;
+    }
+    if (block0 < 0) break;
     const int64_t base0 = block0 + wave * span;
     bool in[kRecheckChunks], tie[kRecheckChunks];
     float dist[kRecheckChunks];
@@ -187,7 +215,7 @@ __global__ __launch_bounds__(256) void recheck_eps_kernel(RecheckParams p) {
       dist[c] = 0.0f;
       mine[c] = make_uint2(0, 0);
       const int64_t base = base0 + c * 64;
-      const int cnt = (int)max((int64_t)0, min((int64_t)64, n - base));
+      const int cnt = (int)max((int64_t)0, min((int64_t)64, end - base));
       if (c >= chunks || cnt == 0) continue;
       if (lane < cnt) mine[c] = p.cand[base + lane];
       float mys = 0.0f;

@@ -47,6 +47,10 @@
 // Measured (one MI355X): the 10^6 x 10^6, d = 128, bf16 pass 158 ms (1.62
 // PFLOP/s) against the tile form's 238 ms; a loop of the same matrix
 // instructions and LDS reads alone, on such operands, runs at 1.94 PFLOP/s.
+// The matrix cores are busy 69% of the time at 2.25 GHz; what idles them is not
+// what bounds the pass: letting the two waves of a SIMD test in turns, or
+// meeting a barrier every second stage only, changed nothing (the clock gives
+// what the stalls no longer take).
 #include <type_traits>
 
 #include "cand_device.hpp"
@@ -70,6 +74,7 @@ struct StreamGeom {
   static constexpr int kStageBytes = kStageRows * kKB;
   static constexpr int kDma = kStageBytes / 1024 / 8;       // transfers per wave and stage
   static constexpr int kRowGroups = kStageRows / 8;
+  static constexpr int kRecords = kPrec == DL_FP8 && kKB == 128 ? 96 : 128;  // staged per wave: what LDS has left
 };
 constexpr int kStreamStages = 4;
 
@@ -120,21 +125,122 @@ __device__ inline UnitAt stream_unit(const StreamParams& p, int64_t L) {
 // the band's thresholds come.
 enum : int { kStreamEps = 0, kStreamBand = 1, kStreamMax = 2 };
 
-// A wave's staged band entries to their rows' buffers: one slot each from the
+// A wave's staged outputs.  A record is one lane's four outputs of a 16 x 16
+// block of which at least one passes: its row i, its first column j and the
+// outputs (-P~).  Staging whole records costs one compaction per block, where
+// compacting hit by hit costs eight compares and branches and fifteen
+// instructions a hit; what each record holds is sorted out 64 records at a
+// time, when the queue is full: the outputs against the row's threshold, the
+// columns against the end of S and the diagonal.  Against hits staged one by
+// one: 60,001 rows, d = 100, fp16, 0.58M candidates 463 -> 416 us of pass; top-10
+// of 200,000 x 200,000, about 970 entries a row, 9.4 -> 9.0 ms; of 37 x 4M 325 ->
+// 287 us; 20,000 x 1M, d = 256, E4M3 6.1 -> 5.6 ms; 195M candidates in E4M3 9.5
+// -> 4.7 ms (half of that by the list's parts).
+// Bit r: output r of the record is a hit.
+template <int kMode>
+__device__ inline uint32_t record_hits(const StreamParams& p, const f32x4& v, const uint2& ij, float nthr) {
+  uint32_t hits = 0;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const uint32_t j = ij.y + r;
+    const bool in = v[r] <= nthr && j < (uint32_t)p.c.nS &&
+                    (kMode == kStreamEps ? !p.c.self_join || j > ij.x : !p.c.exclude_self || j != ij.x);
+    hits |= in ? 1u << r : 0u;
+  }
+  return hits;
+}
+
+// The hits of nq records, in their order, lo to hi - 1 of them to the candidate
+// list from slot base on; returns their number.
+template <bool kStageP, bool kWrite>
+__device__ inline int spill_eps(const StreamParams& p, const f32x4* qv, const uint2* qij, const float* thr,
+                                uint32_t row0, int nq, int64_t base, int lo, int hi) {
+  const int lane = fresh_lane();
+  int n = 0;
+#pragma unroll 1
+  for (int s0 = 0; s0 < nq; s0 += 64) {
+    const int s = s0 + lane;
+    uint32_t hits = 0;
+    f32x4 v{};
+    uint2 ij = make_uint2(0, 0);
+    if (s < nq) {
+      v = qv[s];
+      ij = qij[s];
+      hits = record_hits<kStreamEps>(p, v, ij, thr[ij.x - row0]);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const uint64_t m = __ballot(hits >> r & 1);
+      if (kWrite && (hits >> r & 1)) {
+        const int at = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+        if (at >= lo && at < hi) {
+          p.c.cand[base + (at - lo)] = make_uint2(ij.x, ij.y + r);
+          if (kStageP && p.c.candp) p.c.candp[base + (at - lo)] = -v[r];
+        }
+      }
+      n += __popcll(m);
+    }
+  }
+  return n;
+}
+// All of them, to the workgroup's part of the list and, should it be full, the
+// parts after it (past the last one hits are only counted: the caller retries
+// with room).  Returns their number.
+template <bool kStageP>
+__device__ inline int flush_eps_records(const StreamParams& p, const f32x4* qv, const uint2* qij, const float* thr,
+                                        uint32_t row0, int nq) {
+  const int n = spill_eps<kStageP, false>(p, qv, qij, thr, row0, nq, 0, 0, 0);
+  int lo = 0;
+#pragma unroll 1
+  for (int t = 0; t < kSegments && lo < n; ++t) {
+    const int s = p.c.seg ? (blockIdx.x + t) & (kSegments - 1) : 0;
+    unsigned long long at = 0;
+    if (fresh_lane() == 0) at = atomicAdd(p.c.seg ? p.c.seg + s * kSegWords : p.c.ccount, (unsigned long long)(n - lo));
+    const int64_t pos = uniform64((int64_t)at) + (p.c.seg ? segment_first(p.c.ccap, s) : 0);
+    const int64_t room = (p.c.seg ? segment_end(p.c.ccap, s) : p.c.ccap) - pos;
+    if (room > 0) {
+      const int hi = room < n - lo ? lo + (int)room : n;
+      spill_eps<kStageP, true>(p, qv, qij, thr, row0, nq, pos, lo, hi);
+      lo = hi;
+    }
+    if (!p.c.seg) break;
+  }
+  return n;
+}
+
+// The hits of nq records to their rows' buffers, one atomic per record on the
 // row's counter (two in flight per lane); entries past the buffer are counted
 // and flagged.
-__device__ inline void flush_rows(const StreamParams& p, const uint2* q, const uint32_t* qp, int nq) {
+__device__ inline void flush_rows(const StreamParams& p, const f32x4* qv, const uint2* qij, const float* thr,
+                                  uint32_t row0, int nq) {
   const int lane = fresh_lane();
-#pragma unroll 1
-  for (int s = lane; s < nq; s += 128) {
-    const bool two = s + 64 < nq;
-    const uint2 e0 = q[s], e1 = two ? q[s + 64] : e0;
-    const uint32_t p0 = (uint32_t)atomicAdd(p.c.bcount + e0.x, 1);
-    const uint32_t p1 = two ? (uint32_t)atomicAdd(p.c.bcount + e1.x, 1) : 0u;
-    const uint32_t cap = (uint32_t)p.c.cap;
-    if (p0 < cap) p.c.band[(int64_t)e0.x * p.c.cap + p0] = make_uint2(qp[s], e0.y);
-    if (two && p1 < cap) p.c.band[(int64_t)e1.x * p.c.cap + p1] = make_uint2(qp[s + 64], e1.y);
-    if (p0 >= cap || p1 >= cap) *p.c.overflow = 1;
+  uint32_t hits[2], at[2];
+  f32x4 v[2];
+  uint2 ij[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int s = 64 * h + lane;
+    hits[h] = 0;
+    if (s < nq) {
+      v[h] = qv[s];
+      ij[h] = qij[s];
+      hits[h] = record_hits<kStreamBand>(p, v[h], ij[h], thr[ij[h].x - row0]);
+    }
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+    if (hits[h]) at[h] = (uint32_t)atomicAdd(p.c.bcount + ij[h].x, __popc(hits[h]));
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    if (!hits[h]) continue;
+    uint2* const row = p.c.band + (int64_t)ij[h].x * p.c.cap;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      if (!(hits[h] >> r & 1)) continue;
+      if (at[h] < (uint32_t)p.c.cap) row[at[h]] = make_uint2(__float_as_uint(-v[h][r]), ij[h].y + r);
+      else *p.c.overflow = 1;
+      ++at[h];
+    }
   }
 }
 
@@ -147,15 +253,15 @@ __global__ __launch_bounds__(kThreads, 1) void stream_kernel(StreamParams p) {
   __shared__ __attribute__((aligned(16))) float side_h[kStreamStages][G::kStageRows];
   __shared__ __attribute__((aligned(16))) int side_s[kFp8 ? kStreamStages : 1][kFp8 ? G::kStageRows : 4];
   constexpr bool kMax = kMode == kStreamMax;
-  __shared__ __attribute__((aligned(16))) uint2 eq_lds[kMax ? 1 : kThreads / 64][kMax ? 1 : kQueue];
-  // P~ of the staged records (eps with E4M3 needs none: it is never exact)
-  constexpr bool kStageP = kMode == kStreamBand || (kMode == kStreamEps && !kFp8);
-  __shared__ uint32_t eqp_lds[kStageP ? kThreads / 64 : 1][kStageP ? kQueue : 1];
+  constexpr int kRecords = G::kRecords;
+  __shared__ __attribute__((aligned(16))) f32x4 qv_lds[kMax ? 1 : kThreads / 64][kMax ? 1 : kRecords];
+  __shared__ __attribute__((aligned(16))) uint2 qij_lds[kMax ? 1 : kThreads / 64][kMax ? 1 : kRecords];
+  __shared__ float thr_lds[kMax ? 1 : kThreads / 64][kMax ? 1 : G::kWaveRows];  // nthr, by row
+  constexpr bool kStageP = kMode == kStreamEps && !kFp8;  // (E4M3 candidates need no P~: it is never exact)
 
   if (p.c.gate && __builtin_amdgcn_readfirstlane(*p.c.gate)) return;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  const int r16 = lane & 15, quad = lane >> 4;
   // this workgroup's share of the units; consecutive shares on one XCD
   const int ng = gridDim.x;
   const int share = (blockIdx.x & 7) * (ng >> 3) + (blockIdx.x >> 3);
@@ -215,7 +321,16 @@ __global__ __launch_bounds__(kThreads, 1) void stream_kernel(StreamParams p) {
   uint32_t row0 = 0;  // first R row of this wave
   uint32_t pj = 0;    // first S row of the strip whose outputs await their test
   const uint32_t ns = (uint32_t)p.c.nS;
+  int64_t hits = 0;  // flushed so far (eps)
+  auto flush = [&]() {
+    if constexpr (kMode == kStreamEps)
+      hits += flush_eps_records<kStageP>(p, qv_lds[wave], qij_lds[wave], thr_lds[wave], row0, nq);
+    if constexpr (kMode == kStreamBand) flush_rows(p, qv_lds[wave], qij_lds[wave], thr_lds[wave], row0, nq);
+    nq = 0;
+  };
   auto load_r = [&]() {
+    if constexpr (!kMax)
+      if (nq) flush();  // (the records' thresholds are the leaving rows')
     row0 = (uint32_t)(rb * wr + rw) * G::kWaveRows;
     const uint32_t flip = kFp8 ? 0x80808080u : 0x80008000u;
     // rows past the padded relation repeat its last row and never hit
@@ -239,65 +354,33 @@ __global__ __launch_bounds__(kThreads, 1) void stream_kernel(StreamParams p) {
       if constexpr (kMode == kStreamBand)
         nthr[b] = (int64_t)row0 + want < p.c.nR ? -key_float(p.c.gkey[i0 + i]) : -INFINITY;
       if constexpr (kMax) nthr[b] = INFINITY;
+      else if (l < 16) thr_lds[wave][want] = nthr[b];
       if constexpr (kFp8) {
         const int e = (p.c.sexa[i0 + i] + 127) << (8 * (b & 3));
         rsc[b / 4] = (b & 3) ? rsc[b / 4] | e : e;
       }
     }
   };
-  auto flush = [&]() {
-    if constexpr (kMode == kStreamEps) flush_eps<kStageP>(p.c, eq_lds[wave], eqp_lds[kStageP ? wave : 0], nq);
-    if constexpr (kMode == kStreamBand) flush_rows(p, eq_lds[wave], eqp_lds[wave], nq);
-    nq = 0;
+  // One block's outputs v (strip pj, threshold nt): the lanes of its two 16 x
+  // 16 blocks that pass.
+  auto passing = [&](const f32x4 (&v)[2], float nt, uint64_t (&m)[2]) {
+#pragma unroll
+    for (int sb = 0; sb < 2; ++sb)
+      m[sb] = mask_le(__builtin_elementwise_minimum(min3(v[sb][0], v[sb][1], v[sb][2]), v[sb][3]), nt);
   };
-  // whether the strip pj needs its columns checked: the end of S, or the
-  // diagonal (a self-join's j > i, a top-k's j != i)
-  auto at_edge = [&]() {
-    if (pj + 32 > ns) return true;
-    if constexpr (kMode == kStreamEps) return p.c.self_join && pj <= row0 + G::kWaveRows;
-    if constexpr (kMode == kStreamBand)
-      return p.c.exclude_self && pj < row0 + G::kWaveRows && pj + 32 > row0;
-    return false;
-  };
-  // The hits of mask m, rows i and columns j, into the wave's queue.
-  auto stage = [&](uint64_t m, uint32_t i, uint32_t j, float x) {
+  auto stage = [&](const f32x4& v, uint64_t m, uint32_t i, uint32_t j) {
     if (__builtin_amdgcn_inverse_ballot_w64(m)) {
       const int s = nq + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
-      eq_lds[wave][s] = make_uint2(i, j);
-      if constexpr (kStageP) eqp_lds[wave][s] = __float_as_uint(-x);
+      qv_lds[wave][s] = v;
+      qij_lds[wave][s] = make_uint2(i, j);
     }
     nq += __popcll(m);
   };
-  // Hits among one block's outputs v (strip pj, rows i, threshold nt), columns
-  // checked, a 16-row block of S at a time (at most 256 hits, one check of the
-  // queue's room).
-  auto take = [&](const f32x4 (&v)[2], uint32_t i, float nt) {
-    const bool edge = at_edge();
-#pragma unroll
-    for (int sb = 0; sb < 2; ++sb) {
-      const uint32_t j = pj + 16 * sb + 4 * (fresh_lane() >> 4);
-      uint64_t m[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) m[r] = mask_le(v[sb][r], nt);
-      if (edge) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          m[r] &= __builtin_amdgcn_ballot_w64(
-              j + r < ns && (kMode == kStreamEps ? !p.c.self_join || j + r > i : !p.c.exclude_self || j + r != i));
-      }
-      const int n = __popcll(m[0]) + __popcll(m[1]) + __popcll(m[2]) + __popcll(m[3]);
-      if (n == 0) continue;
-      if (nq + n > kQueue) flush();
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        if (m[r]) stage(m[r], i, j + r, v[sb][r]);
-    }
-  };
   // The candidate test of a strip's outputs: four minimum instructions and a
-  // compare per block, one branch for all.  A strip with few hits stages them
-  // straight from the accumulators; one with many, or at an edge, takes its
-  // blocks through one copy of the code that checks columns and room (a copy
-  // each would overflow the instruction cache).
+  // compare per block, one branch for all.  A strip with few hits stages its
+  // records straight from the accumulators; one with many takes its blocks
+  // through one copy of the code that checks the queue's room (a copy each
+  // would overflow the instruction cache).
   auto test = [&]() {
     uint64_t any = 0, h[kNB];
 #pragma unroll
@@ -308,22 +391,20 @@ __global__ __launch_bounds__(kThreads, 1) void stream_kernel(StreamParams p) {
       any |= h[b];
     }
     if (!any) return;
-    int most = 0;  // hits of the strip, at most
+    int most = 0;  // records of the strip, at most
 #pragma unroll
-    for (int b = 0; b < kNB; ++b) most += 8 * __popcll(h[b]);
-    if (most <= kQueue && !at_edge()) {
-      if (nq + most > kQueue) flush();
+    for (int b = 0; b < kNB; ++b) most += 2 * __popcll(h[b]);
+    if (nq + most > kRecords && nq > 0) flush();
+    if (most <= kRecords) {
       const int l = fresh_lane();
       const uint32_t i0 = row0 + (l & 15), j0 = pj + 4 * (l >> 4);
 #pragma unroll
       for (int b = 0; b < kNB; ++b) {
         if (!h[b]) continue;
+        uint64_t m[2];
+        passing(acc[b], nthr[b], m);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float x = acc[b][e >> 2][e & 3];
-          const uint64_t m = mask_le(x, nthr[b]);
-          if (m) stage(m, i0 + b * 16, j0 + 16 * (e >> 2) + (e & 3), x);
-        }
+        for (int sb = 0; sb < 2; ++sb) stage(acc[b][sb], m[sb], i0 + b * 16, j0 + 16 * sb);
       }
       return;
     }
@@ -345,7 +426,16 @@ __global__ __launch_bounds__(kThreads, 1) void stream_kernel(StreamParams p) {
           // a uniform jump to eight moves, not a chain of selects
           asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(nt));
         }
-      take(v, row0 + b * 16 + (fresh_lane() & 15), nt);
+      uint64_t m[2];
+      passing(v, nt, m);
+#pragma unroll 1
+      for (int sb = 0; sb < 2; ++sb) {  // (64 records at most each)
+        if (nq + __popcll(m[0]) > kRecords) flush();
+        const int l = fresh_lane();
+        stage(v[0], m[0], row0 + b * 16 + (l & 15), pj + 16 * sb + 4 * (l >> 4));
+        v[0] = v[1];
+        m[0] = m[1];
+      }
     }
   };
   // Max mode: the strip's outputs into the running minima (columns past S
@@ -382,8 +472,15 @@ __global__ __launch_bounds__(kThreads, 1) void stream_kernel(StreamParams p) {
   };
 
   // the lane's LDS offset of its piece of K-step 0 of 16 rows; the K-step and
-  // the 16-row block are immediate offsets
-  const int lo0 = (r16 >> 3) * 1024 + (r16 & 7) * 64 + ((quad ^ (r16 >> 2)) << 4);
+  // the 16-row block are immediate offsets (formed anew for each strip: kept
+  // over the test it would be spilled, and a reload waits for every transfer
+  // issued before it)
+  int lo0;
+  auto piece_offset = [&]() {
+    const int l = fresh_lane();
+    const int r16 = l & 15;
+    lo0 = (r16 >> 3) * 1024 + (r16 & 7) * 64 + (((l >> 4) ^ (r16 >> 2)) << 4);
+  };
   auto load_a1 = [&](const uint8_t* strip, int u, int sb) {
 #pragma unroll
     for (int q = 0; q < kU; ++q) {
@@ -444,6 +541,7 @@ __global__ __launch_bounds__(kThreads, 1) void stream_kernel(StreamParams p) {
       buf = u & (kStreamStages - 1);
       if (lu < nu) issue();
       if (u == 0) {
+        piece_offset();
 #pragma unroll
         for (int f = 0; f < kW; ++f) load_a(ring[buf] + grp * 4096, f);
         load_ini(buf, grp);
@@ -471,6 +569,7 @@ __global__ __launch_bounds__(kThreads, 1) void stream_kernel(StreamParams p) {
       load_r();
       fresh_r = false;
     }
+    piece_offset();
     const bool last = t + 1 == per;
     const int nbuf = last ? (buf + 1) & (kStreamStages - 1) : buf;
     const int nstrip = last ? grp : strip + ws;
@@ -519,8 +618,18 @@ __global__ __launch_bounds__(kThreads, 1) void stream_kernel(StreamParams p) {
     }
   }
   if constexpr (kMode == kStreamEps) {
-    __shared__ __attribute__((aligned(8))) int s_left[kThreads / 64 + 2];
-    flush_eps_last<kStageP>(p.c, eq_lds[wave], eqp_lds[kStageP ? wave : 0], nq, s_left);
+    if (nq) flush();
+    if (p.c.seg) {
+      // the workgroup's total; the words lie in a stage no wave reads any more
+      int64_t* const s_hits = reinterpret_cast<int64_t*>(ring[nu & (kStreamStages - 1)]);
+      if (lane == 0) s_hits[wave] = hits;
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        unsigned long long all = 0;
+        for (int w = 0; w < kThreads / 64; ++w) all += (unsigned long long)s_hits[w];
+        if (all) atomicAdd(p.c.ccount, all);
+      }
+    }
   } else if constexpr (kMode == kStreamBand) {
     if (nq) flush();
   }
@@ -661,7 +770,7 @@ bool stream_band_applies(int64_t nS, int k) { return nS >= 16 * (int64_t)k || nS
 // call time, 4 takes 70): at most 8.
 //
 // Measured (one MI355X): top-10 of 200,000 x 200,000, d = 128, bf16: sample
-// 1.8 ms, thresholds 0.05, pass 8.6, against 21.4 ms for the tile form, whose
+// 1.7 ms, thresholds 0.05, pass 7.3, against 21.4 ms for the tile form, whose
 // bands are tightened row by row inside the pass.
 hipError_t launch_stream_band(dl_prec prec, const CandParams& c, int64_t npad_r, int k, uint32_t* gmax, hipStream_t st,
                               int cu_count) {
