@@ -641,8 +641,11 @@ __global__ __launch_bounds__(kThreads, 1) void stream_kernel(StreamParams p) {
 // a P~ at or above it: the band P~ >= v - E_i keeps every one of the k
 // nearest, as in the tile form's tightening.  kPer lanes share a row, each
 // with kKeys of its keys in registers, 64 / kPer rows side by side in a wave.
-constexpr int kKeys = 64;
-template <int kPer>
+// Many rows: 64 keys a lane.  Few: the rows' latency is the kernel's time, so
+// their keys are spread over as many lanes as leave eight each (37 rows of 64
+// keys: 26 -> 8 us).
+constexpr int kKeys = 64, kFewKeys = 8;
+template <int kPer, int kKeys>
 __global__ __launch_bounds__(64) void band_key_kernel(const uint32_t* __restrict__ gmax, int ngroups, int64_t nR, int k,
                                                       const float* __restrict__ marg, uint32_t* __restrict__ gkey) {
   constexpr int kRows = 64 / kPer;
@@ -756,18 +759,55 @@ int stream_groups(int k) {
 constexpr int64_t kAllRows = 512;
 bool stream_band_applies(int64_t nS, int k) { return nS >= 16 * (int64_t)k || nS <= kAllRows; }
 
+// Every how many stages of S the sample takes one.  The sample costs 1 / stride
+// of a pass and leaves about stride times the rows of the band itself to be
+// staged and selected from.  Few rows wait for what they stage: the sum is
+// smallest where stride^2 is nS / 100 (k + 90) or so (37 x 4M, top-10: 20, 285
+// us of passes; 36, 299).  Many hide it behind the matrix cores: nS / (240 k +
+// 600) (200,000 x 200,000, top-10, passes: stride 4 9.08 ms, 5 8.87, 6 8.80, 8
+// 8.69; 178,455 x 247,864, top-50: 4 11.7, 5 11.8, 6 12.0), but at most 8: the
+// neighbours of a row may lie together in S, and a sample that misses them
+// bounds the row loosely.  E4M3 takes at most 8 anyway: its margin is as wide as
+// the spread of near rows, so its bands grow faster as the threshold loosens and
+// a buffer may not hold them (50,000 queries x 4M rows, d = 256, top-32: stride
+// 18 overflows buffers, 9 takes 64 ms of call time, 4 takes 70).
+static int sample_stride(dl_prec prec, int64_t nR, int64_t nS, int k) {
+  int few = 1, many = 1;
+  while ((int64_t)(few + 1) * (few + 1) * 100 * (k + 90) <= nS) ++few;
+  while (many < 8 && (int64_t)(many + 1) * (many + 1) * (240 * k + 600) <= nS) ++many;
+  const int s = nR >= 1024 && many > few ? many : few;
+  return prec == DL_FP8 && s > 8 ? 8 : s;
+}
+
+template <int kKeysOf>
+static hipError_t launch_band_key_of(int per, const uint32_t* gmax, int ng, int64_t nR, int k, const float* marg,
+                                     uint32_t* gkey, hipStream_t st) {
+  const dim3 grid((unsigned)((nR + 64 / per - 1) / (64 / per))), block(64);
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, gmax, ng, nR, k, marg, gkey); };
+  switch (per) {
+    case 1: go(band_key_kernel<1, kKeysOf>); break;
+    case 2: go(band_key_kernel<2, kKeysOf>); break;
+    case 4: go(band_key_kernel<4, kKeysOf>); break;
+    case 8: go(band_key_kernel<8, kKeysOf>); break;
+    case 16: go(band_key_kernel<16, kKeysOf>); break;
+    default: go(band_key_kernel<32, kKeysOf>); break;
+  }
+  return hipGetLastError();
+}
+static hipError_t launch_band_key(const uint32_t* gmax, int ng, int64_t nR, int k, const float* marg, uint32_t* gkey,
+                                  hipStream_t st, int cu_count) {
+  int per = 1, few = 8;
+  while (per * kKeys < ng) per *= 2;
+  while (few * kFewKeys < ng) few *= 2;
+  if (few <= 32 && nR * few <= (int64_t)cu_count * 4 * 64)  // a wave per SIMD at most
+    return launch_band_key_of<kFewKeys>(few, gmax, ng, nR, k, marg, gkey, st);
+  return launch_band_key_of<kKeys>(per, gmax, ng, nR, k, marg, gkey, st);
+}
+
 // Top-k band of every row of R: the group maxima of a sample of S (every
 // stride-th stage) give each row's threshold, then the pass over all of S
 // stages what reaches it.  gmax: scratch of stream_groups(k) * nR words.
 // c.gkey holds what bounds are known (order keys), c.bcount zeros.
-//
-// The sample costs 1 / stride of a pass and leaves about stride times the
-// rows of the band itself to be staged, each at a price of about 250 cycles of
-// a wave; the sum is smallest where stride^2 is nS / 100 (k + 90) or so.  The
-// E4M3 margin is as wide as the spread of near rows, so its bands grow faster
-// as the threshold loosens and a buffer may not hold them (50,000 queries x
-// 4M rows, d = 256, top-32: stride 18 overflows buffers, 9 takes 64 ms of
-// call time, 4 takes 70): at most 8.
 //
 // Measured (one MI355X): top-10 of 200,000 x 200,000, d = 128, bf16: sample
 // 1.7 ms, thresholds 0.05, pass 7.3, against 21.4 ms for the tile form, whose
@@ -781,25 +821,12 @@ hipError_t launch_stream_band(dl_prec prec, const CandParams& c, int64_t npad_r,
   hipError_t e;
   if (c.nS > kAllRows) {
     const int ng = stream_groups(k);
-    p.stride = 1;
-    while ((int64_t)(p.stride + 1) * (p.stride + 1) * 100 * (k + 90) <= c.nS) ++p.stride;
-    if (prec == DL_FP8 && p.stride > 8) p.stride = 8;
+    p.stride = sample_stride(prec, c.nR, c.nS, k);
     p.nslots = ng / 4;
     p.gmax = gmax;
     hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)(cu_count * 4)), dim3(256), 0, st, gmax, ng * c.nR);
     if ((e = launch_stream<kStreamMax>(prec, p, npad_r, st, cu_count)) != hipSuccess) return e;
-    int per = 1;
-    while (per * kKeys < ng) per *= 2;
-    const dim3 grid((unsigned)((c.nR + 64 / per - 1) / (64 / per))), block(64);
-    switch (per) {
-      case 1: hipLaunchKernelGGL(band_key_kernel<1>, grid, block, 0, st, gmax, ng, c.nR, k, c.marg, c.gkey); break;
-      case 2: hipLaunchKernelGGL(band_key_kernel<2>, grid, block, 0, st, gmax, ng, c.nR, k, c.marg, c.gkey); break;
-      case 4: hipLaunchKernelGGL(band_key_kernel<4>, grid, block, 0, st, gmax, ng, c.nR, k, c.marg, c.gkey); break;
-      case 8: hipLaunchKernelGGL(band_key_kernel<8>, grid, block, 0, st, gmax, ng, c.nR, k, c.marg, c.gkey); break;
-      case 16: hipLaunchKernelGGL(band_key_kernel<16>, grid, block, 0, st, gmax, ng, c.nR, k, c.marg, c.gkey); break;
-      default: hipLaunchKernelGGL(band_key_kernel<32>, grid, block, 0, st, gmax, ng, c.nR, k, c.marg, c.gkey); break;
-    }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = launch_band_key(gmax, ng, c.nR, k, c.marg, c.gkey, st, cu_count)) != hipSuccess) return e;
   }
   return launch_stream<kStreamBand>(prec, p, npad_r, st, cu_count);
 }
