@@ -138,8 +138,12 @@ __device__ inline float op_elem(const uint8_t* row, int k, float scale) {
   else return dec_e4m3(row[k]) * scale;
 }
 
+// Bound by the loads' latency (a workgroup per 256 rows): 100,000 rows of 512
+// in fp16 take 55 us with eight waves and 16-byte pieces, 76 with four and a
+// column per thread.
+constexpr int kBallWaves = 8;
 template <int kPrec>
-__global__ __launch_bounds__(256) void block_ball_q_kernel(const uint8_t* __restrict__ q, int64_t qld,
+__global__ __launch_bounds__(64 * kBallWaves) void block_ball_q_kernel(const uint8_t* __restrict__ q, int64_t qld,
                                                            const int* __restrict__ sexp,
                                                            const float* __restrict__ rho, int64_t n, int d,
                                                            double eps, const float* __restrict__ eps_row,
@@ -147,8 +151,10 @@ __global__ __launch_bounds__(256) void block_ball_q_kernel(const uint8_t* __rest
   constexpr int kElem = kPrec == DL_FP32 ? 4 : kPrec == DL_FP8 ? 1 : 2;  // bytes per value
   constexpr int kPer = 16 / kElem;                                       // values per 16-byte piece
   extern __shared__ float c_lds[];  // qld / kElem floats: the centroid, zero past d
-  __shared__ double r_wave[4];
-  __shared__ float e_wave[4];
+  constexpr int kHalf = kPer > 8 ? 8 : kPer;      // values of a piece summed at a time
+  __shared__ double part[kBallWaves][64 * kHalf];  // column sums of a wave's rows
+  __shared__ double r_wave[kBallWaves];
+  __shared__ float e_wave[kBallWaves];
   __shared__ float scale_lds[kTile];
   const int64_t b = blockIdx.x;
   const int64_t r0 = b * kTile;
@@ -158,34 +164,55 @@ __global__ __launch_bounds__(256) void block_ball_q_kernel(const uint8_t* __rest
   for (int r = threadIdx.x; r < rows; r += blockDim.x)
     scale_lds[r] = kPrec == DL_FP8 ? ldexpf(1.0f, sexp[r0 + r]) : 1.0f;
   __syncthreads();
-  // the mean: one value column per thread, eight rows' loads in flight
-  for (int k = threadIdx.x; k < dpad; k += blockDim.x) {
-    double s = 0.0;
-    int r = 0;
-    for (; r + 8 <= rows; r += 8) {
-      float v[8];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int pieces = (int)(qld / 16);
+  // the mean: 16-byte pieces across the lanes, every kBallWaves-th row to a
+  // wave, four rows' loads in flight
+  for (int p0 = 0; p0 < pieces; p0 += 64) {
+    const int pc = p0 + lane;
+    double s[kPer];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = op_elem<kPrec>(base + (int64_t)(r + u) * qld, k, scale_lds[r + u]);
+    for (int e = 0; e < kPer; ++e) s[e] = 0.0;
+    if (pc < pieces)
+      for (int r = wave; r < rows; r += 4 * kBallWaves) {
+        uint4 w[4];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) s += (double)v[u];
+        for (int u = 0; u < 4; ++u)
+          w[u] = *reinterpret_cast<const uint4*>(base + (int64_t)min(r + u * kBallWaves, rows - 1) * qld + (int64_t)pc * 16);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (r + u * kBallWaves >= rows) break;
+          const uint8_t* wb = reinterpret_cast<const uint8_t*>(&w[u]);
+#pragma unroll
+          for (int e = 0; e < kPer; ++e) s[e] += (double)op_elem<kPrec>(wb, e, scale_lds[r + u * kBallWaves]);
+        }
+      }
+#pragma unroll
+    for (int h = 0; h < kPer; h += kHalf) {
+#pragma unroll
+      for (int e = 0; e < kHalf; ++e) part[wave][e * 64 + lane] = s[h + e];
+      __syncthreads();
+      for (int t = threadIdx.x; t < min(64, pieces - p0) * kHalf; t += blockDim.x) {
+        double sum = 0.0;
+#pragma unroll
+        for (int v = 0; v < kBallWaves; ++v) sum += part[v][t % kHalf * 64 + t / kHalf];
+        const int k = (p0 + t / kHalf) * kPer + h + t % kHalf;
+        const float c = k < d ? (float)(sum / (double)rows) : 0.0f;
+        if (k < d) cent[b * (int64_t)d + k] = c;
+        c_lds[k] = c;
+      }
+      __syncthreads();
     }
-    for (; r < rows; ++r) s += (double)op_elem<kPrec>(base + (int64_t)r * qld, k, scale_lds[r]);
-    const float c = k < d ? (float)(s / (double)rows) : 0.0f;
-    if (k < d) cent[b * (int64_t)d + k] = c;
-    c_lds[k] = c;
   }
-  __syncthreads();
   // |x~ - c| + rho per row: a wave takes four rows at a time (four loads in
   // flight per lane), 16-byte pieces across the lanes; rows past the block
   // repeat its last row
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int pieces = (int)(qld / 16);
   constexpr int kRows = 4;
   double rmax = 0.0;
-  for (int r = wave; r < rows; r += 4 * kRows) {
+  for (int r = wave; r < rows; r += kBallWaves * kRows) {
     int rq[kRows];
 #pragma unroll
-    for (int u = 0; u < kRows; ++u) rq[u] = min(r + 4 * u, rows - 1);
+    for (int u = 0; u < kRows; ++u) rq[u] = min(r + kBallWaves * u, rows - 1);
     double s[kRows] = {0.0, 0.0, 0.0, 0.0};
     for (int pc = lane; pc < pieces; pc += 64) {
       uint4 w[kRows];
@@ -221,9 +248,14 @@ __global__ __launch_bounds__(256) void block_ball_q_kernel(const uint8_t* __rest
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    const double m = fmax(fmax(r_wave[0], r_wave[1]), fmax(r_wave[2], r_wave[3]));
+    double m = r_wave[0];
+    float em = e_wave[0];
+    for (int v = 1; v < kBallWaves; ++v) {
+      m = fmax(m, r_wave[v]);
+      em = fmaxf(em, e_wave[v]);
+    }
     const double rr = m * (1.0 + 0x1p-30) + 0x1p-100;
-    const double eb = eps_row ? (double)fmaxf(fmaxf(e_wave[0], e_wave[1]), fmaxf(e_wave[2], e_wave[3])) : eps;
+    const double eb = eps_row ? (double)em : eps;
     const double e = eb + rr;
     Tb[b] = e * e * (1.0 + 0x1p-30);  // +inf when a row has no bound
   }
@@ -434,19 +466,19 @@ hipError_t launch_block_balls_q(const Prep& P, int64_t n, int d, dl_prec prec, d
   const uint8_t* q = static_cast<const uint8_t*>(P.q);
   switch (prec) {
     case DL_FP32:
-      hipLaunchKernelGGL(block_ball_q_kernel<DL_FP32>, dim3((unsigned)nb), dim3(256), lds, st, q, P.qld, P.sexp, P.rho,
+      hipLaunchKernelGGL(block_ball_q_kernel<DL_FP32>, dim3((unsigned)nb), dim3(64 * kBallWaves), lds, st, q, P.qld, P.sexp, P.rho,
                          n, d, eps, eps_row, cent, Tb);
       break;
     case DL_BF16:
-      hipLaunchKernelGGL(block_ball_q_kernel<DL_BF16>, dim3((unsigned)nb), dim3(256), lds, st, q, P.qld, P.sexp, P.rho,
+      hipLaunchKernelGGL(block_ball_q_kernel<DL_BF16>, dim3((unsigned)nb), dim3(64 * kBallWaves), lds, st, q, P.qld, P.sexp, P.rho,
                          n, d, eps, eps_row, cent, Tb);
       break;
     case DL_FP16:
-      hipLaunchKernelGGL(block_ball_q_kernel<DL_FP16>, dim3((unsigned)nb), dim3(256), lds, st, q, P.qld, P.sexp, P.rho,
+      hipLaunchKernelGGL(block_ball_q_kernel<DL_FP16>, dim3((unsigned)nb), dim3(64 * kBallWaves), lds, st, q, P.qld, P.sexp, P.rho,
                          n, d, eps, eps_row, cent, Tb);
       break;
     case DL_FP8:
-      hipLaunchKernelGGL(block_ball_q_kernel<DL_FP8>, dim3((unsigned)nb), dim3(256), lds, st, q, P.qld, P.sexp, P.rho,
+      hipLaunchKernelGGL(block_ball_q_kernel<DL_FP8>, dim3((unsigned)nb), dim3(64 * kBallWaves), lds, st, q, P.qld, P.sexp, P.rho,
                          n, d, eps, eps_row, cent, Tb);
       break;
   }
