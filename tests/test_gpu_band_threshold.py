@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("nr,ns,k", [(8192, 2100, 10), (8193, 2100, 10), (8300, 3000, 60), (1023, 40000, 1),
-                                     (1024, 40000, 1), (1100, 13000, 10), (600, 33000, 120), (2200, 5000, 300)])
+                                     (1024, 40000, 1), (1100, 13000, 10), (600, 33000, 120), (2200, 5000, 256)])
 def test_rows_and_strides(orc, nr, ns, k):
     from gpu_util import assert_topk_equal, dev
     from paper_1812_07607_amd import ops
