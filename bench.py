@@ -71,9 +71,10 @@ def parse():
     return ap.parse_args()
 
 
-KERNEL_SOURCES = ["paper_1812_07607_amd/csrc/join_mfma.hip", "paper_1812_07607_amd/csrc/join_params.hpp",
+KERNEL_SOURCES = ["paper_1812_07607_amd/csrc/join_mfma.hip", "paper_1812_07607_amd/csrc/stream.hip",
+                  "paper_1812_07607_amd/csrc/cand_device.hpp", "paper_1812_07607_amd/csrc/join_params.hpp",
                   "paper_1812_07607_amd/csrc/dl_internal.hpp"]
-TRAFFIC_SUMMARY = {"bf16": "profiles/cand_kernel_bf16_eps_1m_d128_traffic.txt",
+TRAFFIC_SUMMARY = {"bf16": "profiles/stream_kernel_bf16_eps_1m_d128_traffic.txt",
                    "fp16": "profiles/cand_kernel_fp16_selfjoin_100k_traffic.txt"}
 
 
@@ -766,7 +767,8 @@ def main():
     achieved = flops / (c_avg * 1e-3) / 1e12
     peak = PEAK_TFLOPS[args.prec]
     workload = "eps-join %d x %d, d=128, unit-norm 1000-centre mixture" % (n, n)
-    roof = {"kernel": "cand_kernel<%s, eps>" % args.prec, "bound": "mfma", "achieved": achieved, "peak": peak,
+    kernel = "cand_kernel" if args.prec == "fp32" else "stream_kernel"
+    roof = {"kernel": "%s<%s, eps>" % (kernel, args.prec), "bound": "mfma", "achieved": achieved, "peak": peak,
             "unit": "TFLOP/s", "frac": achieved / peak, "traffic": measured_traffic(args.prec, workload),
             "flops_per_launch": flops, "avg_launch_ms": c_avg}
     # the achievable rates of this device (register-operand matrix-core loop,
