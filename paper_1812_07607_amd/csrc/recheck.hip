@@ -160,11 +160,17 @@ __global__ __launch_bounds__(256) void recheck_eps_kernel(RecheckParams p) {
   __shared__ int s_in[4];
   const int wave = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63, sub = lane & (kRecheckLanes - 1);
-  // the candidates of the list's part `lane` (one part without seg)
+  // the candidates of the list's part `lane` (one part without seg: its counter
+  // shares a line with the output's, on which this kernel's atomics queue, so it
+  // is read once a wave through the scalar cache; by the lanes, 0.5M candidates
+  // take 170 us instead of 81)
   int64_t mine_n = 0;
-  if (lane < kSegments) {
-    const int64_t room = p.seg ? segment_end(p.ccap, lane) - segment_first(p.ccap, lane) : lane == 0 ? p.ccap : 0;
-    mine_n = min((int64_t)(p.seg ? p.seg[lane * kSegWords] : *p.ccount), room);
+  if (p.seg) {
+    if (lane < kSegments)
+      mine_n = min((int64_t)p.seg[lane * kSegWords], segment_end(p.ccap, lane) - segment_first(p.ccap, lane));
+  } else {
+    const int64_t all = min((int64_t)*p.ccount, p.ccap);
+    if (lane == 0) mine_n = all;
   }
   auto part = [&](int s) {  // of part s
     const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)mine_n, s);

@@ -133,8 +133,7 @@ enum : int { kStreamEps = 0, kStreamBand = 1, kStreamMax = 2 };
 // time, when the queue is full: the outputs against the row's threshold, the
 // columns against the end of S and the diagonal.  Against hits staged one by
 // one: 60,001 rows, d = 100, fp16, 0.58M candidates 463 -> 416 us of pass; top-10
-// of 200,000 x 200,000, about 970 entries a row, 9.4 -> 9.0 ms; of 37 x 4M 325 ->
-// 287 us; 20,000 x 1M, d = 256, E4M3 6.1 -> 5.6 ms; 195M candidates in E4M3 9.5
+// of 200,000 x 200,000 9.4 -> 9.0 ms of passes; of 37 x 4M 325 -> 287 us; 20,000 x 1M, d = 256, E4M3 6.1 -> 5.6 ms; 195M candidates in E4M3 9.5
 // -> 4.7 ms (half of that by the list's parts).
 // Bit r: output r of the record is a hit.
 template <int kMode>
@@ -810,7 +809,7 @@ static hipError_t launch_band_key(const uint32_t* gmax, int ng, int64_t nR, int 
 // c.gkey holds what bounds are known (order keys), c.bcount zeros.
 //
 // Measured (one MI355X): top-10 of 200,000 x 200,000, d = 128, bf16: sample
-// 1.7 ms, thresholds 0.05, pass 7.3, against 21.4 ms for the tile form, whose
+// 0.85 ms, thresholds 0.05, pass 7.9, against 21.4 ms for the tile form, whose
 // bands are tightened row by row inside the pass.
 hipError_t launch_stream_band(dl_prec prec, const CandParams& c, int64_t npad_r, int k, uint32_t* gmax, hipStream_t st,
                               int cu_count) {
