@@ -490,7 +490,7 @@ dl_status dl_pair_d2(dl_ctx* c, dl_mat R, dl_mat S, const uint32_t* pi, const ui
   DL_HIP(c, hipSetDevice(c->device));
   hipStream_t st = static_cast<hipStream_t>(stream);
   // out-of-range flag: a plain store into the context's pinned host block
-  volatile int* bad = reinterpret_cast<volatile int*>(c->pinned + 31);
+  volatile int* bad = reinterpret_cast<volatile int*>(c->pinned + kPinBox);
   *bad = 0;
   DL_HIP(c, launch_pair_d2(R.data, R.ld, R.n, S.data, S.ld, S.n, R.d, pi, pj, m, out, (int*)bad, st, c->cu_count));
   DL_HIP(c, hipStreamSynchronize(st));
