@@ -573,8 +573,10 @@ static hipError_t prep_relations(dl_ctx* c, const dl_mat& R, const Prep* PR, con
 
 // The end of an eps call: the state goes to the host while the pairs are put
 // in order (the device reads their number; the outputs hold `capacity`).  The
-// ordering of a call that keeps pairs may still run on return, as its outputs
-// belong to the stream; nothing is in flight otherwise.
+// ordering of a call that succeeds with pairs may still run on return, as its
+// outputs belong to the stream.  Any other call returns with nothing in flight:
+// after an error the caller retries with other buffers, or gives the workspace
+// away (the server hands a failed batch's blocks to another stream).
 static dl_status order_and_wait(dl_ctx* c, const EpsLayout& L, int64_t cap, int64_t nR, int bj, dl_pairs* out,
                                 hipStream_t st) {
   DL_HIP(c, publish(c, L.state, kStateWords, st));
@@ -585,7 +587,8 @@ static dl_status order_and_wait(dl_ctx* c, const EpsLayout& L, int64_t cap, int6
   }
   DL_HIP(c, hipEventSynchronize(c->ready));
   const CallState& h = published(c);
-  if (h.c.out == 0 || (int64_t)h.c.cand > cap || h.c.invalid) DL_HIP(c, hipStreamSynchronize(st));
+  if (h.c.out == 0 || (int64_t)h.c.out > out->capacity || (int64_t)h.c.cand > cap || h.c.invalid)
+    DL_HIP(c, hipStreamSynchronize(st));
   if (dl_status bad = check_inputs(c, &h.r, &h.s)) return bad;
   out->candidates = (int64_t)h.c.cand;
   out->ties = (int64_t)h.c.ties;
