@@ -144,9 +144,12 @@ struct StreamParams {
   int nst, nrb;          // stages of S, blocks of R
   int stages_per_block;  // self-join: block rb starts at stage rb * stages_per_block
   int wr;                // waves along R (8 / wr along S)
-  // max mode: every stride-th stage of S, in nslots runs (of slot_strips 32-row strips) whose largest P~ per
-  // row and lane quarter go to gmax[(4 slot + quarter) * nR + row] (order keys)
-  int stride, nslots, slot_strips;
+  // max mode: a sample of S in strips of four octets (8 rows each), nslots
+  // slots of slot_strips strips; the largest P~ per row, slot and lane quarter
+  // go to gmax[(4 slot + quarter) * nR + row] (order keys).  strips = nslots *
+  // slot_strips; step: octets of S per octet of the sample, in 2^-32.
+  int stride, nslots, slot_strips, strips;
+  uint64_t step;
   uint32_t* gmax;
 };
 

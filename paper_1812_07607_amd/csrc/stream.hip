@@ -119,6 +119,22 @@ __device__ inline UnitAt stream_unit(const StreamParams& p, int64_t L) {
   return {lo, stream_first(p, lo) + (int)(L - stream_prefix(p, lo))};
 }
 
+// Max mode: the first of the eight rows of S that octet o of the sample's strip
+// t holds.  Octets lie evenly over S.  Consecutive ones fall into different
+// slots (and the four of a strip into the four quarters of S), so that near rows
+// that lie together in S spread over many groups: with the groups runs of S
+// instead, a neighbourhood of consecutive rows fell into a few of them, and the
+// k-th largest group maximum lay outside it (300,000 rows in order of their 100
+// centres, top-10: 3,100 rows of S at or above a row's bound on average, against
+// 270; in random order 90 either way).  A strip past the sample repeats row 0
+// on (its outputs are dropped).
+__device__ inline uint32_t sample_row(const StreamParams& p, uint32_t t, uint32_t o) {
+  if (t >= (uint32_t)p.strips) return 0;
+  const uint32_t q = t / (uint32_t)p.slot_strips;
+  const uint32_t n = o * (uint32_t)p.strips + (t - q * (uint32_t)p.slot_strips) * (uint32_t)p.nslots + q;
+  return 8 * (n * (uint32_t)(p.step >> 32) + __umulhi(n, (uint32_t)p.step));
+}
+
 // kStreamEps: candidates (P~ >= thr_i) to the global list.  kStreamBand: top-k
 // band entries (P~ >= the row's threshold of p.gkey) to the row's buffer.
 // kStreamMax: per row and group of S rows the largest P~ (p.gmax), from which
@@ -281,9 +297,10 @@ __global__ __launch_bounds__(kThreads, 1) void stream_kernel(StreamParams p) {
   // piece of 16 rows touches all 64 banks.
   auto issue = [&]() {
     const int buf = lu & (kStreamStages - 1);
-    const int64_t j0 = (int64_t)lst * G::kStageRows * (kMax ? p.stride : 1);
+    const int64_t j0 = (int64_t)lst * G::kStageRows;
+    const uint32_t t0 = (uint32_t)lst * G::kStrips;  // first strip
     const int l = fresh_lane();
-    const uint8_t* src = p.c.qb + j0 * kKB;
+    const uint8_t* src = p.c.qb + (kMax ? 0 : j0 * kKB);
     const uint32_t dst = lds_addr(&ring[buf][0]) + wave * G::kDma * 1024;
 #pragma unroll
     for (int t = 0; t < G::kDma; ++t) {
@@ -291,11 +308,18 @@ __global__ __launch_bounds__(kThreads, 1) void stream_kernel(StreamParams p) {
       const int c = q / G::kRowGroups, r8 = q % G::kRowGroups;
       const int row = r8 * 8 + ((l >> 2) & 7);
       const int piece = 4 * (l >> 5) + ((l ^ (row >> 2)) & 3);
-      lds_dma16_at(src + (uint32_t)(row * kKB + c * 128 + piece * 16), dst + t * 1024);
+      if constexpr (kMax)
+        lds_dma16_at(src + (int64_t)sample_row(p, t0 + (r8 >> 2), r8 & 3) * kKB +
+                         (uint32_t)((row & 7) * kKB + c * 128 + piece * 16),
+                     dst + t * 1024);
+      else
+        lds_dma16_at(src + (uint32_t)(row * kKB + c * 128 + piece * 16), dst + t * 1024);
     }
-    if (wave == 7 && l < G::kStageRows / 4) lds_dma16(p.c.hb + j0 + 4 * l, side_h[buf]);
+    // four rows' values per lane
+    const int64_t j4 = kMax ? (int64_t)sample_row(p, t0 + (l >> 3), (l >> 1) & 3) + 4 * (l & 1) : j0 + 4 * l;
+    if (wave == 7 && l < G::kStageRows / 4) lds_dma16(p.c.hb + j4, side_h[buf]);
     if constexpr (kFp8)
-      if (wave == 6 && l < G::kStageRows / 4) lds_dma16(p.c.sexb + j0 + 4 * l, side_s[buf]);
+      if (wave == 6 && l < G::kStageRows / 4) lds_dma16(p.c.sexb + j4, side_s[buf]);
     ++lu;
     if (++lst == p.nst) {
       ++lrb;
@@ -318,8 +342,7 @@ __global__ __launch_bounds__(kThreads, 1) void stream_kernel(StreamParams p) {
   int nq = 0;
   // row numbers fit 32 bits (relations are shorter than 2^31 rows)
   uint32_t row0 = 0;  // first R row of this wave
-  uint32_t pj = 0;    // first S row of the strip whose outputs await their test
-  const uint32_t ns = (uint32_t)p.c.nS;
+  uint32_t pj = 0;    // first S row of the strip whose outputs await their test (max mode: the strip)
   int64_t hits = 0;  // flushed so far (eps)
   auto flush = [&]() {
     if constexpr (kMode == kStreamEps)
@@ -437,21 +460,12 @@ __global__ __launch_bounds__(kThreads, 1) void stream_kernel(StreamParams p) {
       }
     }
   };
-  // Max mode: the strip's outputs into the running minima (columns past S
-  // left out; the row itself, in a self-join, is not: the caller takes the
-  // (k + 1)-th largest).
+  // Max mode: the strip's outputs into the running minima (all of its rows are
+  // rows of S; the row itself, in a self-join, is not left out: the caller takes
+  // the (k + 1)-th largest).
   bool fresh_acc = false;  // the accumulators hold a strip's outputs
   auto fold = [&]() {
-    if (!fresh_acc) return;
-    if (pj + 32 > ns) {
-      const uint32_t j = pj + 4 * (fresh_lane() >> 4);
-#pragma unroll
-      for (int b = 0; b < kNB; ++b)
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          nthr[b] = fminf(nthr[b], j + 16 * (e >> 2) + (e & 3) < ns ? acc[b][e >> 2][e & 3] : INFINITY);
-      return;
-    }
+    if (!fresh_acc || pj >= (uint32_t)p.strips) return;
 #pragma unroll
     for (int b = 0; b < kNB; ++b) {
       const f32x4 &v = acc[b][0], &w = acc[b][1];
@@ -460,6 +474,7 @@ __global__ __launch_bounds__(kThreads, 1) void stream_kernel(StreamParams p) {
   };
   // the running minima to group `slot` (of every lane quarter), and restart
   auto put_max = [&](uint32_t slot) {
+    if (slot >= (uint32_t)p.nslots) return;  // strips past the sample
     const int l = fresh_lane();
     uint32_t* const g = p.gmax + (int64_t)slot * 4 * p.c.nR;
 #pragma unroll
@@ -605,7 +620,7 @@ __global__ __launch_bounds__(kThreads, 1) void stream_kernel(StreamParams p) {
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    pj = (uint32_t)st * (G::kStageRows * (kMax ? p.stride : 1)) + strip * 32;
+    pj = kMax ? (uint32_t)(st * G::kStrips + strip) : (uint32_t)st * G::kStageRows + strip * 32;
     if (++t == per) {
       t = 0;
       ++u;
@@ -687,11 +702,8 @@ template <int kPrec, int kKB, int kMode>
 static hipError_t launch_stream_kb(StreamParams p, int64_t npad_r, hipStream_t st, int cu_count) {
   using G = StreamGeom<kPrec, kKB>;
   p.npad_r = npad_r;
-  p.nst = (int)((p.c.nS + G::kStageRows - 1) / G::kStageRows);
-  if (kMode == kStreamMax) {
-    p.nst = (p.nst + p.stride - 1) / p.stride;
-    p.slot_strips = (p.nst * G::kStrips + p.nslots - 1) / p.nslots;
-  }
+  p.nst = kMode == kStreamMax ? (p.strips + G::kStrips - 1) / G::kStrips
+                              : (int)((p.c.nS + G::kStageRows - 1) / G::kStageRows);
   // waves along R: as many as R fills, fewer while there are fewer than four
   // units per workgroup (a stage has to hold a strip for every wave along S,
   // and a self-join's block at least a stage)
@@ -746,8 +758,8 @@ hipError_t launch_stream_eps(dl_prec prec, const CandParams& c, int64_t npad_r, 
 }
 
 // Groups of S rows whose maxima bound a row's k-th largest P~: a few times k,
-// so that the k largest rarely share one (ngroups / 4 runs of S rows, each
-// split over the four lane quarters).
+// so that the k largest rarely share one (ngroups / 4 slots of sampled strips,
+// each split over the four lane quarters).
 int stream_groups(int k) {
   const int g = (4 * k + 63) / 64 * 64;
   return g < 64 ? 64 : g;
@@ -758,18 +770,17 @@ int stream_groups(int k) {
 constexpr int64_t kAllRows = 512;
 bool stream_band_applies(int64_t nS, int k) { return nS >= 16 * (int64_t)k || nS <= kAllRows; }
 
-// Every how many stages of S the sample takes one.  The sample costs 1 / stride
+// One row in how many of S the sample takes.  The sample costs 1 / stride
 // of a pass and leaves about stride times the rows of the band itself to be
 // staged and selected from.  Few rows wait for what they stage: the sum is
 // smallest where stride^2 is nS / 100 (k + 90) or so (37 x 4M, top-10: 20, 285
 // us of passes; 36, 299).  Many hide it behind the matrix cores: nS / (240 k +
 // 600) (200,000 x 200,000, top-10, passes: stride 4 9.08 ms, 5 8.87, 6 8.80, 8
-// 8.69; 178,455 x 247,864, top-50: 4 11.7, 5 11.8, 6 12.0), but at most 8: the
-// neighbours of a row may lie together in S, and a sample that misses them
-// bounds the row loosely.  E4M3 takes at most 8 anyway: its margin is as wide as
-// the spread of near rows, so its bands grow faster as the threshold loosens and
-// a buffer may not hold them (50,000 queries x 4M rows, d = 256, top-32: stride
-// 18 overflows buffers, 9 takes 64 ms of call time, 4 takes 70).
+// 8.69; 178,455 x 247,864, top-50: 4 11.7, 5 11.8, 6 12.0), up to 8, or what few
+// rows would take where that is more.  E4M3 takes at most 8: its margin is as
+// wide as the spread of near rows, so its bands grow faster as the threshold
+// loosens (50,000 queries x 4M rows, d = 256, top-32: stride 9 takes 64 ms of
+// call time, 4 takes 70, 18 overflows buffers).
 static int sample_stride(dl_prec prec, int64_t nR, int64_t nS, int k) {
   int few = 1, many = 1;
   while ((int64_t)(few + 1) * (few + 1) * 100 * (k + 90) <= nS) ++few;
@@ -803,9 +814,26 @@ static hipError_t launch_band_key(const uint32_t* gmax, int ng, int64_t nR, int 
   return launch_band_key_of<kKeys>(per, gmax, ng, nR, k, marg, gkey, st);
 }
 
-// Top-k band of every row of R: the group maxima of a sample of S (every
-// stride-th stage) give each row's threshold, then the pass over all of S
-// stages what reaches it.  gmax: scratch of stream_groups(k) * nR words.
+// The sample: as many strips as S has octets for at this stride, cut to whole
+// slots (of at most nslots, the number that drops the fewest strips; S of 16 k
+// rows and more leaves at least 2 k groups), its octets spread over all of S.
+static void plan_sample(StreamParams& p, int64_t nS, int ngroups) {
+  const int64_t octets = nS / 8, strips = (octets + p.stride - 1) / p.stride / 4;
+  int best = 1;
+  int64_t left = strips;
+  for (int n = ngroups / 4 < strips ? ngroups / 4 : (int)strips; 8 * n >= ngroups || (n > 0 && n == strips); --n)
+    if (strips % n < left) {
+      best = n;
+      left = strips % n;
+    }
+  p.nslots = best;
+  p.slot_strips = (int)(strips / best);
+  p.strips = p.nslots * p.slot_strips;
+  p.step = p.strips ? ((uint64_t)octets << 32) / (4 * (uint64_t)p.strips) : 0;
+}
+
+// Top-k band of every row of R: the group maxima of a sample of S give each
+// row's threshold, then the pass over all of S stages what reaches it.  gmax: scratch of stream_groups(k) * nR words.
 // c.gkey holds what bounds are known (order keys), c.bcount zeros.
 //
 // Measured (one MI355X): top-10 of 200,000 x 200,000, d = 128, bf16: sample
@@ -819,9 +847,9 @@ hipError_t launch_stream_band(dl_prec prec, const CandParams& c, int64_t npad_r,
   if (c.nR == 0 || c.nS == 0) return hipSuccess;
   hipError_t e;
   if (c.nS > kAllRows) {
-    const int ng = stream_groups(k);
     p.stride = sample_stride(prec, c.nR, c.nS, k);
-    p.nslots = ng / 4;
+    plan_sample(p, c.nS, stream_groups(k));
+    const int ng = 4 * p.nslots;
     p.gmax = gmax;
     hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)(cu_count * 4)), dim3(256), 0, st, gmax, ng * c.nR);
     if ((e = launch_stream<kStreamMax>(prec, p, npad_r, st, cu_count)) != hipSuccess) return e;
