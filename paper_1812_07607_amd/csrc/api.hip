@@ -1,5 +1,6 @@
 // api.hip -- the C ABI of libdlmi.so: validation, workspace layout, launch
 // sequencing and status codes.  Kernels live in the other sources.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -38,7 +39,8 @@ hipError_t launch_cand_list(dl_prec, CandParams, hipStream_t, int);
 bool stream_applies(dl_prec, int64_t, int64_t, int64_t);
 hipError_t launch_stream_eps(dl_prec, const CandParams&, int64_t, hipStream_t, int);
 bool stream_band_applies(int64_t, int);
-hipError_t launch_stream_band(dl_prec, const CandParams&, int64_t, int, uint32_t*, hipStream_t, int);
+int64_t stream_band_room(dl_prec, int64_t, int64_t, int);
+hipError_t launch_stream_band(dl_prec, const CandParams&, int64_t, int, int64_t, uint32_t*, hipStream_t, int);
 hipError_t launch_cand_mark(dl_prec, CandParams, hipStream_t, int);
 hipError_t launch_cand_nearest(dl_prec, CandParams, hipStream_t, int);
 // index.hip
@@ -535,6 +537,10 @@ size_t eps_workspace(int64_t nR, int64_t nS, int d, dl_prec prec, bool self, boo
   return layout_eps(nullptr, nR, nS, d, prec, self, cap, s_ext, r_ext).bytes;
 }
 
+// Rows of R in a block of the streaming top-k are a multiple of this many (the
+// rows its waves hold at a time).
+constexpr int64_t kBandBlock = 1024;
+
 // E4M3 top-k pilot.  The E4M3 margin E_i (about 0.1 on unit vectors) is
 // wide next to the spread of unrelated rows' P, so a band seeded at -inf
 // keeps most of them until the row has met k close neighbours, and can
@@ -729,10 +735,27 @@ dl_status topk_core(dl_ctx* c, const TopkJob& J, void* ws, size_t ws_bytes, uint
   if (R.n == 0) return DL_OK;
   // The streaming pass (stream.hip) sets each row's threshold from a sample of
   // S and fills one buffer per row, the memory of its P split buffers; should
-  // a row's buffer overflow (the sample missed a dense neighbourhood), the
-  // tile form, which tightens as it goes, runs after it.
+  // a row's buffer overflow (more rows of S about its k-th neighbour than any
+  // sample tells), the tile form, which tightens as it goes, runs after it.
+  // Where P buffers are too few for what the sample leaves (P is 1 for about a
+  // sixth of the row counts up to 200,000), R goes in blocks, each with the
+  // whole band memory: a block costs its launches and a wait (about 50 us), an
+  // overflow a pass.  Top-10 of 65,536 rows against 8M, d = 128, bf16 (the
+  // fullest of 1,024 rows had 1,270 entries, the buffer 1,024): 223 ms with the
+  // tile form after the pass, 93 in three blocks.
+  const int kk = k + (excl ? 1 : 0);
+  const int64_t row_cap = (int64_t)P * band_cap;
   bool stream = !J.surv && !J.seed && S.n > 0 && stream_applies(prec, dpad_of(R.d, prec) * elem_bytes(prec), R.n, S.n) &&
-                stream_band_applies(S.n, k + (excl ? 1 : 0)) && (int64_t)P * band_cap < (1 << 30);
+                stream_band_applies(S.n, kk) && row_cap < (1 << 30);
+  int64_t block = R.n;  // rows of R at a time
+  if (stream) {
+    const int64_t room = stream_band_room(prec, R.n, S.n, kk);
+    if (room > row_cap) {  // blocks of equal size
+      block = std::max(kBandBlock, R.n * row_cap / room / kBandBlock * kBandBlock);
+      const int64_t blocks = (R.n + block - 1) / block;
+      block = round_up((R.n + blocks - 1) / blocks, kBandBlock);
+    }
+  }
   // the pilot (see pilot_of), in its own part of the workspace
   const float* pilot_dist = nullptr;
   auto run_pilot = [&]() -> dl_status {
@@ -782,7 +805,6 @@ dl_status topk_core(dl_ctx* c, const TopkJob& J, void* ws, size_t ws_bytes, uint
     if (pilot_dist) DL_HIP(c, launch_band_seed(L.pr, R.n, pilot_dist, k, L.marg, L.gkey, st));
     if (J.seed) DL_HIP(c, launch_band_seed(L.pr, R.n, J.seed, 1, L.marg, L.gkey, st));
   }
-  SelectParams q{};
   const bool small_sel = topk_select_small(k);
   Counters hc;
   auto wait = [&]() -> dl_status {
@@ -799,36 +821,38 @@ dl_status topk_core(dl_ctx* c, const TopkJob& J, void* ws, size_t ws_bytes, uint
                                  reinterpret_cast<uint32_t*>(L.rstate), rows ? R.n : 0, st, c->cu_count));
     return DL_OK;
   };
-  for (;;) {
+  // The band and the selection of rows r0 to r0 + n - 1 of R; hc holds the
+  // counts on return.
+  auto run_rows = [&](int64_t r0, int64_t n) -> dl_status {
+    const int64_t cap = stream ? std::min(R.n * row_cap / n, (int64_t)1 << 30) : band_cap;
     if (S.n > 0) {
       StageTimer t(c, 2, st);
       CandParams p{};
-      p.qa = static_cast<const uint8_t*>(L.pr.q);
+      p.qa = static_cast<const uint8_t*>(L.pr.q) + r0 * L.pr.qld;
       p.qb = static_cast<const uint8_t*>(L.ps.q);
       p.qld = L.pr.qld;
       p.nchunks = (int)(L.pr.qld / kChunkBytes);
       p.hb = L.ps.h;
-      p.sexa = L.pr.sexp;
+      p.sexa = L.pr.sexp + r0;
       p.sexb = L.ps.sexp;
-      p.nR = R.n;
+      p.nR = n;
       p.nS = S.n;
       p.self_join = self;
       p.exclude_self = excl;
-      p.marg = L.marg;
-      p.gkey = L.gkey;
+      p.marg = L.marg + r0;
+      p.gkey = L.gkey + r0;
       p.band = L.band;
-      p.bcount = L.bcount;
+      p.bcount = L.bcount + r0;  // (r0 is 0 where a row has more than one)
       p.overflow = &L.cnt->overflow;
       p.gate = &L.cnt->invalid;
+      p.cap = (int)cap;
       if (stream) {
-        p.cap = P * band_cap;
         // (the group maxima lie in the band's memory, which is written later)
-        DL_HIP(c, launch_stream_band(prec, p, L.pr.npad, k + (excl ? 1 : 0), reinterpret_cast<uint32_t*>(L.band), st,
+        DL_HIP(c, launch_stream_band(prec, p, L.pr.npad - r0, kk, r0, reinterpret_cast<uint32_t*>(L.band), st,
                                      c->cu_count));
       } else {
         p.P = P;
         p.k = k;
-        p.cap = band_cap;
         p.limit = band_limit_of(band_cap, k, tps);
         p.batch = band_defers(band_cap, k, tps) ? 8 : 1;  // one row per wave of the workgroup
         p.retight = retight_of(k, p.limit);
@@ -841,63 +865,76 @@ dl_status topk_core(dl_ctx* c, const TopkJob& J, void* ws, size_t ws_bytes, uint
         DL_HIP(c, launch_cand_band(prec, p, st));
       }
     }
-    {
-      StageTimer t(c, 5, st);
-      q.R = R.data; q.ldr = R.ld;
-      q.S = S.data; q.lds = S.ld;
-      q.d = R.d; q.nR = R.n;
-      q.band = L.band; q.bcount = L.bcount; q.k = k;
-      q.P = stream ? 1 : P;
-      q.cap = stream ? P * band_cap : band_cap;
-      q.marg = L.marg;
-      q.nrm2R = L.pr.nrm2;
-      q.xnR = L.pr.xnorm; q.mlR = L.pr.mlsb;
-      q.sS = L.ss;
-      q.out_j = out_j; q.out_dist = out_dist;
-      q.counts = L.state->sel; q.too_many = &L.cnt->too_many;
-      q.gate = &L.cnt->invalid;
-      q.rstate = L.rstate;
-      q.wide = L.wide;
-      DL_HIP(c, launch_topk_select(q, small_sel, prec == DL_FP8, st));
+    SelectParams q{};
+    q.R = R.data + r0 * R.ld; q.ldr = R.ld;
+    q.S = S.data; q.lds = S.ld;
+    q.d = R.d; q.nR = n;
+    q.band = L.band; q.bcount = L.bcount + r0; q.k = k;
+    q.P = stream ? 1 : P;
+    q.cap = (int)cap;
+    q.marg = L.marg + r0;
+    q.nrm2R = L.pr.nrm2 + r0;
+    q.xnR = L.pr.xnorm + r0; q.mlR = L.pr.mlsb + r0;
+    q.sS = L.ss;
+    q.out_j = out_j + r0 * k; q.out_dist = out_dist + r0 * k;
+    q.counts = L.state->sel; q.too_many = &L.cnt->too_many;
+    q.gate = &L.cnt->invalid;
+    q.rstate = L.rstate + r0;
+    q.wide = L.wide + r0;
+    auto select = [&](bool small) -> dl_status {
+      {
+        StageTimer t(c, 5, st);
+        DL_HIP(c, launch_topk_select(q, small, prec == DL_FP8, st));
+      }
+      return wait();
+    };
+    if (const dl_status s = select(small_sel)) return s;
+    if (small_sel && hc.too_many && !hc.overflow) {
+      // a row had more near-tie contenders than the small selection holds:
+      // select again (the bands are unchanged) with the large one
+      if (const dl_status s = restart(false)) return s;
+      if (const dl_status s = select(false)) return s;
     }
-    if (const dl_status s = wait()) return s;
-    if (!(stream && hc.overflow)) break;
-    // the tile form from the thresholds found (the gate stays as it is)
-    stream = false;
-    restarted = true;
-    if (pilot) {
-      if (const dl_status ps = run_pilot()) return ps;
-      if (pilot_dist) DL_HIP(c, launch_band_seed(L.pr, R.n, pilot_dist, k, L.marg, L.gkey, st));
+    if (hc.too_many && !hc.overflow) {
+      // rows with more near-tie contenders than the selection holds: the wide
+      // selection works on their band buffers in memory (the others are done)
+      hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t*>(&L.cnt->too_many),
+                         (int64_t)1);
+      {
+        StageTimer t(c, 5, st);
+        DL_HIP(c, launch_topk_select_wide(q, st));
+      }
+      if (const dl_status s = wait()) return s;
     }
-    if (const dl_status s = restart(true)) return s;
-  }
-  if (small_sel && hc.too_many && !hc.overflow) {
-    // a row had more near-tie contenders than the small selection holds:
-    // select again (the bands are unchanged) with the large one
-    if (const dl_status s = restart(false)) return s;
-    {
-      StageTimer t(c, 5, st);
-      DL_HIP(c, launch_topk_select(q, false, prec == DL_FP8, st));
+    return DL_OK;
+  };
+  int64_t band_entries = 0, ties = 0;
+  for (int64_t r0 = 0; r0 < R.n;) {
+    const int64_t n = stream ? std::min(block, R.n - r0) : R.n;
+    if (const dl_status s = run_rows(r0, n)) return s;
+    if (stream && hc.overflow) {
+      // the tile form for all rows, from the thresholds found (the gate stays as it is)
+      stream = false;
+      restarted = true;
+      if (pilot) {
+        if (const dl_status ps = run_pilot()) return ps;
+        if (pilot_dist) DL_HIP(c, launch_band_seed(L.pr, R.n, pilot_dist, k, L.marg, L.gkey, st));
+      }
+      if (const dl_status s = restart(true)) return s;
+      r0 = band_entries = ties = 0;
+      continue;
     }
-    if (const dl_status s = wait()) return s;
-  }
-  if (hc.too_many && !hc.overflow) {
-    // rows with more near-tie contenders than the selection holds: the wide
-    // selection works on their band buffers in memory (the others are done)
-    hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t*>(&L.cnt->too_many),
-                       (int64_t)1);
-    {
-      StageTimer t(c, 5, st);
-      DL_HIP(c, launch_topk_select_wide(q, st));
+    for (const SelectCount& n_of : published(c).sel) {
+      band_entries += (int64_t)n_of.band;
+      ties += (int64_t)n_of.ties;
     }
-    if (const dl_status s = wait()) return s;
+    r0 += n;
+    if (r0 < R.n)
+      if (const dl_status s = restart(false)) return s;
   }
   if (info) {
-    const SelectCount* n = published(c).sel;
-    for (int t = 0; t < kSelectCounts; ++t) {
-      info->band_entries += (int64_t)n[t].band;
-      info->ties += (int64_t)n[t].ties;
-    }
+    info->band_entries = band_entries;
+    info->ties = ties;
   }
   if (dl_status bad = check_inputs(c, &published(c).r, &published(c).s)) return bad;
   if (hc.overflow || hc.too_many) {

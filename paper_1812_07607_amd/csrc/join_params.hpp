@@ -144,6 +144,7 @@ struct StreamParams {
   int nst, nrb;          // stages of S, blocks of R
   int stages_per_block;  // self-join: block rb starts at stage rb * stages_per_block
   int wr;                // waves along R (8 / wr along S)
+  uint32_t first_row;    // R's number of the first row (band mode)
   // max mode: a sample of S in strips of four octets (8 rows each), nslots
   // slots of slot_strips strips; the largest P~ per row, slot and lane quarter
   // go to gmax[(4 slot + quarter) * nR + row] (order keys).  strips = nslots *

@@ -159,7 +159,7 @@ __device__ inline uint32_t record_hits(const StreamParams& p, const f32x4& v, co
   for (int r = 0; r < 4; ++r) {
     const uint32_t j = ij.y + r;
     const bool in = v[r] <= nthr && j < (uint32_t)p.c.nS &&
-                    (kMode == kStreamEps ? !p.c.self_join || j > ij.x : !p.c.exclude_self || j != ij.x);
+                    (kMode == kStreamEps ? !p.c.self_join || j > ij.x : !p.c.exclude_self || j != ij.x + p.first_row);
     hits |= in ? 1u << r : 0u;
   }
   return hits;
@@ -789,6 +789,20 @@ static int sample_stride(dl_prec prec, int64_t nR, int64_t nS, int k) {
   return prec == DL_FP8 && s > 8 ? 8 : s;
 }
 
+// Room for a row's entries: with less the rows of R are to go in blocks.  The
+// k-th largest of the group maxima is about the 1.15 k stride-th largest P~, up
+// to twice that for the worst of many rows, and the margin lets a few times as
+// many in where the rows of S are dense about the k-th; of rows that lie
+// together in S near ones share groups, so that up to 4 k stride of them can be
+// above the bound.  The fullest of 1,024 rows, random mixtures (d = 128, bf16):
+// k = 10, stride 8: 255 entries; 50, 4: 550; 100, 3: 507; 256, 2: 845; 10, 28
+// (8M rows): 1,272; S in order of its centres: 10, 8: 587; 50, 4: 1,059; 256, 2:
+// 2,105.  E4M3's margin holds 980 of its own at d = 256, k = 32.
+int64_t stream_band_room(dl_prec prec, int64_t nR, int64_t nS, int k) {
+  const int64_t room = 6 * (int64_t)k * sample_stride(prec, nR, nS, k) + (prec == DL_FP8 ? 4096 : 512);
+  return room < nS ? room : nS;
+}
+
 template <int kKeysOf>
 static hipError_t launch_band_key_of(int per, const uint32_t* gmax, int ng, int64_t nR, int k, const float* marg,
                                      uint32_t* gkey, hipStream_t st) {
@@ -833,17 +847,19 @@ static void plan_sample(StreamParams& p, int64_t nS, int ngroups) {
 }
 
 // Top-k band of every row of R: the group maxima of a sample of S give each
-// row's threshold, then the pass over all of S stages what reaches it.  gmax: scratch of stream_groups(k) * nR words.
-// c.gkey holds what bounds are known (order keys), c.bcount zeros.
+// row's threshold, then the pass over all of S stages what reaches it.  gmax:
+// scratch of stream_groups(k) * nR words.  c.gkey holds what bounds are known
+// (order keys), c.bcount zeros; c's row 0 is R's row first_row.
 //
 // Measured (one MI355X): top-10 of 200,000 x 200,000, d = 128, bf16: sample
 // 0.85 ms, thresholds 0.05, pass 7.9, against 21.4 ms for the tile form, whose
 // bands are tightened row by row inside the pass.
-hipError_t launch_stream_band(dl_prec prec, const CandParams& c, int64_t npad_r, int k, uint32_t* gmax, hipStream_t st,
-                              int cu_count) {
+hipError_t launch_stream_band(dl_prec prec, const CandParams& c, int64_t npad_r, int k, int64_t first_row,
+                              uint32_t* gmax, hipStream_t st, int cu_count) {
   StreamParams p{};
   p.c = c;
   p.c.self_join = 0;
+  p.first_row = (uint32_t)first_row;
   if (c.nR == 0 || c.nS == 0) return hipSuccess;
   hipError_t e;
   if (c.nS > kAllRows) {
