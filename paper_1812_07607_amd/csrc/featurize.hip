@@ -4,10 +4,10 @@
 // image matching); the patches are crops of frames given by bounding boxes
 // (section "Iterator API for Patches": a patch refers to a region of an
 // image), either already cut out (n patches of h x w pixels) or as boxes over
-// full frames.  One wavefront builds the histogram of one aligned patch in a
+// full frames.  One wavefront builds the histogram of one patch in a
 // wave-private LDS array, so the waves of a workgroup never wait for one
-// another (wave-level LDS ordering only); a box over a frame, or a patch no
-// 16-byte load fits, takes a workgroup of two or four waves.  The only global
+// another (wave-level LDS ordering only); boxes that are few, and large patches
+// no 16-byte load fits, take a workgroup of two or four waves.  The only global
 // traffic is one read of the pixels and one coalesced write of the normalised
 // bins.  HBM-bound: algorithmic bytes per patch are h*w*3 read plus bins^3*4
 // written.
@@ -72,7 +72,10 @@ __device__ inline void count_runs(uint32_t* __restrict__ hist, const uint8_t* __
   const int width = 8 - shift;
   auto field = [&](uint32_t w, int off) { return __builtin_amdgcn_ubfe(w, off + shift, width); };
   auto bin_of = [&](uint32_t r, uint32_t g, uint32_t b) { return __umul24(__umul24(r, bins) + g, bins) + b; };
-  const int per = cw < 4 ? cw : (cw + 3) / 4;  // pixels (narrow runs) or groups of a run
+  // pixels of a run (narrow ones, and all of them at most one per thread), or
+  // groups of four
+  const bool single = cw < 4 || cw * rows <= kThreads;
+  const int per = single ? cw : (cw + 3) / 4;
   const int units = per * rows;
   // run of a unit by a float reciprocal, then one correction step each way
   // (units < 2^24, so the estimate is off by at most one)
@@ -89,7 +92,7 @@ __device__ inline void count_runs(uint32_t* __restrict__ hist, const uint8_t* __
     }
     return base + y * pitch;
   };
-  if (cw < 4) {
+  if (single) {
     for (int q = t; q < units; q += kThreads) {
       int x;
       const uint8_t* px = run_of(q, x) + 3 * x;
@@ -147,42 +150,52 @@ struct PixelSource {
   int* bad_box;            // crops: set when a box is not inside its frame
 };
 
-// Counts the pixels of patch p into the bins by kThreads threads (`lane` of
-// them); returns the pixel count (0 for an invalid box, which contributes
-// nothing).
-template <int kSrc, int kThreads = 64>
-__device__ inline int count_patch(const PixelSource& src, int64_t p, uint32_t* __restrict__ hist, int shift,
-                                  int bins, int lane) {
+// The pixels of a box or of a contiguous patch: `rows` runs of cw pixels (none
+// for a box that is not inside its frame).
+struct Runs {
+  const uint8_t* base;
+  int64_t pitch;
+  int cw, rows;
+  bool bad;
+};
+template <int kSrc>
+__device__ inline Runs runs_of(const PixelSource& src, int64_t p) {
   if constexpr (kSrc == kSrcCrop) {
     const dl_box bx = src.boxes[p];
-    const bool ok = bx.frame >= 0 && bx.frame < src.nframes && bx.x0 >= 0 && bx.x0 < bx.x1 && bx.x1 <= src.w &&
-                    bx.y0 >= 0 && bx.y0 < bx.y1 && bx.y1 <= src.h;
-    if (!ok) {
-      if (lane == 0) atomicOr(src.bad_box, 1);
-      return 0;
-    }
-    const int cw = bx.x1 - bx.x0, area = cw * (bx.y1 - bx.y0);
-    const uint8_t* base = src.pix + (((int64_t)bx.frame * src.h + bx.y0) * src.w + bx.x0) * 3;
-    count_runs<kThreads>(hist, base, (int64_t)src.w * 3, cw, bx.y1 - bx.y0, shift, bins, lane);
-    return area;
+    if (bx.frame >= 0 && bx.frame < src.nframes && bx.x0 >= 0 && bx.x0 < bx.x1 && bx.x1 <= src.w && bx.y0 >= 0 &&
+        bx.y0 < bx.y1 && bx.y1 <= src.h)
+      return {src.pix + (((int64_t)bx.frame * src.h + bx.y0) * src.w + bx.x0) * 3, (int64_t)src.w * 3, bx.x1 - bx.x0,
+              bx.y1 - bx.y0, false};
+    return {nullptr, 0, 0, 0, true};
   } else {
     const int npx = src.h * src.w;
-    const uint8_t* s = src.pix + p * (int64_t)npx * 3;
-    if constexpr (kSrc == kSrcPatch48) {
-      typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-      const u32x4* v = reinterpret_cast<const u32x4*>(s);
-      const int groups = npx / 16;  // 16 pixels = 48 bytes = 3 x 16 bytes
-      for (int c = lane; c < groups; c += 64) {
-        const u32x4 x0 = __builtin_nontemporal_load(v + 3 * c + 0);
-        const u32x4 x1 = __builtin_nontemporal_load(v + 3 * c + 1);
-        const u32x4 x2 = __builtin_nontemporal_load(v + 3 * c + 2);
-        uint32_t w[12] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w, x2.x, x2.y, x2.z, x2.w};
-        count16(hist, w, shift, bins);
-      }
-    } else {
-      count_runs<kThreads>(hist, s, 0, npx, 1, shift, bins, lane);
+    return {src.pix + p * (int64_t)npx * 3, 0, npx, 1, false};
+  }
+}
+
+// Counts the pixels of patch p into the wave's bins; returns the pixel count
+// (0 for an invalid box, which contributes nothing).
+template <int kSrc>
+__device__ inline int count_patch(const PixelSource& src, int64_t p, uint32_t* __restrict__ hist, int shift,
+                                  int bins, int lane) {
+  if constexpr (kSrc == kSrcPatch48) {
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    const int npx = src.h * src.w;
+    const u32x4* v = reinterpret_cast<const u32x4*>(src.pix + p * (int64_t)npx * 3);
+    const int groups = npx / 16;  // 16 pixels = 48 bytes = 3 x 16 bytes
+    for (int c = lane; c < groups; c += 64) {
+      const u32x4 x0 = __builtin_nontemporal_load(v + 3 * c + 0);
+      const u32x4 x1 = __builtin_nontemporal_load(v + 3 * c + 1);
+      const u32x4 x2 = __builtin_nontemporal_load(v + 3 * c + 2);
+      uint32_t w[12] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w, x2.x, x2.y, x2.z, x2.w};
+      count16(hist, w, shift, bins);
     }
     return npx;
+  } else {
+    const Runs r = runs_of<kSrc>(src, p);
+    if (r.bad && lane == 0) atomicOr(src.bad_box, 1);
+    if (r.rows) count_runs<64>(hist, r.base, r.pitch, r.cw, r.rows, shift, bins, lane);
+    return r.cw * r.rows;
   }
 }
 
@@ -192,10 +205,14 @@ static int bin_shift(int bins) {
   return shift;
 }
 
-// Histograms only: bin / pixel count, rounded once (IEEE division).  Aligned
-// patches: a wave each.
-__global__ __launch_bounds__(64 * kHistWaves) void hist_patch48_kernel(PixelSource src, int64_t n, int32_t bins,
-                                                                    int32_t shift, float* __restrict__ out) {
+// Histograms only: bin / pixel count, rounded once (IEEE division).  A wave per
+// patch: aligned patches, others of at most kWaveArea pixels (a workgroup of two
+// waves each: 200,000 of 5 x 7, 8 / 4 bins, 141 / 78 us against 93 / 27; 60,000 of 31
+// x 33 80 against 72), and boxes that are many.
+constexpr int kWaveArea = 1024;
+template <int kSrc>
+__global__ __launch_bounds__(64 * kHistWaves) void hist_patch_kernel(PixelSource src, int64_t n, int32_t bins,
+                                                                   int32_t shift, float* __restrict__ out) {
   extern __shared__ uint32_t lds_hist[];
   const int nb = bins * bins * bins;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -206,7 +223,7 @@ __global__ __launch_bounds__(64 * kHistWaves) void hist_patch48_kernel(PixelSour
     if (p >= n) break;
     for (int b = lane; b < nb; b += 64) hist[b] = 0u;
     wave_lds_fence();
-    const int npx = count_patch<kSrcPatch48>(src, p, hist, shift, bins, lane);
+    const int npx = count_patch<kSrc>(src, p, hist, shift, bins, lane);
     wave_lds_fence();
     const float fnpx = (float)(npx > 0 ? npx : 1);  // exact: npx < 2^24
     float* dst = out + p * (int64_t)nb;
@@ -215,40 +232,52 @@ __global__ __launch_bounds__(64 * kHistWaves) void hist_patch48_kernel(PixelSour
   }
 }
 
-// Boxes and other patches: a workgroup each.  A box's size varies, and a wave
-// alone is bound by its loads' latency round after round (200 boxes of up to
-// 200 x 200: 38 us with a wave each, 20 / 12 with two / four); many boxes are
-// bound by how many a CU holds at once, times the same latency (40,000 of up to
-// 64 x 64: 43, 41 / 57).  So four waves while every box is resident at once, two
-// beyond.  20,000 boxes of up to 96 x 96: 47 -> 34 us.
-constexpr int64_t kRunBlocks = 1 << 20;
+// Boxes and larger unaligned patches: a workgroup each.
 template <int kSrc, int kThreads>
-__global__ __launch_bounds__(kThreads) void hist_runs_kernel(PixelSource src, int64_t n, int32_t bins, int32_t shift,
+__global__ __launch_bounds__(kThreads) void hist_runs_kernel(PixelSource src, int32_t bins, int32_t shift,
                                                              float* __restrict__ out) {
   extern __shared__ uint32_t lds_hist[];
   const int nb = bins * bins * bins;
-  for (int64_t p = blockIdx.x; p < n; p += gridDim.x) {
-    for (int b = threadIdx.x; b < nb; b += kThreads) lds_hist[b] = 0u;
-    __syncthreads();
-    const int npx = count_patch<kSrc, kThreads>(src, p, lds_hist, shift, bins, threadIdx.x);
-    __syncthreads();
-    const float fnpx = (float)(npx > 0 ? npx : 1);
-    float* dst = out + p * (int64_t)nb;
-    for (int b = threadIdx.x; b < nb; b += kThreads) dst[b] = (float)lds_hist[b] / fnpx;
-    __syncthreads();
-  }
+  const int64_t p = blockIdx.x;
+  for (int b = threadIdx.x; b < nb; b += kThreads) lds_hist[b] = 0u;
+  __syncthreads();
+  const Runs r = runs_of<kSrc>(src, p);
+  if (r.bad && threadIdx.x == 0) atomicOr(src.bad_box, 1);
+  if (r.rows) count_runs<kThreads>(lds_hist, r.base, r.pitch, r.cw, r.rows, shift, bins, threadIdx.x);
+  __syncthreads();
+  const float fnpx = (float)(r.rows ? r.cw * r.rows : 1);
+  float* dst = out + p * (int64_t)nb;
+  for (int b = threadIdx.x; b < nb; b += kThreads) dst[b] = (float)lds_hist[b] / fnpx;
 }
 
 template <int kSrc>
+static hipError_t launch_hist_patches(const PixelSource& src, int64_t n, int32_t bins, float* out, hipStream_t st,
+                                      int cu_count) {
+  const int64_t groups = (n + kHistWaves - 1) / kHistWaves, most = (int64_t)cu_count * 64;
+  const size_t lds = (size_t)kHistWaves * bins * bins * bins * sizeof(uint32_t);
+  hipLaunchKernelGGL(hist_patch_kernel<kSrc>, dim3((unsigned)(groups < most ? groups : most)), dim3(64 * kHistWaves),
+                     lds, st, src, n, bins, bin_shift(bins), out);
+  return hipGetLastError();
+}
+
+// A box's size varies and is known on the device alone.  A wave by itself is
+// bound by its loads' latency round after round (200 boxes of up to 200 x 200: 38
+// us with a wave each, 20 / 12 with two / four), many workgroups by their
+// launches and barriers.  So four waves a box while every box is resident at
+// once, two up to 160 boxes per CU, a wave each beyond: call time with two waves /
+// one, sides of up to 8, 96 and 200 pixels: 20,000 boxes 35 / 33 us, 48 / 54; 40,000
+// 46 / 41, 68 / 73, 117 / 143; 300,000 of up to 8 250 / 200, 16 254 / 203, 96 336 /
+// 346.
+template <int kSrc>
 static hipError_t launch_hist_runs(const PixelSource& src, int64_t n, int32_t bins, float* out, hipStream_t st,
                                    int cu_count) {
-  const dim3 grid((unsigned)(n < kRunBlocks ? n : kRunBlocks));
-  const size_t lds = bins * bins * bins * sizeof(uint32_t);
-  if (n <= (int64_t)cu_count * 8)
-    hipLaunchKernelGGL((hist_runs_kernel<kSrc, 256>), grid, dim3(256), lds, st, src, n, bins, bin_shift(bins), out);
-  else
-    hipLaunchKernelGGL((hist_runs_kernel<kSrc, 128>), grid, dim3(128), lds, st, src, n, bins, bin_shift(bins), out);
-  return hipGetLastError();
+  if (n > (int64_t)cu_count * 160) return launch_hist_patches<kSrc>(src, n, bins, out, st, cu_count);
+  auto go = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(threads), bins * bins * bins * sizeof(uint32_t), st, src, bins,
+                       bin_shift(bins), out);
+    return hipGetLastError();
+  };
+  return n <= (int64_t)cu_count * 8 ? go(hist_runs_kernel<kSrc, 256>, 256) : go(hist_runs_kernel<kSrc, 128>, 128);
 }
 
 // Histograms plus the join's operand prep of each histogram row (rows n..npad
@@ -301,16 +330,11 @@ hipError_t launch_hist_rgb8(const uint8_t* patches, int64_t n, int32_t h, int32_
                             float* out, hipStream_t st, int cu_count) {
   if (n == 0) return hipSuccess;
   const int32_t npx = h * w;
-  const int nb = bins * bins * bins;
-  const size_t lds = (size_t)kHistWaves * nb * sizeof(uint32_t);
-  const int64_t ngroups = (n + kHistWaves - 1) / kHistWaves;
-  const int grid = (int)(ngroups < (int64_t)cu_count * 64 ? ngroups : (int64_t)cu_count * 64);
   const PixelSource src{patches, h, w, nullptr, 0, nullptr};
-  if (npx % 16 != 0 || (reinterpret_cast<uintptr_t>(patches) & 15) != 0)
-    return launch_hist_runs<kSrcPatch>(src, n, bins, out, st, cu_count);
-  hipLaunchKernelGGL(hist_patch48_kernel, dim3(grid), dim3(64 * kHistWaves), lds, st, src, n, bins, bin_shift(bins),
-                     out);
-  return hipGetLastError();
+  if (npx % 16 == 0 && (reinterpret_cast<uintptr_t>(patches) & 15) == 0)
+    return launch_hist_patches<kSrcPatch48>(src, n, bins, out, st, cu_count);
+  if (npx <= kWaveArea) return launch_hist_patches<kSrcPatch>(src, n, bins, out, st, cu_count);
+  return launch_hist_runs<kSrcPatch>(src, n, bins, out, st, cu_count);
 }
 
 hipError_t launch_hist_crops(const uint8_t* frames, int64_t nframes, int32_t height, int32_t width,
