@@ -83,15 +83,6 @@ constexpr int dma_per_op(int rows_per_dma) { return kTile / rows_per_dma / dma_w
 // groups.  (Measured: this closed form, whose divisions by block-uniform
 // values compile to scalar code, beats carrying (group, offset) forward
 // with vector-unit 32-bit divisions.)
-// Division of a 32-bit block-uniform n by an invariant d through a
-// multiply-high and shifts (Granlund and Montgomery, "Division by Invariant
-// Integers using Multiplication", PLDI 1994): q = (t + ((n - t) >> s1)) >> s2
-// with t = mulhi(m, n); m, s1, s2 come from the host (div_magic).
-__device__ inline uint32_t udiv32(uint32_t n, uint32_t m, uint32_t s1, uint32_t s2) {
-  const uint32_t t = __umulhi(n, m);
-  return (t + ((n - t) >> s1)) >> s2;
-}
-
 __device__ inline bool tile_of(const CandParams& p, int64_t L, int64_t& ti, int64_t& tj) {
   const int64_t GM = p.GM;
   if (p.small32) {
@@ -1199,14 +1190,6 @@ int cand_group_rows(int64_t qld, int64_t nTR) { return group_rows(qld, nTR); }
 // Multiplier and shifts for udiv32 by d >= 1 (Granlund and Montgomery):
 // l = ceil(log2 d), m = floor(2^32 (2^l - d) / d) + 1, s1 = min(l, 1),
 // s2 = max(l - 1, 0); exact for every 32-bit dividend.
-static void div_magic(uint32_t d, uint32_t& m, uint32_t& s1, uint32_t& s2) {
-  uint32_t l = 0;
-  while (l < 32 && (1ull << l) < d) ++l;
-  m = (uint32_t)(((((1ull << l) - d) << 32) / d) + 1);
-  s1 = l < 1 ? l : 1;
-  s2 = l > 1 ? l - 1 : 0;
-}
-
 // eps mode over a device tile list (p.tiles, *p.ntiles entries): persistent
 // workgroups, one per CU, walk the list; mark = the bound pass (every tile).
 static hipError_t launch_eps_like(dl_prec prec, CandParams p, hipStream_t st, int cu_count, int mode);

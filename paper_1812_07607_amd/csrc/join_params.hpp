@@ -64,6 +64,22 @@ __host__ __device__ inline int64_t segment_end(int64_t cap, int s) {
   return s + 1 == kSegments ? cap : segment_first(cap, s + 1);
 }
 
+// Division of a 32-bit block-uniform n by an invariant d through a
+// multiply-high and shifts (Granlund and Montgomery, "Division by Invariant
+// Integers using Multiplication", PLDI 1994): q = (t + ((n - t) >> s1)) >> s2
+// with t = mulhi(m, n); m, s1, s2 come from the host (div_magic).
+__device__ inline uint32_t udiv32(uint32_t n, uint32_t m, uint32_t s1, uint32_t s2) {
+  const uint32_t t = __umulhi(n, m);
+  return (t + ((n - t) >> s1)) >> s2;
+}
+inline void div_magic(uint32_t d, uint32_t& m, uint32_t& s1, uint32_t& s2) {
+  uint32_t l = 0;
+  while (l < 32 && (1ull << l) < d) ++l;
+  m = (uint32_t)(((((1ull << l) - d) << 32) / d) + 1);
+  s1 = l < 1 ? l : 1;
+  s2 = l > 1 ? l - 1 : 0;
+}
+
 // Candidate pass on the matrix cores (join_mfma.hip).
 struct CandParams {
   const uint8_t* qa;   // R operand rows (qld bytes each, npad rows)
@@ -150,6 +166,7 @@ struct StreamParams {
   // go to gmax[(4 slot + quarter) * nR + row] (order keys).  strips = nslots *
   // slot_strips; step: octets of S per octet of the sample, in 2^-32.
   int stride, nslots, slot_strips, strips;
+  uint32_t dv_slot_m, dv_slot_s1, dv_slot_s2;  // division by slot_strips
   uint64_t step;
   uint32_t* gmax;
 };

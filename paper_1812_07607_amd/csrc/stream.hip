@@ -130,7 +130,7 @@ __device__ inline UnitAt stream_unit(const StreamParams& p, int64_t L) {
 // on (its outputs are dropped).
 __device__ inline uint32_t sample_row(const StreamParams& p, uint32_t t, uint32_t o) {
   if (t >= (uint32_t)p.strips) return 0;
-  const uint32_t q = t / (uint32_t)p.slot_strips;
+  const uint32_t q = udiv32(t, p.dv_slot_m, p.dv_slot_s1, p.dv_slot_s2);
   const uint32_t n = o * (uint32_t)p.strips + (t - q * (uint32_t)p.slot_strips) * (uint32_t)p.nslots + q;
   return 8 * (n * (uint32_t)(p.step >> 32) + __umulhi(n, (uint32_t)p.step));
 }
@@ -315,11 +315,12 @@ __global__ __launch_bounds__(kThreads, 1) void stream_kernel(StreamParams p) {
       else
         lds_dma16_at(src + (uint32_t)(row * kKB + c * 128 + piece * 16), dst + t * 1024);
     }
-    // four rows' values per lane
-    const int64_t j4 = kMax ? (int64_t)sample_row(p, t0 + (l >> 3), (l >> 1) & 3) + 4 * (l & 1) : j0 + 4 * l;
-    if (wave == 7 && l < G::kStageRows / 4) lds_dma16(p.c.hb + j4, side_h[buf]);
+    auto four = [&]() {  // the first of the lane's four rows
+      return kMax ? (int64_t)sample_row(p, t0 + (l >> 3), (l >> 1) & 3) + 4 * (l & 1) : j0 + 4 * l;
+    };
+    if (wave == 7 && l < G::kStageRows / 4) lds_dma16(p.c.hb + four(), side_h[buf]);
     if constexpr (kFp8)
-      if (wave == 6 && l < G::kStageRows / 4) lds_dma16(p.c.sexb + j4, side_s[buf]);
+      if (wave == 6 && l < G::kStageRows / 4) lds_dma16(p.c.sexb + four(), side_s[buf]);
     ++lu;
     if (++lst == p.nst) {
       ++lrb;
@@ -843,6 +844,7 @@ static void plan_sample(StreamParams& p, int64_t nS, int ngroups) {
   p.nslots = best;
   p.slot_strips = (int)(strips / best);
   p.strips = p.nslots * p.slot_strips;
+  div_magic((uint32_t)p.slot_strips, p.dv_slot_m, p.dv_slot_s1, p.dv_slot_s2);
   p.step = p.strips ? ((uint64_t)octets << 32) / (4 * (uint64_t)p.strips) : 0;
 }
 
