@@ -70,7 +70,8 @@ hipError_t launch_filter_pairs(const uint32_t*, const uint32_t*, const float*, i
 hipError_t launch_gather(const float*, int64_t, int, const uint32_t*, int64_t, float*, hipStream_t, int);
 hipError_t launch_remap(uint32_t*, uint32_t*, int64_t, const uint32_t*, const uint32_t*, hipStream_t, int);
 // sort.hip
-hipError_t launch_exclusive_scan(const uint32_t*, int64_t, uint32_t*, uint32_t*, hipStream_t);
+hipError_t launch_exclusive_scan(const uint32_t*, int64_t, uint32_t*, uint32_t*, hipStream_t,
+                                 const unsigned long long* some = nullptr);
 int64_t scan_scratch_words(int64_t);
 hipError_t launch_cand_band(dl_prec, CandParams, hipStream_t);
 hipError_t launch_recheck_eps(const RecheckParams&, hipStream_t, int);

@@ -18,7 +18,8 @@
 
 namespace dl {
 
-hipError_t launch_exclusive_scan(const uint32_t* in, int64_t n, uint32_t* out, uint32_t* sums, hipStream_t st);
+hipError_t launch_exclusive_scan(const uint32_t* in, int64_t n, uint32_t* out, uint32_t* sums, hipStream_t st,
+                                 const unsigned long long* some = nullptr);
 int64_t scan_scratch_words(int64_t n);
 
 constexpr int kPlanThreads = 256;
