@@ -38,6 +38,7 @@ hipError_t launch_cand_eps(dl_prec, CandParams, hipStream_t, int);
 hipError_t launch_cand_list(dl_prec, CandParams, hipStream_t, int);
 bool stream_applies(dl_prec, int64_t, int64_t, int64_t);
 hipError_t launch_stream_eps(dl_prec, const CandParams&, int64_t, hipStream_t, int);
+bool few_tiles(int64_t, int64_t, bool, int);
 bool stream_band_applies(int64_t, int);
 int64_t stream_band_room(dl_prec, int64_t, int64_t, int);
 hipError_t launch_stream_band(dl_prec, const CandParams&, int64_t, int, int64_t, uint32_t*, hipStream_t, int);
@@ -637,7 +638,7 @@ dl_status eps_core(dl_ctx* c, const EpsJob& J, void* ws, size_t ws_bytes, dl_pai
   }
   // The streaming pass's part counters lie where the ordering puts its row
   // offsets later (few rows: one counter does).
-  const bool stream = stream_applies(prec, L.pr.qld, R.n, S.n);
+  const bool stream = stream_applies(prec, L.pr.qld, R.n, S.n) && !few_tiles(R.n, S.n, self, c->cu_count);
   const int64_t at_seg = round_up(R.n + 1, 32);
   const bool parts = stream && at_seg + 2 * kSegWords * kSegments <= 2 * (R.n + 1);
   unsigned long long* const seg = parts ? reinterpret_cast<unsigned long long*>(L.rows + at_seg) : nullptr;

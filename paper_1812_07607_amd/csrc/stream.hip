@@ -699,6 +699,25 @@ bool stream_applies(dl_prec prec, int64_t qld, int64_t nR, int64_t nS) {
          (double)nR * (double)nS < 0x1p51;
 }
 
+// Whether an eps-join's pass is left to the tile form, having few tiles of 256 x
+// 256: where every tile has a CU of its own that form is a load of two tiles and
+// one epilogue, and the streaming pass has its R fragments to load and its ring
+// to fill first (12.5 us of pass against 24.4 at 3,000 x 3,000, d = 256, no
+// candidates).  Call time, tile form over streaming, d = 128, bf16, no pairs and 5
+// a row: 2,560 x 2,560 (100 tiles) 0.84 and 0.97, 4,000 x 4,000 (256) 0.83 and
+// 0.96, 300 x 30,000 (236) 0.82 and 0.92.  With more tiles than CUs the pairs make
+// up for it: 6,000 x 6,000 (576) 0.91 and 1.01.  So they do where the form leaves
+// CUs idle over the candidates' staging, with few tiles (1,100 x 1,100, 25: 0.91
+// and 1.04; 2,600 to itself, 66: 0.91 and 1.03), or with an R much longer than S,
+// whose candidates sit in few columns (20,000 x 300: 0.90 and 1.05), and earlier in
+// self-joins, half of whose diagonal tiles is dropped (4,000, 136: 0.90 and 0.98;
+// 5,500, 253: 0.87 and 0.99, E4M3 1.08).
+bool few_tiles(int64_t nR, int64_t nS, bool self, int cu_count) {
+  const int64_t tr = (nR + kTile - 1) / kTile, ts = (nS + kTile - 1) / kTile;
+  const int64_t tiles = self ? tr * (tr + 1) / 2 : tr * ts;
+  return tiles > cu_count * 3 / 8 && tiles <= (self ? cu_count * 5 / 8 : cu_count) && tr <= 4 * ts;
+}
+
 template <int kPrec, int kKB, int kMode>
 static hipError_t launch_stream_kb(StreamParams p, int64_t npad_r, hipStream_t st, int cu_count) {
   using G = StreamGeom<kPrec, kKB>;
