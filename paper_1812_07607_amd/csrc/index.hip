@@ -160,7 +160,6 @@ __global__ __launch_bounds__(64 * kBallWaves) void block_ball_q_kernel(const uin
   const int64_t b = blockIdx.x;
   const int64_t r0 = b * kTile;
   const int rows = (int)min((int64_t)kTile, n - r0);
-  const int dpad = (int)(qld / kElem);
   const uint8_t* base = q + r0 * qld;
   for (int r = threadIdx.x; r < rows; r += blockDim.x)
     scale_lds[r] = kPrec == DL_FP8 ? ldexpf(1.0f, sexp[r0 + r]) : 1.0f;

@@ -35,10 +35,8 @@ __device__ inline uint32_t block_exclusive_scan(uint32_t v, uint32_t* lds_w, uin
   return off + x - v;
 }
 
-__global__ __launch_bounds__(kScanThreads) void scan_reduce_kernel(const uint32_t* in, int64_t n, uint32_t* sums,
-                                                                   const unsigned long long* some) {
+__global__ __launch_bounds__(kScanThreads) void scan_reduce_kernel(const uint32_t* in, int64_t n, uint32_t* sums) {
   __shared__ uint32_t lw[kScanThreads / 64];
-  if (some && *some == 0) return;
   const int64_t base = (int64_t)blockIdx.x * kScanChunk;
   uint32_t s = 0;
   for (int t = 0; t < kScanItems; ++t) {
@@ -78,7 +76,9 @@ __global__ __launch_bounds__(kScanThreads) void scan_apply_kernel(const uint32_t
     before = sums[blockIdx.x];
   } else if (!sums) {
     uint32_t x = 0;
-    for (int t = threadIdx.x; t < (int)blockIdx.x * kScanChunk; t += kScanThreads) x += in[t];
+    for (int c = 0; c < (int)blockIdx.x; ++c)
+#pragma unroll
+      for (int t = 0; t < kScanItems; ++t) x += in[c * kScanChunk + t * kScanThreads + threadIdx.x];
     block_exclusive_scan(x, lw, before);
   } else if (blockIdx.x > 0) {
     uint32_t x = 0;
@@ -107,18 +107,19 @@ int64_t scan_scratch_words(int64_t n) { return (n + kScanChunk - 1) / kScanChunk
 // One launch for up to kScanSelf chunks, whose entries a workgroup adds up for
 // itself, and two up to kScanFlat, whose sums it adds up (a few loads a thread,
 // where a launch costs about 5 us: 5,000 rows 10.8 us in two, 7.0 in one); three
-// beyond, where that would grow quadratically.  some (nullable): nothing is done
-// where it holds zero.
+// beyond, where that would grow quadratically.  some (nullable): a scan of one
+// launch does nothing where it holds zero (the wait for it costs each launch of a
+// longer one a microsecond).
 constexpr int64_t kScanSelf = 4, kScanFlat = 4096;
 hipError_t launch_exclusive_scan(const uint32_t* in, int64_t n, uint32_t* out, uint32_t* sums, hipStream_t st,
                                  const unsigned long long* some) {
   if (n == 0) return hipSuccess;
   const int64_t nb = (n + kScanChunk - 1) / kScanChunk;
-  if (nb > kScanSelf)
-    hipLaunchKernelGGL(scan_reduce_kernel, dim3((unsigned)nb), dim3(kScanThreads), 0, st, in, n, sums, some);
+  const bool one = nb <= kScanSelf;
+  if (!one) hipLaunchKernelGGL(scan_reduce_kernel, dim3((unsigned)nb), dim3(kScanThreads), 0, st, in, n, sums);
   if (nb > kScanFlat) hipLaunchKernelGGL(scan_top_kernel, dim3(1), dim3(1024), 0, st, sums, nb);
-  hipLaunchKernelGGL(scan_apply_kernel, dim3((unsigned)nb), dim3(kScanThreads), 0, st, in, n,
-                     nb > kScanSelf ? sums : nullptr, nb > kScanFlat, out, some);
+  hipLaunchKernelGGL(scan_apply_kernel, dim3((unsigned)nb), dim3(kScanThreads), 0, st, in, n, one ? nullptr : sums,
+                     nb > kScanFlat, out, one ? some : nullptr);
   return hipGetLastError();
 }
 
