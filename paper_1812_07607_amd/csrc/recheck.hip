@@ -561,9 +561,11 @@ __global__ __launch_bounds__(64 * kSelWaves, kSelMax == kSelSmall && kSelRegs ==
     fence();
   };
   bool listed = kept <= kList, done = false;
+  const bool known = listed;  // v, and from it bt and th
+  float bt = -INFINITY, th = -INFINITY;
   if (listed) {
     // (2) the band P~ >= bt, and the list: first the entries at or above v
-    const float bt = v ? f32_down((double)key_float(v) - (double)p.marg[i]) : -INFINITY;
+    if (v) bt = f32_down((double)key_float(v) - (double)p.marg[i]);
     fence();
     int nl = 0;
 #pragma unroll
@@ -574,7 +576,7 @@ __global__ __launch_bounds__(64 * kSelWaves, kSelMax == kSelSmall && kSelRegs ==
         nl += __popcll(m);
       }
     const int na = nl;
-    float th = bt;
+    th = bt;
     if (v) {
       // their largest d2 bounds the k-th distance: D, rounded up
       distances(0, na);
@@ -699,7 +701,7 @@ __global__ __launch_bounds__(64 * kSelWaves, kSelMax == kSelSmall && kSelRegs ==
   double* ck = reinterpret_cast<double*>(s_buf[wave] + 8 * kSelMax);
   if (!listed) {
     // a union or list too large for the above: the same steps over the split
-    // buffers in memory, with the band alone
+    // buffers in memory, with the band refined where its k-th largest P~ was found
     auto count = [&](auto pred) {
       int c = 0;
       for (int s = 0; s < p.P; ++s) {
@@ -713,18 +715,18 @@ __global__ __launch_bounds__(64 * kSelWaves, kSelMax == kSelSmall && kSelRegs ==
       return c;
     };
     if (!in_d2) {
-      float bt = -INFINITY;
-      if (total >= k) {
+      if (!known && total >= k) {
         uint32_t t = 0;
         for (int b = 31; b >= 0; --b) {
           const uint32_t cand = t | (1u << b);
           if (count([&](uint32_t w) { return ord_f(__uint_as_float(w)) >= cand; }) >= k) t = cand;
         }
         const float pk = __uint_as_float((t & 0x80000000u) ? (t & 0x7fffffffu) : ~t);
-        bt = f32_down((double)pk - (double)p.marg[i]);
+        bt = th = f32_down((double)pk - (double)p.marg[i]);
       }
-      // each entry's P~ is replaced by its float32 d2 (+inf outside the
-      // band): the steps below, and any later selection of the row, read that
+      // each entry's P~ is replaced by its float32 d2 (+inf outside the band, and
+      // what no d2 reaches in the band but not the refined one): the steps below,
+      // and any later selection of the row, read that
       for (int s = 0; s < p.P; ++s) {
         uint2* e = p.band + (i * p.P + s) * (int64_t)p.cap;
         const int n = band_count(p, i * p.P + s);
@@ -732,8 +734,8 @@ __global__ __launch_bounds__(64 * kSelWaves, kSelMax == kSelSmall && kSelRegs ==
           const int t = base + lane;
           const uint2 v = t < n ? e[t] : make_uint2(0, 0);
           const bool inband = t < n && __uint_as_float(v.x) >= bt;
-          float d2 = INFINITY;
-          if (inband) d2 = lane_d2(a, p.S + (int64_t)v.y * p.lds, p.d, vec4);
+          float d2 = inband ? 0x1.fffffep127f : INFINITY;
+          if (inband && __uint_as_float(v.x) >= th) d2 = lane_d2(a, p.S + (int64_t)v.y * p.lds, p.d, vec4);
           if (t < n) e[t].x = __float_as_uint(d2);
           nb += __popcll(__ballot(inband));
         }
