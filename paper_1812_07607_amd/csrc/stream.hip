@@ -51,6 +51,7 @@
 // what bounds the pass: letting the two waves of a SIMD test in turns, or
 // meeting a barrier every second stage only, changed nothing (the clock gives
 // what the stalls no longer take).
+#include <algorithm>
 #include <type_traits>
 
 #include "cand_device.hpp"
@@ -817,9 +818,16 @@ static int sample_stride(dl_prec prec, int64_t nR, int64_t nS, int k) {
 // above the bound.  The fullest of 1,024 rows, random mixtures (d = 128, bf16):
 // k = 10, stride 8: 255 entries; 50, 4: 550; 100, 3: 507; 256, 2: 845; 10, 28
 // (8M rows): 1,272; S in order of its centres: 10, 8: 587; 50, 4: 1,059; 256, 2:
-// 2,105.  E4M3's margin holds 980 of its own at d = 256, k = 32.
+// 2,105.  E4M3's margin holds a row's whole neighbourhood (980 entries at d = 256, k
+// = 32, 1,000 rows a centre; 2,960 at d = 128 and 3,000): room for a thirty-second of
+// S, up to 4,096 (65,536 x 4,000, k = 10: 0.59 ms; in blocks 0.87).  A sample of every
+// row leaves less: buffers of 1,024 held k = 100 to 127 of 65,536 x 2,100 to 20,000
+// rows (16 bits, d = 64 and 256, 3 to 1,000 centres, in order and not), where two
+// blocks cost 5% (k = 100 of 65,536 x 4,000: 1.85 ms, 1.95).
 int64_t stream_band_room(dl_prec prec, int64_t nR, int64_t nS, int k) {
-  const int64_t room = 6 * (int64_t)k * sample_stride(prec, nR, nS, k) + (prec == DL_FP8 ? 4096 : 512);
+  const int stride = sample_stride(prec, nR, nS, k);
+  const int64_t margin = prec == DL_FP8 ? std::clamp<int64_t>(nS / 32, 512, 4096) : 512;
+  const int64_t room = (stride == 1 ? 4 : 6) * (int64_t)k * stride + margin;
   return room < nS ? room : nS;
 }
 
