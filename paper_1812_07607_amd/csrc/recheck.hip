@@ -561,11 +561,9 @@ __global__ __launch_bounds__(64 * kSelWaves, kSelMax == kSelSmall && kSelRegs ==
     fence();
   };
   bool listed = kept <= kList, done = false;
-  const bool known = listed;  // v, and from it bt and th
-  float bt = -INFINITY, th = -INFINITY;
   if (listed) {
     // (2) the band P~ >= bt, and the list: first the entries at or above v
-    if (v) bt = f32_down((double)key_float(v) - (double)p.marg[i]);
+    const float bt = v ? f32_down((double)key_float(v) - (double)p.marg[i]) : -INFINITY;
     fence();
     int nl = 0;
 #pragma unroll
@@ -576,7 +574,7 @@ __global__ __launch_bounds__(64 * kSelWaves, kSelMax == kSelSmall && kSelRegs ==
         nl += __popcll(m);
       }
     const int na = nl;
-    th = bt;
+    float th = bt;
     if (v) {
       // their largest d2 bounds the k-th distance: D, rounded up
       distances(0, na);
@@ -694,7 +692,13 @@ __global__ __launch_bounds__(64 * kSelWaves, kSelMax == kSelSmall && kSelRegs ==
         }
       }
     } else {
-      nb = 0;
+      nb = -1;  // (the thresholds found are left in LDS)
+      fence();
+      if (lane == 0) {
+        reinterpret_cast<float*>(s_buf[wave])[0] = bt;
+        reinterpret_cast<float*>(s_buf[wave])[1] = th;
+      }
+      fence();
     }
   }
   cd = reinterpret_cast<float*>(s_buf[wave] + 4 * kSelMax);
@@ -715,7 +719,12 @@ __global__ __launch_bounds__(64 * kSelWaves, kSelMax == kSelSmall && kSelRegs ==
       return c;
     };
     if (!in_d2) {
-      if (!known && total >= k) {
+      float bt = -INFINITY, th = -INFINITY;
+      if (nb < 0) {
+        bt = reinterpret_cast<const float*>(s_buf[wave])[0];
+        th = reinterpret_cast<const float*>(s_buf[wave])[1];
+        nb = 0;
+      } else if (total >= k) {
         uint32_t t = 0;
         for (int b = 31; b >= 0; --b) {
           const uint32_t cand = t | (1u << b);
