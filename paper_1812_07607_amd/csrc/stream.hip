@@ -58,6 +58,9 @@
 
 namespace dl {
 
+hipError_t launch_zero_ranges(uint32_t*, int64_t, uint32_t*, int64_t, uint32_t*, int64_t, uint32_t*, int64_t,
+                              hipStream_t, int);
+
 template <int kPrec, int kKB>
 struct StreamGeom {
   static constexpr int kSteps = kKB / 64;                   // 16-byte pieces per lane and 16 rows
@@ -688,10 +691,6 @@ __global__ __launch_bounds__(64) void band_key_kernel(const uint32_t* __restrict
     gkey[i] = max(gkey[i], order_key(f32_down((double)key_float(v) - (double)marg[i])));
 }
 
-__global__ void fill_zero_kernel(uint32_t* p, int64_t n) {
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) p[t] = 0;
-}
-
 // Whether the pass takes rows of qld operand bytes: as many R fragments as
 // registers hold.  float32 candidates stay with the tile form (its rate is the
 // matrix cores' own there).  The unit count of a workgroup is 32-bit.
@@ -896,7 +895,8 @@ hipError_t launch_stream_band(dl_prec prec, const CandParams& c, int64_t npad_r,
     plan_sample(p, c.nS, stream_groups(k));
     const int ng = 4 * p.nslots;
     p.gmax = gmax;
-    hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)(cu_count * 4)), dim3(256), 0, st, gmax, ng * c.nR);
+    if ((e = launch_zero_ranges(gmax, ng * c.nR, nullptr, 0, nullptr, 0, nullptr, 0, st, cu_count)) != hipSuccess)
+      return e;
     if ((e = launch_stream<kStreamMax>(prec, p, npad_r, st, cu_count)) != hipSuccess) return e;
     if ((e = launch_band_key(gmax, ng, c.nR, k, c.marg, c.gkey, st, cu_count)) != hipSuccess) return e;
   }
