@@ -207,9 +207,12 @@ static int bin_shift(int bins) {
 
 // Histograms only: bin / pixel count, rounded once (IEEE division).  A wave per
 // patch: aligned patches, others of at most kWaveArea pixels (a workgroup of two
-// waves each: 200,000 of 5 x 7, 8 / 4 bins, 141 / 78 us against 93 / 27; 60,000 of 31
-// x 33 80 against 72), and boxes that are many.
-constexpr int kWaveArea = 1024;
+// waves each: 200,000 of 5 x 7, 8 / 4 bins, 141 / 78 us against 93 / 26; 60,000 of 31
+// x 33 60 against 53), and boxes that are many.  Not with more than kWaveBins bins a
+// channel, unless the loads are aligned: LDS holds eight histograms of 16 KiB a CU so,
+// ten workgroups the other way (16 bins: 200,000 of 5 x 7 605 us against 775, 60,000 of
+// 31 x 33 203 against 278).
+constexpr int kWaveArea = 1024, kWaveBins = 8;
 template <int kSrc>
 __global__ __launch_bounds__(64 * kHistWaves) void hist_patch_kernel(PixelSource src, int64_t n, int32_t bins,
                                                                    int32_t shift, float* __restrict__ out) {
@@ -266,12 +269,13 @@ static hipError_t launch_hist_patches(const PixelSource& src, int64_t n, int32_t
 // launches and barriers.  So four waves a box while every box is resident at
 // once, two up to 160 boxes per CU, a wave each beyond: call time with two waves /
 // one, sides of up to 8, 96 and 200 pixels: 20,000 boxes 35 / 33 us, 48 / 54; 40,000
-// 46 / 41, 68 / 73, 117 / 143; 300,000 of up to 8 250 / 200, 16 254 / 203, 96 336 /
-// 346.
+// 46 / 41, 68 / 73, 117 / 143; 45,000 50 / 41, 106 / 111, 274 / 314; 300,000 of up to
+// 8 265 / 187, 16 270 / 194, 96 535 / 567.
 template <int kSrc>
 static hipError_t launch_hist_runs(const PixelSource& src, int64_t n, int32_t bins, float* out, hipStream_t st,
                                    int cu_count) {
-  if (n > (int64_t)cu_count * 160) return launch_hist_patches<kSrc>(src, n, bins, out, st, cu_count);
+  if (n > (int64_t)cu_count * 160 && (bins <= kWaveBins || n > (1 << 24)))  // (a launch holds 2^32 threads)
+    return launch_hist_patches<kSrc>(src, n, bins, out, st, cu_count);
   auto go = [&](auto kernel, int threads) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(threads), bins * bins * bins * sizeof(uint32_t), st, src, bins,
                        bin_shift(bins), out);
@@ -333,7 +337,7 @@ hipError_t launch_hist_rgb8(const uint8_t* patches, int64_t n, int32_t h, int32_
   const PixelSource src{patches, h, w, nullptr, 0, nullptr};
   if (npx % 16 == 0 && (reinterpret_cast<uintptr_t>(patches) & 15) == 0)
     return launch_hist_patches<kSrcPatch48>(src, n, bins, out, st, cu_count);
-  if (npx <= kWaveArea) return launch_hist_patches<kSrcPatch>(src, n, bins, out, st, cu_count);
+  if (npx <= kWaveArea && bins <= kWaveBins) return launch_hist_patches<kSrcPatch>(src, n, bins, out, st, cu_count);
   return launch_hist_runs<kSrcPatch>(src, n, bins, out, st, cu_count);
 }
 
