@@ -21,8 +21,8 @@
  *     finished.  "host" pointers are read or written before the call returns.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     All GPU work of a call is enqueued on it.  A call that reports a count
- *     synchronises the stream before returning; other results are ready when
- *     the stream reaches the end of the call's work.
+ *     waits for that count before returning; its device arrays, like other
+ *     results, are ready when the stream reaches the end of the call's work.
  *   - No call allocates device memory except where stated: scratch memory is
  *     the caller's `ws` buffer, sized by the matching *_workspace query.
  *     Workspaces, store memory and server arenas must be 256-byte aligned
@@ -189,7 +189,10 @@ size_t dl_join_eps_workspace(int64_t nR, int64_t nS, int32_t d, dl_prec prec,
  * (i, j) order are written, out->count holds the total), DL_ERR_WORKSPACE if
  * the candidates exceed what ws holds (dl_required_workspace() gives the
  * bytes that would have sufficed), DL_ERR_INVALID for bad shapes or a
- * non-finite value in R or S.  Synchronises `stream`. */
+ * non-finite value in R or S.  Waits for the counts: on DL_OK with pairs the
+ * ordering may still run on `stream` (its arrays, R, S and ws belong to the
+ * stream until then); without pairs and on every error but DL_ERR_DEVICE the
+ * stream is idle. */
 dl_status dl_join_eps(dl_ctx* ctx, dl_mat R, dl_mat S, int self_join,
                       double eps, dl_prec prec, void* ws, size_t ws_bytes,
                       dl_pairs* out, void* stream);
@@ -213,7 +216,7 @@ size_t dl_required_workspace(const dl_ctx* ctx);
  * fit beside them, returns DL_ERR_WORKSPACE at once (dl_last_error says how
  * much it needs; dl_required_workspace() gives 0: use dl_join_eps with a
  * workspace instead), and DL_ERR_DEVICE if the scratch could not be set up
- * on the context's device.  Synchronises `stream`. */
+ * on the context's device.  Waits as dl_join_eps does. */
 #define DL_NOALLOC_SCRATCH_BYTES ((size_t)64 << 20)
 dl_status dl_join_eps_noalloc(dl_ctx* ctx, dl_mat R, dl_mat S, int self_join,
                               double eps, dl_prec prec, dl_pairs* out,
@@ -255,7 +258,7 @@ size_t dl_join_eps_indexed_workspace(int64_t nR, int64_t nS, int32_t d,
  * points to: the rows of one cluster share few nonzero histogram bins).
  * Without a finite eps, or with a relation under 512 rows, it runs as
  * dl_join_eps.  info (host, nullable) reports the tiles and K-steps
- * computed.  Synchronises `stream`. */
+ * computed.  Waits as dl_join_eps does. */
 dl_status dl_join_eps_indexed(dl_ctx* ctx, dl_mat R, dl_mat S, int self_join,
                               double eps, dl_prec prec, int32_t pivots,
                               void* ws, size_t ws_bytes, dl_pairs* out,
@@ -303,7 +306,8 @@ typedef struct dl_topk_info {
 /* Scratch bytes for dl_join_topk with `band_cap` band entries per row and
  * S-split (0 = library default).  For DL_FP8 (not self-joins, nS at least
  * 4,096 rows) this includes an exact bf16 pilot top-k against every 16th row
- * of S, whose k-th distances seed the E4M3 band thresholds. */
+ * of S, whose k-th distances seed the E4M3 band thresholds where the join runs
+ * in tiles (rows of more than 512 operand bytes, or bands that overflow). */
 size_t dl_join_topk_workspace(int64_t nR, int64_t nS, int32_t d, dl_prec prec,
                               int self_join, int32_t k, int32_t band_cap);
 

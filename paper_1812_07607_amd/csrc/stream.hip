@@ -41,16 +41,16 @@
 // R-major; each workgroup takes one contiguous, equal share of the units, so
 // no last round is part empty and R changes only a few times per workgroup.
 // (Workgroups of one XCD walking S in step, so that its L2 serves them all,
-// gained 1% on the 10^6-row join and lost the even shares: S is read at 2.4
-// TB/s in all, which HBM gives.)
+// gained 1% on the 10^6-row join and lost the even shares: S is read once for
+// each block of 1,024 rows of R, 250 GB there, 1.5 TB/s, which HBM gives.)
 //
-// Measured (one MI355X): the 10^6 x 10^6, d = 128, bf16 pass 158 ms (1.62
-// PFLOP/s) against the tile form's 238 ms; a loop of the same matrix
-// instructions and LDS reads alone, on such operands, runs at 1.94 PFLOP/s.
-// The matrix cores are busy 69% of the time at 2.25 GHz; what idles them is not
-// what bounds the pass: letting the two waves of a SIMD test in turns, or
-// meeting a barrier every second stage only, changed nothing (the clock gives
-// what the stalls no longer take).
+// Measured (one MI355X): the 10^6 x 10^6, d = 128, bf16 pass 158 to 169 ms on the
+// cards seen (1.62 to 1.52 PFLOP/s) against the tile form's 238 ms; a loop of the
+// same matrix instructions and LDS reads alone, on such operands, runs at 1.94
+// PFLOP/s.  The matrix cores are busy 68% of the time at 2.13 GHz (168 ms); what
+// idles them is not what bounds the pass: letting the two waves of a SIMD test in
+// turns, or meeting a barrier every second stage only, changed nothing (the clock
+// gives what the stalls no longer take).
 #include <algorithm>
 #include <type_traits>
 
