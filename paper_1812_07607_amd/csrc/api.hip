@@ -41,7 +41,8 @@ hipError_t launch_stream_eps(dl_prec, const CandParams&, int64_t, hipStream_t, i
 bool few_tiles(int64_t, int64_t, bool, int);
 bool stream_band_applies(int64_t, int);
 int64_t stream_band_room(dl_prec, int64_t, int64_t, int);
-hipError_t launch_stream_band(dl_prec, const CandParams&, int64_t, int, int64_t, uint32_t*, hipStream_t, int);
+hipError_t launch_stream_keys(dl_prec, const CandParams&, int64_t, int, uint32_t*, hipStream_t, int);
+hipError_t launch_stream_band(dl_prec, const CandParams&, int64_t, int64_t, hipStream_t, int);
 hipError_t launch_cand_mark(dl_prec, CandParams, hipStream_t, int);
 hipError_t launch_cand_nearest(dl_prec, CandParams, hipStream_t, int);
 // index.hip
@@ -741,8 +742,8 @@ dl_status topk_core(dl_ctx* c, const TopkJob& J, void* ws, size_t ws_bytes, uint
   // sample tells), the tile form, which tightens as it goes, runs after it.
   // Where P buffers are too few for what the sample leaves (P is 1 for about a
   // sixth of the row counts up to 200,000), R goes in blocks, each with the
-  // whole band memory: a block costs its launches and a wait (about 50 us), an
-  // overflow a pass.  Top-10 of 65,536 rows against 8M, d = 128, bf16 (the
+  // whole band memory: a block costs its launches, a wait and the ends of its
+  // kernels (0.05 to 0.15 ms), an overflow a pass.  Top-10 of 65,536 rows against 8M, d = 128, bf16 (the
   // fullest of 1,024 rows had 1,270 entries, the buffer 1,024): 223 ms with the
   // tile form after the pass, 93 in three blocks.
   const int kk = k + (excl ? 1 : 0);
@@ -849,9 +850,15 @@ dl_status topk_core(dl_ctx* c, const TopkJob& J, void* ws, size_t ws_bytes, uint
       p.gate = &L.cnt->invalid;
       p.cap = (int)cap;
       if (stream) {
-        // (the group maxima lie in the band's memory, which is written later)
-        DL_HIP(c, launch_stream_band(prec, p, L.pr.npad - r0, kk, r0, reinterpret_cast<uint32_t*>(L.band), st,
-                                     c->cu_count));
+        if (r0 == 0) {
+          // all rows' thresholds at once: a sample of a block's rows alone leaves
+          // the chip idle at its ends (the group maxima lie in the band's memory,
+          // which is written later)
+          p.nR = R.n;
+          DL_HIP(c, launch_stream_keys(prec, p, L.pr.npad, kk, reinterpret_cast<uint32_t*>(L.band), st, c->cu_count));
+          p.nR = n;
+        }
+        DL_HIP(c, launch_stream_band(prec, p, L.pr.npad - r0, r0, st, c->cu_count));
       } else {
         p.P = P;
         p.k = k;

@@ -42,7 +42,7 @@
 // no last round is part empty and R changes only a few times per workgroup.
 // (Workgroups of one XCD walking S in step, so that its L2 serves them all,
 // gained 1% on the 10^6-row join and lost the even shares: S is read once for
-// each block of 1,024 rows of R, 250 GB there, 1.5 TB/s, which HBM gives.)
+// each block of 1,024 rows of R, 250 GB there, 1.5 to 1.6 TB/s, which HBM gives.)
 //
 // Measured (one MI355X): the 10^6 x 10^6, d = 128, bf16 pass 158 to 169 ms on the
 // cards seen (1.62 to 1.52 PFLOP/s) against the tile form's 238 ms; a loop of the
@@ -874,32 +874,37 @@ static void plan_sample(StreamParams& p, int64_t nS, int ngroups) {
   p.step = p.strips ? ((uint64_t)octets << 32) / (4 * (uint64_t)p.strips) : 0;
 }
 
-// Top-k band of every row of R: the group maxima of a sample of S give each
-// row's threshold, then the pass over all of S stages what reaches it.  gmax:
-// scratch of stream_groups(k) * nR words.  c.gkey holds what bounds are known
-// (order keys), c.bcount zeros; c's row 0 is R's row first_row.
+// Thresholds of the top-k band of every row of R: its k-th largest group maximum
+// over a sample of S.  gmax: scratch of stream_groups(k) * nR words.  c.gkey holds
+// what bounds are known (order keys).
+hipError_t launch_stream_keys(dl_prec prec, const CandParams& c, int64_t npad_r, int k, uint32_t* gmax, hipStream_t st,
+                              int cu_count) {
+  if (c.nR == 0 || c.nS <= kAllRows) return hipSuccess;
+  StreamParams p{};
+  p.c = c;
+  p.c.self_join = 0;
+  p.stride = sample_stride(prec, c.nR, c.nS, k);
+  plan_sample(p, c.nS, stream_groups(k));
+  const int ng = 4 * p.nslots;
+  p.gmax = gmax;
+  hipError_t e = launch_zero_ranges(gmax, ng * c.nR, nullptr, 0, nullptr, 0, nullptr, 0, st, cu_count);
+  if (e != hipSuccess) return e;
+  if ((e = launch_stream<kStreamMax>(prec, p, npad_r, st, cu_count)) != hipSuccess) return e;
+  return launch_band_key(gmax, ng, c.nR, k, c.marg, c.gkey, st, cu_count);
+}
+
+// Top-k band of rows of R whose thresholds are known: the pass over all of S
+// stages what reaches them.  c.bcount: zeros; c's row 0 is R's row first_row.
 //
 // Measured (one MI355X): top-10 of 200,000 x 200,000, d = 128, bf16: sample
 // 0.85 ms, thresholds 0.05, pass 7.9, against 21.4 ms for the tile form, whose
 // bands are tightened row by row inside the pass.
-hipError_t launch_stream_band(dl_prec prec, const CandParams& c, int64_t npad_r, int k, int64_t first_row,
-                              uint32_t* gmax, hipStream_t st, int cu_count) {
+hipError_t launch_stream_band(dl_prec prec, const CandParams& c, int64_t npad_r, int64_t first_row, hipStream_t st,
+                              int cu_count) {
   StreamParams p{};
   p.c = c;
   p.c.self_join = 0;
   p.first_row = (uint32_t)first_row;
-  if (c.nR == 0 || c.nS == 0) return hipSuccess;
-  hipError_t e;
-  if (c.nS > kAllRows) {
-    p.stride = sample_stride(prec, c.nR, c.nS, k);
-    plan_sample(p, c.nS, stream_groups(k));
-    const int ng = 4 * p.nslots;
-    p.gmax = gmax;
-    if ((e = launch_zero_ranges(gmax, ng * c.nR, nullptr, 0, nullptr, 0, nullptr, 0, st, cu_count)) != hipSuccess)
-      return e;
-    if ((e = launch_stream<kStreamMax>(prec, p, npad_r, st, cu_count)) != hipSuccess) return e;
-    if ((e = launch_band_key(gmax, ng, c.nR, k, c.marg, c.gkey, st, cu_count)) != hipSuccess) return e;
-  }
   return launch_stream<kStreamBand>(prec, p, npad_r, st, cu_count);
 }
 
